@@ -105,14 +105,16 @@ int zero_partition_layout(int64_t total_numel, int32_t nd, int32_t rank, zero_la
  * caller then lowers its loss scale and does not advance t.
  *
  * All five arrays must be distinct, non-overlapping ranges; base pointers of
- * any element alignment are accepted (when all five share one misalignment
- * the vectorised path runs after a few scalar head elements).  Placement
+ * any element alignment are accepted, each its own: the step runs on
+ * 4-element vectors from the first 128-byte line of master32, and the other
+ * arrays' vectors may be unaligned (fp16 slices of flat buffers at any
+ * rank * S cost about 5 %).  Placement
  * affects speed, not results: separate allocations, or arrays packed into one
  * buffer each on its own 2 MiB boundary, run fastest; arrays offset from one
  * another by a few hundred bytes run about 5 % slower.  Shards small enough
  * for one resident grid (a quarter of the device's co-resident capacity for
  * the kernel, or 1/q with q = GPU_MAX_HW_QUEUES when that is larger: about
- * 1.5 million elements on MI355X with the default four queues) whose arrays share one
+ * 1.5 million elements on MI355X with the default four queues) whose fp32 arrays share one
  * misalignment take a single launch (statistics, a grid barrier and the
  * update in one kernel, the gradient read once); larger ones take the
  * statistics kernels and the update kernel.  The barrier relies on the whole

@@ -89,6 +89,10 @@ int lock_ctx(hipStream_t stream, CtxLock* out);
 uint32_t next_seq(Ctx* ctx);
 
 bool is_fin(double x);
+
+// Elements of `size` bytes before the first cache line that starts in the array.
+int64_t line_head(const void* p, size_t size);
+
 bool overlaps(uintptr_t a, size_t an, uintptr_t b, size_t bn);
 
 // Scalar arguments shared by every update: finite lr >= 0, eps >= 0, finite

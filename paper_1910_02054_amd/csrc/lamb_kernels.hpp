@@ -102,11 +102,11 @@ __device__ __forceinline__ void block_sum2(double& a, double& b) {
     }
 }
 
-// Tiles of the shard: with head h (0..3) the 4-element vectors begin at
+// Tiles of the shard: with head h (0..kMaxHead) the 4-element vectors begin at
 // indices congruent to h mod 4; tile 0 is [0, h) when h > 0, and the other
-// tiles are T = 4*BLOCK*U elements long, aligned to the vectors.  Returns the
-// first vector's element index (h - 4 for the partial tile [0, h)) and the
-// tile's element range [ts, te).
+// tiles are T = 4*BLOCK*U elements long, from h on.  Returns the tile's first
+// vector's element index (which lies before the shard when tile 0 begins with
+// part of a vector) and the tile's element range [ts, te).
 template <int BLOCK, int U>
 __device__ __forceinline__ int64_t tile_range(int64_t b, int64_t head, int64_t n, int64_t* ts, int64_t* te) {
     constexpr int64_t T = 4 * (int64_t)BLOCK * U;
@@ -114,7 +114,7 @@ __device__ __forceinline__ int64_t tile_range(int64_t b, int64_t head, int64_t n
     if (b < hs) {
         *ts = 0;
         *te = head < n ? head : n;
-        return head - 4;
+        return head - (head + 3) / 4 * 4;
     }
     const int64_t base = head + (b - hs) * T;
     *ts = base;
@@ -130,12 +130,12 @@ __device__ __forceinline__ int64_t tile_range(int64_t b, int64_t head, int64_t n
 // depend on b only, so the loads are issued before the tile's work items
 // (its layer pieces, [tile_first[b], tile_first[b+1]) of the item list) are
 // read; the items are needed only to attribute each element's theta^2 and u^2
-// to its layer piece.  VEC: all arrays share the element misalignment `head`,
-// so a vector inside the tile is one 16-byte fp32 access per array and one
-// 8-byte fp16 access; the partial vectors at the array's ends and every
-// element when !VEC (head = 0) take the scalar path.
+// to its layer piece.  A vector inside the tile is one 16-byte fp32 access per
+// array and one 8-byte fp16 access: `head` brings the master array's vectors
+// to cache lines, the other arrays' may be unaligned (as k_adam_vec's);
+// the partial vectors at the shard's ends go element by element.
 // ---------------------------------------------------------------------------
-template <int BLOCK, int U, bool NTL, bool NTS, bool VEC, bool XCD>
+template <int BLOCK, int U, bool NTL, bool NTS, bool XCD>
 __global__ __launch_bounds__(BLOCK) void k_lamb_moments(const uint16_t* __restrict__ g, const float* __restrict__ th,
                                                         float* __restrict__ m, float* __restrict__ v,
                                                         const LambItem* __restrict__ items,
@@ -154,11 +154,11 @@ __global__ __launch_bounds__(BLOCK) void k_lamb_moments(const uint16_t* __restri
         for (int u = 0; u < U; ++u) {
             const int64_t e0 = base + 4 * ((int64_t)threadIdx.x + (int64_t)u * BLOCK);
             e0s[u] = e0;
-            if (VEC && e0 >= ts && e0 + 4 <= te) {
-                const u32x2 gq = ld<NTL>(reinterpret_cast<const u32x2*>(g + e0));
-                const f32x4 tq = ld<NTL>(reinterpret_cast<const f32x4*>(th + e0));
-                f32x4 mq = ld<NTL>(reinterpret_cast<const f32x4*>(m + e0));
-                f32x4 vq = ld<NTL>(reinterpret_cast<const f32x4*>(v + e0));
+            if (e0 >= ts && e0 + 4 <= te) {
+                const u32x2 gq = ld4<NTL>(g + e0);
+                const f32x4 tq = ld4<NTL>(th + e0);
+                f32x4 mq = ld4<NTL>(m + e0);
+                f32x4 vq = ld4<NTL>(v + e0);
                 const uint32_t gw[4] = {gq.x & 0xFFFFu, gq.x >> 16, gq.y & 0xFFFFu, gq.y >> 16};
                 const float t4[4] = {tq.x, tq.y, tq.z, tq.w};
                 float m4[4] = {mq.x, mq.y, mq.z, mq.w};
@@ -171,8 +171,8 @@ __global__ __launch_bounds__(BLOCK) void k_lamb_moments(const uint16_t* __restri
                     w2[u][j] = td * td;
                     u2[u][j] = ud * ud;
                 }
-                st<NTS>(f32x4{m4[0], m4[1], m4[2], m4[3]}, reinterpret_cast<f32x4*>(m + e0));
-                st<NTS>(f32x4{v4[0], v4[1], v4[2], v4[3]}, reinterpret_cast<f32x4*>(v + e0));
+                st4<NTS>(f32x4{m4[0], m4[1], m4[2], m4[3]}, m + e0);
+                st4<NTS>(f32x4{v4[0], v4[1], v4[2], v4[3]}, v + e0);
             } else {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
@@ -269,7 +269,7 @@ __global__ __launch_bounds__(kLayerBlock) void k_lamb_layer(const LayerSums* __r
 // Apply pass: same tile walk as the moments pass; each element moves by its
 // layer piece's step size (theta <- theta - step*u) and gets its fp16 copy.
 // ---------------------------------------------------------------------------
-template <int BLOCK, int U, bool NTL, bool NTS, bool VEC, bool XCD>
+template <int BLOCK, int U, bool NTL, bool NTS, bool XCD>
 __global__ __launch_bounds__(BLOCK) void k_lamb_apply(float* __restrict__ th, const float* __restrict__ m,
                                                       const float* __restrict__ v, uint16_t* __restrict__ p,
                                                       const LambItem* __restrict__ items,
@@ -290,11 +290,11 @@ __global__ __launch_bounds__(BLOCK) void k_lamb_apply(float* __restrict__ th, co
         for (int u = 0; u < U; ++u) {
             const int64_t e0 = base + 4 * ((int64_t)threadIdx.x + (int64_t)u * BLOCK);
             e0s[u] = e0;
-            full[u] = VEC && e0 >= ts && e0 + 4 <= te;
+            full[u] = e0 >= ts && e0 + 4 <= te;
             if (full[u]) {
-                const f32x4 tq = ld<NTL>(reinterpret_cast<const f32x4*>(th + e0));
-                const f32x4 mq = ld<NTL>(reinterpret_cast<const f32x4*>(m + e0));
-                const f32x4 vq = ld<NTL>(reinterpret_cast<const f32x4*>(v + e0));
+                const f32x4 tq = ld4<NTL>(th + e0);
+                const f32x4 mq = ld4<NTL>(m + e0);
+                const f32x4 vq = ld4<NTL>(v + e0);
                 const float tt[4] = {tq.x, tq.y, tq.z, tq.w};
                 const float mm[4] = {mq.x, mq.y, mq.z, mq.w};
                 const float vv[4] = {vq.x, vq.y, vq.z, vq.w};
@@ -349,8 +349,8 @@ __global__ __launch_bounds__(BLOCK) void k_lamb_apply(float* __restrict__ th, co
                 h[j] = f32_to_f16(o[j]);
             }
             if (full[u]) {
-                st<NTS>(f32x4{o[0], o[1], o[2], o[3]}, reinterpret_cast<f32x4*>(th + e0));
-                st<NTS>(u32x2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)}, reinterpret_cast<u32x2*>(p + e0));
+                st4<NTS>(f32x4{o[0], o[1], o[2], o[3]}, th + e0);
+                st4<NTS>(u32x2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)}, p + e0);
             } else {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {

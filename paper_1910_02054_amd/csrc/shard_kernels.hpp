@@ -16,7 +16,7 @@
 //               of the unscaled gradient, the global-norm clipping coefficient,
 //               the fp32 gradient multiplier and the skip flag, written to
 //               device memory and to a host-mapped record.
-//   k_adam_*    the fused update: unscale+clip, Adam with bias correction, fp16
+//   k_adam_vec  the fused update: unscale+clip, Adam with bias correction, fp16
 //               cast; 14 bytes read and 14 bytes written per element.
 // Small shards take one launch instead (k_small_step): every thread keeps
 // its elements in registers, the workgroups meet at a grid barrier after the
@@ -48,8 +48,15 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
+// The same vectors at element alignment, for arrays that start anywhere.  gfx950
+// runs in unaligned access mode, so they compile to the same single 16-byte
+// (fp32) and 8-byte (fp16) loads and stores as the aligned types.
+typedef u32x2 u32x2_e __attribute__((aligned(2)));
+typedef f32x4 f32x4_e __attribute__((aligned(4)));
+
+constexpr int kLineBytes = 128;        // a cache line
+constexpr int kMaxHead = kLineBytes / 4 - 1;  // elements before the first line of an fp32 array
 constexpr int kMaxStatsBlocks = 4096;  // partial-sum records in the workspace
-constexpr int kScalarBlock = 256;
 
 // Launch-policy knobs of the streaming kernels are template parameters:
 //   BLOCK  threads per workgroup;  U  vectors per thread per tile;
@@ -71,6 +78,43 @@ __device__ __forceinline__ void st(T v, T* p) {
         __builtin_nontemporal_store(v, p);
     else
         *p = v;
+}
+
+// Four consecutive elements at any element alignment.
+template <bool NT>
+__device__ __forceinline__ f32x4 ld4(const float* p) {
+    const f32x4_e* q = reinterpret_cast<const f32x4_e*>(p);
+    if constexpr (NT)
+        return __builtin_nontemporal_load(q);
+    else
+        return *q;
+}
+
+template <bool NT>
+__device__ __forceinline__ u32x2 ld4(const uint16_t* p) {
+    const u32x2_e* q = reinterpret_cast<const u32x2_e*>(p);
+    if constexpr (NT)
+        return __builtin_nontemporal_load(q);
+    else
+        return *q;
+}
+
+template <bool NT>
+__device__ __forceinline__ void st4(f32x4 v, float* p) {
+    f32x4_e* q = reinterpret_cast<f32x4_e*>(p);
+    if constexpr (NT)
+        __builtin_nontemporal_store(v, q);
+    else
+        *q = v;
+}
+
+template <bool NT>
+__device__ __forceinline__ void st4(u32x2 v, uint16_t* p) {
+    u32x2_e* q = reinterpret_cast<u32x2_e*>(p);
+    if constexpr (NT)
+        __builtin_nontemporal_store(v, q);
+    else
+        *q = v;
 }
 
 template <bool XCD>
@@ -255,8 +299,8 @@ __device__ __forceinline__ Result make_result(double tot, double loss_scale, dou
 }
 
 // ---------------------------------------------------------------------------
-// K1: statistics.  `head` leading elements (0..7) are not 16-byte aligned and
-// `nvec` 8-element vectors follow; elements [head + 8*nvec, n) are the tail.
+// K1: statistics.  `head` leading elements (0..63) lie before the gradient's
+// first cache line and `nvec` 8-element vectors follow; elements [head + 8*nvec, n) are the tail.
 // Grid: 1 .. kMaxStatsBlocks workgroups of BLOCK threads; workgroup b writes
 // part[b].
 // ---------------------------------------------------------------------------
@@ -435,8 +479,8 @@ __device__ __forceinline__ Result resident_advance(zero_resident_state_t* __rest
 }
 
 // ---------------------------------------------------------------------------
-// The per-element update: one definition for the vector body, the unaligned
-// head/tail and the scalar path, so every element is computed identically.
+// The per-element update: one definition for the vectors and for the single
+// elements at the ends, so every element is computed identically.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t adam_elem(uint32_t g16, float mult, float& th, float& m, float& v,
                                               const AdamConst& c) {
@@ -466,7 +510,18 @@ __device__ __forceinline__ void adam_one(const uint16_t* g, float* th, float* m,
     p[i] = (uint16_t)h;
 }
 
-// Four consecutive elements of the vector path: the loaded gradient word pair
+// The elements outside the vectors, [0, head) and [head + 4*nvec, n), by the
+// first kMaxHead + 4 threads of one workgroup.
+__device__ __forceinline__ void adam_ends(const uint16_t* g, float* th, float* m, float* v, uint16_t* p, int64_t n,
+                                          int64_t head, int64_t nvec, float mult, const AdamConst& c) {
+    const int64_t t = threadIdx.x, tail = head + 4 * nvec + (t - kMaxHead);
+    if (t < head)
+        adam_one(g, th, m, v, p, t, mult, c);
+    else if (t >= kMaxHead && tail < n)
+        adam_one(g, th, m, v, p, tail, mult, c);
+}
+
+// Four consecutive elements of the vectors: the loaded gradient word pair
 // and fp32 vectors in, the updated fp32 vectors and fp16 word pair out.
 __device__ __forceinline__ void adam_vec4(u32x2 gq, f32x4 tq, f32x4 mq, f32x4 vq, float mult, const AdamConst& c,
                                           f32x4& to, f32x4& mo, f32x4& vo, u32x2& po) {
@@ -484,15 +539,26 @@ __device__ __forceinline__ void adam_vec4(u32x2 gq, f32x4 tq, f32x4 mq, f32x4 vq
     po = u32x2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
 }
 
-// K2 (vector path).  All five arrays share the same element misalignment, so
-// after `head` (0..3) scalar elements every array is aligned for 4-element
-// vectors: 16-byte fp32 and 8-byte fp16 accesses, consecutive lanes on
-// consecutive vectors.  A tile is BLOCK*U vectors; each thread loads its U
+// K2.  The shard in 4-element vectors after `head` (0..kMaxHead) single
+// elements, which bring the fp32 master array to a cache line: one 16-byte
+// access per fp32 array and one 8-byte access per fp16 array, consecutive
+// lanes on consecutive vectors.  The other arrays may start at any element
+// (the rank's slice of the flat fp16 buffers starts at rank * S, the fp32
+// state at the start of an allocation): their accesses are then unaligned but
+// still one instruction each.  HBM bandwidth bounds it.  Whole steps on 61M
+// elements: 279 us aligned; 293 us with the fp16 arrays three elements off
+// (two of the five lines of a wave's fp16 store are partial), 351 us by the
+// element-by-element kernel that such arrays took before; 288 us with all five
+// arrays three elements off, 363 us when their vectors began at the first
+// 16-byte boundary and every fp32 store ended in partial lines.
+// A tile is BLOCK*U vectors; each thread loads its U
 // vectors of all four inputs before computing (with U = 1, the production
 // shape, the loads, the update and the stores sit under one bounds test,
 // which measured about 4 us faster per 250M-element launch than a separate
 // test for the loads and for the rest).  Elements [head + 4*nvec, n) are the
-// tail (0..3).  Any grid size is valid (tiles are strided by it).  The fp32
+// tail (0..3).  The last workgroup takes head and tail; the host gives them a
+// workgroup without a tile, so that no workgroup has both latencies in a row.
+// Any grid size is valid (tiles are strided by it).  The fp32
 // constants come by value, or with CDEV from device memory (the resident step
 // computes them on the device).
 template <int BLOCK, int U, bool NTL, bool NTS, bool XCD, bool REV, bool CDEV>
@@ -507,31 +573,23 @@ __global__ __launch_bounds__(BLOCK) void k_adam_vec(const uint16_t* __restrict__
     AdamConst c = c_arg;
     if constexpr (CDEV)
         c = *cdev;
-    if (blockIdx.x == 0 && threadIdx.x < 8) {
-        const int64_t t = threadIdx.x;
-        const int64_t i = t < 4 ? t : head + 4 * nvec + (t - 4);
-        if ((t < 4 && i < head) || (t >= 4 && i < n))
-            adam_one(g, th, m, v, p, i, mult, c);
-    }
-    const u32x2* __restrict__ gv = reinterpret_cast<const u32x2*>(g + head);
-    f32x4* __restrict__ tv = reinterpret_cast<f32x4*>(th + head);
-    f32x4* __restrict__ mv = reinterpret_cast<f32x4*>(m + head);
-    f32x4* __restrict__ vv = reinterpret_cast<f32x4*>(v + head);
-    u32x2* __restrict__ pv = reinterpret_cast<u32x2*>(p + head);
+    if (blockIdx.x == gridDim.x - 1)
+        adam_ends(g, th, m, v, p, n, head, nvec, mult, c);
     const int64_t tile = (int64_t)BLOCK * U;
     const int64_t ntiles = (nvec + tile - 1) / tile;
     for (int64_t tb = logical_block<XCD>(); tb < ntiles; tb += gridDim.x) {
         const int64_t base = (REV ? ntiles - 1 - tb : tb) * tile + threadIdx.x;
         if constexpr (U == 1) {
             if (base < nvec) {
+                const int64_t e = head + 4 * base;
                 f32x4 to, mo, vo;
                 u32x2 po;
-                adam_vec4(ld<NTL>(gv + base), ld<NTL>(tv + base), ld<NTL>(mv + base), ld<NTL>(vv + base), mult, c,
-                          to, mo, vo, po);
-                st<NTS>(to, tv + base);
-                st<NTS>(mo, mv + base);
-                st<NTS>(vo, vv + base);
-                st<NTS>(po, pv + base);
+                adam_vec4(ld4<NTL>(g + e), ld4<NTL>(th + e), ld4<NTL>(m + e), ld4<NTL>(v + e), mult, c, to, mo, vo,
+                          po);
+                st4<NTS>(to, th + e);
+                st4<NTS>(mo, m + e);
+                st4<NTS>(vo, v + e);
+                st4<NTS>(po, p + e);
             }
         } else {
             u32x2 gq[U];
@@ -540,10 +598,11 @@ __global__ __launch_bounds__(BLOCK) void k_adam_vec(const uint16_t* __restrict__
             for (int u = 0; u < U; ++u) {
                 const int64_t i = base + (int64_t)u * BLOCK;
                 if (i < nvec) {
-                    gq[u] = ld<NTL>(gv + i);
-                    tq[u] = ld<NTL>(tv + i);
-                    mq[u] = ld<NTL>(mv + i);
-                    vq[u] = ld<NTL>(vv + i);
+                    const int64_t e = head + 4 * i;
+                    gq[u] = ld4<NTL>(g + e);
+                    tq[u] = ld4<NTL>(th + e);
+                    mq[u] = ld4<NTL>(m + e);
+                    vq[u] = ld4<NTL>(v + e);
                 }
             }
 #pragma unroll
@@ -553,31 +612,15 @@ __global__ __launch_bounds__(BLOCK) void k_adam_vec(const uint16_t* __restrict__
                     f32x4 to, mo, vo;
                     u32x2 po;
                     adam_vec4(gq[u], tq[u], mq[u], vq[u], mult, c, to, mo, vo, po);
-                    st<NTS>(to, tv + i);
-                    st<NTS>(mo, mv + i);
-                    st<NTS>(vo, vv + i);
-                    st<NTS>(po, pv + i);
+                    const int64_t e = head + 4 * i;
+                    st4<NTS>(to, th + e);
+                    st4<NTS>(mo, m + e);
+                    st4<NTS>(vo, v + e);
+                    st4<NTS>(po, p + e);
                 }
             }
         }
     }
-}
-
-// K2 (scalar path) for arrays whose element misalignments differ.
-template <bool CDEV>
-__global__ __launch_bounds__(kScalarBlock) void k_adam_scalar(
-    const uint16_t* __restrict__ g, float* __restrict__ th, float* __restrict__ m, float* __restrict__ v,
-    uint16_t* __restrict__ p, int64_t n, const Result* __restrict__ res, AdamConst c_arg,
-    const AdamConst* __restrict__ cdev) {
-    if (res->skip)
-        return;
-    const float mult = res->mult;
-    AdamConst c = c_arg;
-    if constexpr (CDEV)
-        c = *cdev;
-    const int64_t stride = (int64_t)gridDim.x * kScalarBlock;
-    for (int64_t i = (int64_t)blockIdx.x * kScalarBlock + threadIdx.x; i < n; i += stride)
-        adam_one(g, th, m, v, p, i, mult, c);
 }
 
 // ---------------------------------------------------------------------------
@@ -585,7 +628,7 @@ __global__ __launch_bounds__(kScalarBlock) void k_adam_scalar(
 // the device at once (the host keeps it to a fraction of the co-resident
 // capacity, so a few such steps on concurrent streams also fit together), which
 // the grid barrier below relies on.  The shard's vector layout is
-// k_adam_vec's (`head` scalar elements, `nvec` 4-element vectors, a tail of
+// k_adam_vec's (`head` single elements, `nvec` 4-element vectors, a tail of
 // 0..3); workgroup b owns vectors (b*V + u)*kSmallBlock + threadIdx.x for
 // u < V, so consecutive lanes touch consecutive vectors.
 //   1. Thread 0 reads its group's wake flag (its value before this launch),
@@ -685,11 +728,6 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_step(
     double clip, uint32_t seq, AdamConst c) {
     __shared__ float s_mult;
     __shared__ int s_state;  // 1: this workgroup is the last arrival; then 0 proceed, 1 skip, 2 abort
-    const u32x2* __restrict__ gv = reinterpret_cast<const u32x2*>(g + head);
-    f32x4* __restrict__ tv = reinterpret_cast<f32x4*>(th + head);
-    f32x4* __restrict__ mv = reinterpret_cast<f32x4*>(m + head);
-    f32x4* __restrict__ vv = reinterpret_cast<f32x4*>(v + head);
-    u32x2* __restrict__ pv = reinterpret_cast<u32x2*>(p + head);
     const int64_t b = blockIdx.x;
     const int G = (int)gridDim.x;
     const int grp = (int)(b % kSyncGroups);
@@ -704,7 +742,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_step(
 #pragma unroll
     for (int u = 0; u < V; ++u) {
         const int64_t i = (b * V + u) * kSmallBlock + threadIdx.x;
-        gq[u] = i < nvec ? ld<true>(gv + i) : u32x2{0u, 0u};
+        gq[u] = i < nvec ? ld4<true>(g + head + 4 * i) : u32x2{0u, 0u};
         a0 = acc_sq2(gq[u].x, a0);
         a1 = acc_sq2(gq[u].y, a1);
     }
@@ -737,9 +775,10 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_step(
     for (int u = 0; u < V; ++u) {
         const int64_t i = (b * V + u) * kSmallBlock + threadIdx.x;
         if (i < nvec) {
-            tq[u] = ld<true>(tv + i);
-            mq[u] = ld<true>(mv + i);
-            vq[u] = ld<true>(vv + i);
+            const int64_t e = head + 4 * i;
+            tq[u] = ld4<true>(th + e);
+            mq[u] = ld4<true>(m + e);
+            vq[u] = ld4<true>(v + e);
         }
     }
     __syncthreads();
@@ -789,12 +828,8 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_step(
     const float mult = s_mult;
 
     // 5. the update from the registers (workgroup 0 also takes head and tail)
-    if (b == 0 && threadIdx.x < 8) {
-        const int64_t t = threadIdx.x;
-        const int64_t i = t < 4 ? t : head + 4 * nvec + (t - 4);
-        if ((t < 4 && i < head) || (t >= 4 && i < n))
-            adam_one(g, th, m, v, p, i, mult, c);
-    }
+    if (b == 0)
+        adam_ends(g, th, m, v, p, n, head, nvec, mult, c);
 #pragma unroll
     for (int u = 0; u < V; ++u) {
         const int64_t i = (b * V + u) * kSmallBlock + threadIdx.x;
@@ -802,10 +837,11 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_step(
             f32x4 to, mo, vo;
             u32x2 po;
             adam_vec4(gq[u], tq[u], mq[u], vq[u], mult, c, to, mo, vo, po);
-            st<true>(to, tv + i);
-            st<true>(mo, mv + i);
-            st<true>(vo, vv + i);
-            st<true>(po, pv + i);
+            const int64_t e = head + 4 * i;
+            st4<true>(to, th + e);
+            st4<true>(mo, m + e);
+            st4<true>(vo, v + e);
+            st4<true>(po, p + e);
         }
     }
 }

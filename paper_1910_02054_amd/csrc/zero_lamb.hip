@@ -32,7 +32,7 @@ constexpr int kLambBlock = 128, kLambUnroll = 1, kLambPerCU = 16;
 constexpr bool kLambNTL = true, kLambNTS = true, kLambXCD = true;
 constexpr int64_t kLambTile = 4 * (int64_t)kLambBlock * kLambUnroll;  // elements per tile
 constexpr int64_t kLambMaxBlocks = 1 << 26;
-constexpr int kPhases = 5;  // vector paths for element misalignment 0..3, then the scalar path
+constexpr int kHeads = zs::kMaxHead + 1;  // one work list per head (elements before the master array's first cache line)
 }  // namespace
 
 using namespace zsh;
@@ -60,7 +60,7 @@ struct zero_lamb_plan {
     int64_t n = 0;
     int32_t n_seg = 0;
     std::vector<int64_t> seg_off;
-    LambWork work[kPhases];
+    LambWork work[kHeads];
     zs::LayerSums* part = nullptr;   // one partial per item (sized for the longest list)
     zs::LayerSums* cpart = nullptr;  // one partial per level-1 chunk
     zs::LayerSums* sums = nullptr;   // per-layer sums of zero_lamb_step
@@ -69,8 +69,7 @@ struct zero_lamb_plan {
     hipStream_t last_stream = nullptr;
     bool used = false;
     uint64_t prof_tick = 0;
-    size_t lds[2] = {0, 0};  // occupancy reservations of the moments and apply kernels (per phase kind)
-    size_t lds_scalar[2] = {0, 0};
+    size_t lds[2] = {0, 0};  // occupancy reservations of the moments and apply kernels
 };
 
 namespace {
@@ -80,17 +79,15 @@ std::vector<LambProfRec> g_lprof_pending;
 std::vector<hipEvent_t> g_lprof_pool;
 zero_lamb_profile_t g_lprof_acc = {0, 0.0, 0.0, 0.0, 0.0};
 
-template <bool VEC>
 const void* moments_kernel() {
-    return reinterpret_cast<const void*>(zs::k_lamb_moments<kLambBlock, kLambUnroll, kLambNTL, kLambNTS, VEC, kLambXCD>);
+    return reinterpret_cast<const void*>(zs::k_lamb_moments<kLambBlock, kLambUnroll, kLambNTL, kLambNTS, kLambXCD>);
 }
 template <int PASS>
 const void* probe_kernel() {
     return reinterpret_cast<const void*>(zs::k_probe_lamb<kLambBlock, kLambUnroll, kLambNTL, kLambNTS, kLambXCD, PASS>);
 }
-template <bool VEC>
 const void* apply_kernel() {
-    return reinterpret_cast<const void*>(zs::k_lamb_apply<kLambBlock, kLambUnroll, kLambNTL, kLambNTS, VEC, kLambXCD>);
+    return reinterpret_cast<const void*>(zs::k_lamb_apply<kLambBlock, kLambUnroll, kLambNTL, kLambNTS, kLambXCD>);
 }
 
 // Upper bound on the items of any alignment: one per tile the shard touches
@@ -171,13 +168,12 @@ int upload(const std::vector<T>& h, T** d) {
     return ZERO_OK;
 }
 
-// The work list of `phase` (0..3: vector path with that head; 4: scalar path),
-// built and uploaded on first use.  Caller holds plan->mu.
-int get_work(zero_lamb_plan* plan, int phase, LambWork** out) {
-    LambWork& w = plan->work[phase];
+// The work list of `head`, built and uploaded on first use.  Caller holds
+// plan->mu.
+int get_work(zero_lamb_plan* plan, int head, LambWork** out) {
+    LambWork& w = plan->work[head];
     if (!w.built) {
         HostWork h;
-        const int64_t head = phase < 4 ? phase : 0;  // the kernels take the same head
         build_work(plan->seg_off, plan->n_seg, head, &h);
         const int64_t n_items = (int64_t)h.items.size() - 1, n_chunks = (int64_t)h.chunk.size() - 1;
         if (n_items > plan->max_items || n_chunks > plan->max_chunks)
@@ -194,19 +190,6 @@ int get_work(zero_lamb_plan* plan, int phase, LambWork** out) {
     }
     *out = &w;
     return ZERO_OK;
-}
-
-// Element misalignment shared by all arrays (0..3), or 4 when they differ (or
-// when an fp16 array is only 2-byte aligned relative to its fp32 partners).
-int phase_of(const uint16_t* g, const float* th, const float* m, const float* v, const uint16_t* p) {
-    const uintptr_t ef[3] = {(reinterpret_cast<uintptr_t>(th) & 15) / 4, (reinterpret_cast<uintptr_t>(m) & 15) / 4,
-                             (reinterpret_cast<uintptr_t>(v) & 15) / 4};
-    bool same = ef[0] == ef[1] && ef[0] == ef[2];
-    if (g)
-        same = same && (reinterpret_cast<uintptr_t>(g) & 7) / 2 == ef[0];
-    if (p)
-        same = same && (reinterpret_cast<uintptr_t>(p) & 7) / 2 == ef[0];
-    return same ? (int)((4 - ef[0]) & 3) : 4;
 }
 
 int check_plan(const char* fn, const zero_lamb_plan_t* plan) {
@@ -297,17 +280,12 @@ unsigned tile_grid(int64_t ntiles) {
     return (unsigned)((b + 7) / 8 * 8);
 }
 
-int launch_moments(zero_lamb_plan* plan, const LambWork& w, int phase, const uint16_t* g, const float* th, float* m,
+int launch_moments(zero_lamb_plan* plan, const LambWork& w, int head, const uint16_t* g, const float* th, float* m,
                    float* v, const zs::Result* res, const zs::AdamConst& c, hipStream_t stream) {
     const unsigned grid = tile_grid(w.ntiles);
-    if (phase < 4)
-        zs::k_lamb_moments<kLambBlock, kLambUnroll, kLambNTL, kLambNTS, true, kLambXCD>
-            <<<grid, kLambBlock, plan->lds[0], stream>>>(g, th, m, v, w.items, w.tile_first, w.ntiles, plan->n,
-                                                         phase, res, c, plan->part);
-    else
-        zs::k_lamb_moments<kLambBlock, kLambUnroll, kLambNTL, kLambNTS, false, kLambXCD>
-            <<<grid, kLambBlock, plan->lds_scalar[0], stream>>>(g, th, m, v, w.items, w.tile_first, w.ntiles,
-                                                                 plan->n, 0, res, c, plan->part);
+    zs::k_lamb_moments<kLambBlock, kLambUnroll, kLambNTL, kLambNTS, kLambXCD>
+        <<<grid, kLambBlock, plan->lds[0], stream>>>(g, th, m, v, w.items, w.tile_first, w.ntiles, plan->n, head, res,
+                                                     c, plan->part);
     HIP_TRY(hipGetLastError());
     return ZERO_OK;
 }
@@ -323,18 +301,13 @@ int launch_layer(zero_lamb_plan* plan, const LambWork& w, zs::LayerSums* sums, c
     return ZERO_OK;
 }
 
-int launch_apply(zero_lamb_plan* plan, const LambWork& w, int phase, float* th, const float* m, const float* v,
+int launch_apply(zero_lamb_plan* plan, const LambWork& w, int head, float* th, const float* m, const float* v,
                  uint16_t* p, const zs::LayerSums* sums, const zs::Result* res, const zs::AdamConst& c, double lr,
                  double phi_lo, double phi_hi, hipStream_t stream) {
     const unsigned grid = tile_grid(w.ntiles);
-    if (phase < 4)
-        zs::k_lamb_apply<kLambBlock, kLambUnroll, kLambNTL, kLambNTS, true, kLambXCD>
-            <<<grid, kLambBlock, plan->lds[1], stream>>>(th, m, v, p, w.items, w.tile_first, w.ntiles, plan->n,
-                                                         phase, sums, res, c, lr, phi_lo, phi_hi);
-    else
-        zs::k_lamb_apply<kLambBlock, kLambUnroll, kLambNTL, kLambNTS, false, kLambXCD>
-            <<<grid, kLambBlock, plan->lds_scalar[1], stream>>>(th, m, v, p, w.items, w.tile_first, w.ntiles,
-                                                                 plan->n, 0, sums, res, c, lr, phi_lo, phi_hi);
+    zs::k_lamb_apply<kLambBlock, kLambUnroll, kLambNTL, kLambNTS, kLambXCD>
+        <<<grid, kLambBlock, plan->lds[1], stream>>>(th, m, v, p, w.items, w.tile_first, w.ntiles, plan->n, head, sums,
+                                                     res, c, lr, phi_lo, phi_hi);
     HIP_TRY(hipGetLastError());
     return ZERO_OK;
 }
@@ -494,10 +467,8 @@ int zero_lamb_plan_create(const int64_t* seg_off, int32_t n_seg, int64_t n, zero
             return fail(ZERO_EHIP, "zero_lamb_plan_create: hipGetDeviceProperties failed");
         }
         int resident = 0;
-        p->lds[0] = occupancy_lds(moments_kernel<true>(), kLambBlock, kLambPerCU, prop, &resident);
-        p->lds[1] = occupancy_lds(apply_kernel<true>(), kLambBlock, kLambPerCU, prop, &resident);
-        p->lds_scalar[0] = occupancy_lds(moments_kernel<false>(), kLambBlock, kLambPerCU, prop, &resident);
-        p->lds_scalar[1] = occupancy_lds(apply_kernel<false>(), kLambBlock, kLambPerCU, prop, &resident);
+        p->lds[0] = occupancy_lds(moments_kernel(), kLambBlock, kLambPerCU, prop, &resident);
+        p->lds[1] = occupancy_lds(apply_kernel(), kLambBlock, kLambPerCU, prop, &resident);
     }
     *out = p.release();
     return ZERO_OK;
@@ -551,9 +522,9 @@ int zero_lamb_step(const zero_lamb_plan_t* plan_, const uint16_t* grad16, float*
     CtxLock ctx;
     if ((rc = lock_ctx(stream, &ctx)))
         return rc;
-    const int phase = phase_of(grad16, master32, m32, v32, param16_out);
+    const int head = (int)line_head(master32, sizeof(float));
     LambWork* w = nullptr;
-    if ((rc = get_work(plan, phase, &w)) || (rc = switch_stream(plan, stream)))
+    if ((rc = get_work(plan, head, &w)) || (rc = switch_stream(plan, stream)))
         return rc;
     const zs::AdamConst c = adam_const(lr, beta1, beta2, eps, weight_decay, step);
     const uint32_t seq = next_seq(ctx.get());
@@ -564,13 +535,13 @@ int zero_lamb_step(const zero_lamb_plan_t* plan_, const uint16_t* grad16, float*
     rc = launch_stats_planned(ctx.get(), grad16, n, loss_scale, clip, seq, stream);
     lprof_record(&pr, &prof, 1, stream);
     if (!rc)
-        rc = launch_moments(plan, *w, phase, grad16, master32, m32, v32, ctx->res, c, stream);
+        rc = launch_moments(plan, *w, head, grad16, master32, m32, v32, ctx->res, c, stream);
     lprof_record(&pr, &prof, 2, stream);
     if (!rc)
         rc = launch_layer(plan, *w, plan->sums, ctx->res, stream);
     lprof_record(&pr, &prof, 3, stream);
     if (!rc)
-        rc = launch_apply(plan, *w, phase, master32, m32, v32, param16_out, plan->sums, ctx->res, c, lr, phi_lo,
+        rc = launch_apply(plan, *w, head, master32, m32, v32, param16_out, plan->sums, ctx->res, c, lr, phi_lo,
                           phi_hi, stream);
     lprof_record(&pr, &prof, 4, stream);
     if (sampled)
@@ -612,16 +583,16 @@ int zero_lamb_moments(const zero_lamb_plan_t* plan_, const uint16_t* grad16, con
     CtxLock ctx;
     if ((rc = lock_ctx(stream, &ctx)))
         return rc;
-    const int phase = phase_of(grad16, master32, m32, v32, nullptr);
+    const int head = (int)line_head(master32, sizeof(float));
     LambWork* w = nullptr;
-    if ((rc = get_work(plan, phase, &w)) || (rc = switch_stream(plan, stream)))
+    if ((rc = get_work(plan, head, &w)) || (rc = switch_stream(plan, stream)))
         return rc;
     const zs::AdamConst c = adam_const(0.0, beta1, beta2, eps, weight_decay, step);
     const uint32_t seq = next_seq(ctx.get());
     zs::k_set_result<<<1, 64, 0, stream>>>(ctx->res, global_sumsq, loss_scale, clip, seq);
     rc = hipGetLastError() == hipSuccess ? ZERO_OK : fail(ZERO_EHIP, "%s: result-record launch failed", fn);
     if (!rc)
-        rc = launch_moments(plan, *w, phase, grad16, master32, m32, v32, ctx->res, c, stream);
+        rc = launch_moments(plan, *w, head, grad16, master32, m32, v32, ctx->res, c, stream);
     if (!rc)
         rc = launch_layer(plan, *w, reinterpret_cast<zs::LayerSums*>(layer_sumsq), ctx->res, stream);
     const int rc_done = mark_done(plan, stream);
@@ -657,9 +628,9 @@ int zero_lamb_apply(const zero_lamb_plan_t* plan_, float* master32, const float*
     CtxLock ctx;
     if ((rc = lock_ctx(stream, &ctx)))
         return rc;
-    const int phase = phase_of(nullptr, master32, m32, v32, param16_out);
+    const int head = (int)line_head(master32, sizeof(float));
     LambWork* w = nullptr;
-    if ((rc = get_work(plan, phase, &w)) || (rc = switch_stream(plan, stream)))
+    if ((rc = get_work(plan, head, &w)) || (rc = switch_stream(plan, stream)))
         return rc;
     const zs::AdamConst c = adam_const(lr, beta1, beta2, eps, weight_decay, step);
     const uint32_t seq = next_seq(ctx.get());
@@ -667,7 +638,7 @@ int zero_lamb_apply(const zero_lamb_plan_t* plan_, float* master32, const float*
     zs::k_set_result<<<1, 64, 0, stream>>>(ctx->res, 0.0, 1.0, 0.0, seq);
     rc = hipGetLastError() == hipSuccess ? ZERO_OK : fail(ZERO_EHIP, "%s: result-record launch failed", fn);
     if (!rc)
-        rc = launch_apply(plan, *w, phase, master32, m32, v32, param16_out,
+        rc = launch_apply(plan, *w, head, master32, m32, v32, param16_out,
                           reinterpret_cast<const zs::LayerSums*>(layer_sumsq), ctx->res, c, lr, phi_lo, phi_hi,
                           stream);
     const int rc_done = mark_done(plan, stream);

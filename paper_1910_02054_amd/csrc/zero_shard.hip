@@ -62,8 +62,8 @@ constexpr int64_t kAdamMaxBlocks = 1 << 26;
 constexpr int kCopyBlock = 64, kCopyUnroll = 1;
 constexpr bool kCopyNTL = true, kCopyNTS = true, kCopyXCD = false;
 // One-launch small-shard step (k_small_step): shards of at most kSmallMaxNumel
-// elements whose arrays share one misalignment, on a grid of at most
-// kSmallMaxGrid workgroups (each totals every workgroup's partial).
+// elements whose fp32 arrays share one misalignment (the fp16 arrays may start
+// at any element), on a grid of at most kSmallMaxGrid workgroups (each totals every workgroup's partial).
 #ifndef ZS_SMALL_MAX_NUMEL
 #define ZS_SMALL_MAX_NUMEL (1 << 22)
 #endif
@@ -96,49 +96,46 @@ constexpr int kSmallFirstV = ZS_SMALL_FIRST_V;  // index into kSmallV of the fir
 
 // ---------------------------------------------------------------------------
 // Launch planning.  One function decides every launch shape from n and the
-// arrays' alignments, so tests and benchmarks exercise the same configuration.
+// arrays' alignment, so tests and benchmarks exercise the same configuration.
 // ---------------------------------------------------------------------------
 struct Plan {
     int64_t ghead, gvec;   // statistics: unaligned head elements, 8-element vectors
     int stats_blocks;
-    bool vec;              // update: vector path (all arrays share misalignment)
     int64_t head, nvec;    // update: head elements, 4-element vectors
     int64_t adam_blocks;
+    bool one_phase;        // the fp32 arrays share one misalignment
     int small_v;           // one-launch small-shard step: vectors per thread (0: not taken)
     int64_t small_grid;
 };
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-Plan plan_step(const uint16_t* g, const float* th, const float* m, const float* v, const uint16_t* p, int64_t n,
-               int ncu) {
+// Elements of `size` bytes before the first cache line that starts in the array.
+int64_t line_head(const void* p, size_t size) {
+    return (int64_t)((zs::kLineBytes - (reinterpret_cast<uintptr_t>(p) & (zs::kLineBytes - 1))) % zs::kLineBytes / size);
+}
+
+Plan plan_step(const uint16_t* g, const float* th, const float* m, const float* v, int64_t n, int ncu) {
     Plan pl{};
-    // statistics: 16-byte vectors of the gradient, at most kStatsPerCU workgroups per CU
-    const uintptr_t ga = reinterpret_cast<uintptr_t>(g);
-    int64_t gh = (int64_t)(((16 - (ga & 15)) & 15) / 2);
+    // statistics: 16-byte vectors of the gradient from its first cache line, at most kStatsPerCU
+    // workgroups per CU
+    const int64_t gh = line_head(g, sizeof(uint16_t));
     pl.ghead = gh < n ? gh : n;
     pl.gvec = (n - pl.ghead) / 8;
     int64_t sb = ceil_div(pl.gvec, (int64_t)kStatsBlock * kStatsUnroll);
     const int64_t scap = std::min<int64_t>((int64_t)ncu * kStatsPerCU, zs::kMaxStatsBlocks);
     pl.stats_blocks = (int)(sb < 1 ? 1 : (sb > scap ? scap : sb));
-    // update: 4-element vectors (16-byte fp32, 8-byte fp16) need one common misalignment
-    const int64_t ef[3] = {(int64_t)((reinterpret_cast<uintptr_t>(th) & 15) / 4),
-                           (int64_t)((reinterpret_cast<uintptr_t>(m) & 15) / 4),
-                           (int64_t)((reinterpret_cast<uintptr_t>(v) & 15) / 4)};
-    const int64_t eh[2] = {(int64_t)((reinterpret_cast<uintptr_t>(g) & 7) / 2),
-                           (int64_t)((reinterpret_cast<uintptr_t>(p) & 7) / 2)};
-    pl.vec = ef[0] == ef[1] && ef[0] == ef[2] && ef[0] == eh[0] && ef[0] == eh[1];
-    if (pl.vec) {
-        int64_t h = (4 - ef[0]) & 3;
-        pl.head = h < n ? h : n;
-        pl.nvec = (n - pl.head) / 4;
-        int64_t ab = ceil_div(pl.nvec, (int64_t)kAdamBlock * kAdamUnroll);
-        pl.adam_blocks = ab < 1 ? 1 : (ab > kAdamMaxBlocks ? kAdamMaxBlocks : ab);
-    } else {
-        pl.head = pl.nvec = 0;
-        int64_t ab = ceil_div(n, zs::kScalarBlock);
-        pl.adam_blocks = ab < 1 ? 1 : (ab > kAdamMaxBlocks ? kAdamMaxBlocks : ab);
-    }
+    // update: 4-element vectors from the first cache line of the master parameters, so that no wave
+    // writes part of a line of an fp32 array that shares master's place in its line; the other
+    // arrays' vectors may be unaligned (a slice of a flat fp16 buffer starts at any element)
+    const uintptr_t ta = reinterpret_cast<uintptr_t>(th) & 15;
+    pl.one_phase = ta == (reinterpret_cast<uintptr_t>(m) & 15) && ta == (reinterpret_cast<uintptr_t>(v) & 15);
+    const int64_t h = line_head(th, sizeof(float));
+    pl.head = h < n ? h : n;
+    pl.nvec = (n - pl.head) / 4;
+    const int64_t ends = n > 4 * pl.nvec ? 1 : 0;  // a workgroup for the head and the tail
+    const int64_t ab = ceil_div(pl.nvec, (int64_t)kAdamBlock * kAdamUnroll) + ends;
+    pl.adam_blocks = ab < 1 ? 1 : (ab > kAdamMaxBlocks ? kAdamMaxBlocks : ab);
     return pl;
 }
 
@@ -148,7 +145,7 @@ Plan plan_step(const uint16_t* g, const float* th, const float* m, const float* 
 void plan_small(Plan* pl, int64_t n, const DevInfo* info) {
     pl->small_v = 0;
     pl->small_grid = 0;
-    if (!pl->vec || n > kSmallMaxNumel)
+    if (!pl->one_phase || n > kSmallMaxNumel)
         return;
     for (int k = kSmallFirstV; k < 4; ++k) {
         int64_t grid = ceil_div(pl->nvec, (int64_t)zs::kSmallBlock * kSmallV[k]);
@@ -607,7 +604,7 @@ int launch_stats_into(const DevInfo* info, zs::Partial* part, zs::Result* res, z
 
 int launch_stats_planned(Ctx* ctx, const uint16_t* grad16, int64_t n, double loss_scale, double clip, uint32_t seq,
                          hipStream_t stream) {
-    const Plan pl = plan_step(grad16, nullptr, nullptr, nullptr, nullptr, n, ctx->info->ncu);
+    const Plan pl = plan_step(grad16, nullptr, nullptr, nullptr, n, ctx->info->ncu);
     return launch_stats_into(ctx->info, ctx->part, ctx->res, ctx->host_dev, grad16, n, pl, loss_scale, clip, seq,
                              stream);
 }
@@ -622,20 +619,14 @@ int prof_every() {
 int launch_update_from(const DevInfo* info, const zs::Result* res, const uint16_t* grad16, float* master32,
                        float* m32, float* v32, uint16_t* param16_out, int64_t n, const Plan& pl,
                        const zs::AdamConst& c, hipStream_t stream, const zs::AdamConst* cdev = nullptr) {
-    if (pl.vec && cdev)
+    if (cdev)
         zs::k_adam_vec<kAdamBlock, kAdamUnroll, kAdamNTL, kAdamNTS, kAdamXCD, kAdamREV, true>
             <<<(unsigned)pl.adam_blocks, kAdamBlock, info->adam_lds, stream>>>(
                 grad16, master32, m32, v32, param16_out, n, pl.head, pl.nvec, res, c, cdev);
-    else if (pl.vec)
+    else
         zs::k_adam_vec<kAdamBlock, kAdamUnroll, kAdamNTL, kAdamNTS, kAdamXCD, kAdamREV, false>
             <<<(unsigned)pl.adam_blocks, kAdamBlock, info->adam_lds, stream>>>(
                 grad16, master32, m32, v32, param16_out, n, pl.head, pl.nvec, res, c, nullptr);
-    else if (cdev)
-        zs::k_adam_scalar<true><<<(unsigned)pl.adam_blocks, zs::kScalarBlock, 0, stream>>>(
-            grad16, master32, m32, v32, param16_out, n, res, c, cdev);
-    else
-        zs::k_adam_scalar<false><<<(unsigned)pl.adam_blocks, zs::kScalarBlock, 0, stream>>>(
-            grad16, master32, m32, v32, param16_out, n, res, c, nullptr);
     HIP_TRY(hipGetLastError());
     return ZERO_OK;
 }
@@ -954,7 +945,7 @@ int zero_shard_step(const uint16_t* grad16, float* master32, float* m32, float* 
     if ((rc = check_shard_ranges("zero_shard_step", grad16, master32, m32, v32, param16_out, n)))
         return rc;
     const zs::AdamConst c = adam_const(lr, beta1, beta2, eps, weight_decay, step);
-    Plan pl = plan_step(grad16, master32, m32, v32, param16_out, n, ctx->info->ncu);
+    Plan pl = plan_step(grad16, master32, m32, v32, n, ctx->info->ncu);
     plan_small(&pl, n, ctx->info);
     const uint32_t seq = next_seq(ctx.get());
 
@@ -1052,7 +1043,7 @@ int zero_shard_apply(const uint16_t* grad16, float* master32, float* m32, float*
     if ((rc = check_shard_ranges("zero_shard_apply", grad16, master32, m32, v32, param16_out, n)))
         return rc;
     const zs::AdamConst c = adam_const(lr, beta1, beta2, eps, weight_decay, step);
-    const Plan pl = plan_step(grad16, master32, m32, v32, param16_out, n, ctx->info->ncu);
+    const Plan pl = plan_step(grad16, master32, m32, v32, n, ctx->info->ncu);
     const uint32_t seq = next_seq(ctx.get());
     // sampled timing as in zero_shard_step: the "statistics" interval here is the
     // result-record kernel only (the statistics ran in zero_shard_stats)
@@ -1105,7 +1096,7 @@ int zero_shard_stats_async(const uint16_t* grad16, int64_t n, double* local_sums
         HIP_TRY(hipGetLastError());
         return ZERO_OK;
     }
-    const Plan pl = plan_step(grad16, nullptr, nullptr, nullptr, nullptr, n, ctx->info->ncu);
+    const Plan pl = plan_step(grad16, nullptr, nullptr, nullptr, n, ctx->info->ncu);
     zs::k_stats<kStatsBlock, kStatsUnroll, kStatsNTL, kStatsXCD>
         <<<pl.stats_blocks, kStatsBlock, ctx->info->stats_lds, stream>>>(grad16, n, pl.ghead, pl.gvec, ctx->part);
     HIP_TRY(hipGetLastError());
@@ -1156,7 +1147,7 @@ int zero_shard_apply_async(const uint16_t* grad16, float* master32, float* m32, 
         return ZERO_OK;
     }
     const zs::AdamConst c = adam_const(lr, beta1, beta2, eps, weight_decay, step);
-    const Plan pl = plan_step(grad16, master32, m32, v32, param16_out, n, ctx->info->ncu);
+    const Plan pl = plan_step(grad16, master32, m32, v32, n, ctx->info->ncu);
     ProfRec pr{};
     const int prof = prof_begin(&ctx->prof_tick, &ctx->prof_epoch, &pr);  // timed as zero_shard_apply
     if (prof < 0)
@@ -1245,7 +1236,7 @@ int zero_shard_step_resident(const uint16_t* grad16, float* master32, float* m32
     if (++ws->seq == 0)
         ++ws->seq;
     const uint32_t seq = ws->seq;
-    const Plan pl = plan_step(grad16, master32, m32, v32, param16_out, n, info->ncu);
+    const Plan pl = plan_step(grad16, master32, m32, v32, n, info->ncu);
     ProfRec pr{};
     const int prof = !capturing && n > 0 ? prof_begin(&ws->prof_tick, &ws->prof_epoch, &pr) : 0;
     if (prof < 0)
@@ -1403,7 +1394,7 @@ int zero_shard_step_noalloc(const uint16_t* grad16, float* master32, float* m32,
     zs::Result* res = reinterpret_cast<zs::Result*>(base + kScratchRes);
     zs::Result* res2 = reinterpret_cast<zs::Result*>(base + kScratchRes2);
     const zs::AdamConst c = adam_const(lr, beta1, beta2, eps, weight_decay, step);
-    Plan pl = plan_step(grad16, master32, m32, v32, param16_out, n, info->ncu);
+    Plan pl = plan_step(grad16, master32, m32, v32, n, info->ncu);
     plan_small(&pl, n, info);
     if (pl.stats_blocks > zs::kMaxStatsBlocks || pl.small_grid > (int64_t)zs::kMaxStatsBlocks)
         return fail(ZERO_EINVAL, "%s: launch needs more partials than the fixed workspace holds", fn);
