@@ -18,8 +18,8 @@
  *   - Array arguments are DEVICE pointers owned by the caller.  The library
  *     never allocates, frees or retains them and touches exactly [0, n).
  *   - The library owns a small per-(device, stream) workspace (per-workgroup
- *     partial sums, one result record, a barrier counter, one pinned host
- *     record: about 64 KiB of device memory), allocated on a stream's first
+ *     partial sums, one result record, exchange slots, two pinned host
+ *     words: about 68 KiB of device memory), allocated on a stream's first
  *     call and held until zero_stream_release(stream) or the process ends, so
  *     the library's memory grows with the number of distinct streams it has
  *     seen.  Its size does not depend on n (constant-size buffers, Sec. 6.2).
@@ -115,9 +115,9 @@ int zero_partition_layout(int64_t total_numel, int32_t nd, int32_t rank, zero_la
  * for one resident grid (a quarter of the device's co-resident capacity for
  * the kernel, or 1/q with q = GPU_MAX_HW_QUEUES when that is larger: about
  * 1.5 million elements on MI355X with the default four queues) whose fp32 arrays share one
- * misalignment take a single launch (statistics, a grid barrier and the
+ * misalignment take a single launch (statistics, an exchange of the workgroups' sums and the
  * update in one kernel, the gradient read once); larger ones take the
- * statistics kernels and the update kernel.  The barrier relies on the whole
+ * statistics kernels and the update kernel.  The exchange relies on the whole
  * grid being resident at once; its wait is bounded, and should the device
  * not run the grid together within seconds, the step writes nothing and
  * returns ZERO_EHIP.  The call
@@ -134,8 +134,8 @@ int zero_shard_step(const uint16_t* grad16, float* master32, float* m32, float* 
  * harnesses that forbid the allocator): zero_shard_step with the same
  * arguments, checks, kernels, results and return values, that calls no
  * hipMalloc, hipFree or other allocating routine.  Its workspace (statistics
- * partials for up to 4096 workgroups, the one-launch step's barrier words and
- * two result records: 73 KiB) is one fixed device array per GPU, held by
+ * partials for up to 4096 workgroups, the one-launch step's exchange slots and
+ * the result: 69 KiB) is one fixed device array per GPU, held by
  * every GPU the library runs on until the process ends; n up to 2^40 (the
  * library's limit, ZERO_EINVAL above it) needs no more.  Differences: the call
  * returns once the whole step (update included) has completed on `stream`,

@@ -41,13 +41,21 @@ struct DevInfo {
     int ncu = 0;
     size_t stats_lds = 0, adam_lds = 0, probe_adam_lds = 0;
     int stats_resident = 0, adam_resident = 0, probe_adam_resident = 0;
-    int64_t small_cap[4] = {};  // co-resident workgroups of k_small_step<1, 2, 4, 8>
+    int64_t small_cap = 0;      // co-resident workgroups of k_small_step
     int64_t small_share = 4;    // a one-launch grid takes at most small_cap / small_share
 };
 
 // The facts of device `dev` (0 <= dev < kMaxDevices), filled on first use.
 int dev_info(int dev, const DevInfo** out);
 constexpr int kMaxDevices = 64;
+
+// Exchange slots of the one-launch small-shard step: two sets in device memory,
+// one filled and the other emptied by each launch.
+struct Slots {
+    uint64_t* words = nullptr;  // zs::kSlotWords
+    bool ready = false;         // the words have been zeroed on the stream
+    int set = 0;                // the set the next launch fills
+};
 
 // Per-(device, stream) context: the constant-size workspace of the gradient
 // statistics and the result record the update kernels read.  A context is
@@ -62,10 +70,9 @@ struct Ctx {
     hipStream_t stream = nullptr;
     zs::Partial* part = nullptr;    // kMaxStatsBlocks partial records (device)
     zs::Result* res = nullptr;      // result record (device), read by the update kernel
-    zs::Result* host = nullptr;     // host-mapped, GPU-uncached copy of the result record
-    zs::Result* host_dev = nullptr; // its device-side address
-    uint64_t* sync = nullptr;       // grid-barrier words of the small-shard step (device)
-    bool sync_ready = false;        // the words have been zeroed on the stream
+    uint64_t* host = nullptr;       // host-mapped, GPU-uncached words of the published sum
+    uint64_t* host_dev = nullptr;   // their device-side address
+    Slots slots;                    // exchange slots of the small-shard step (device)
     uint64_t prof_tick = 0;         // steps seen while profiling (for sampling)
     uint64_t prof_epoch = 0;        // profiling period the tick belongs to
     uint32_t seq = 0;               // call counter echoed in the result record
@@ -111,12 +118,13 @@ size_t occupancy_lds(const void* kernel, int block, int per_cu, const hipDeviceP
 zs::AdamConst adam_const(double lr, double beta1, double beta2, double eps, double wd, int64_t step);
 
 // Statistics + finalize of grad16[0, n) with the production launch shape; the
-// result record lands in ctx->res and in the host-mapped ctx->host.
+// result record lands in ctx->res and the sum in the host-mapped ctx->host.
 int launch_stats_planned(Ctx* ctx, const uint16_t* grad16, int64_t n, double loss_scale, double clip, uint32_t seq,
                          hipStream_t stream);
 
-// Waits (host polling) until the finalize kernel has published call `seq`.
-int wait_result(Ctx* ctx, uint32_t seq, hipStream_t stream, zs::Result* out);
+// Waits (host polling) until the device has published the sum of call `seq`;
+// *out is the result record of that sum at the call's loss scale and clip.
+int wait_result(Ctx* ctx, uint32_t seq, hipStream_t stream, double loss_scale, double clip, zs::Result* out);
 
 // Sampling period of kernel profiling (0 = off), set by zero_profile_enable.
 int prof_every();

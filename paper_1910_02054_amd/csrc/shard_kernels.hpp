@@ -15,13 +15,10 @@
 //   k_finalize  one workgroup: fixed-order reduction of the partials; the norm
 //               of the unscaled gradient, the global-norm clipping coefficient,
 //               the fp32 gradient multiplier and the skip flag, written to
-//               device memory and to a host-mapped record.
+//               device memory, and the sum to the host.
 //   k_adam_vec  the fused update: unscale+clip, Adam with bias correction, fp16
 //               cast; 14 bytes read and 14 bytes written per element.
-// Small shards take one launch instead (k_small_step): every thread keeps
-// its elements in registers, the workgroups meet at a grid barrier after the
-// statistics, each totals the partials in the same fixed order, and the update
-// follows from the registers (28 bytes per element, one launch).
+// Small shards take one launch instead (k_small_step in small_kernels.hpp).
 // The other ways of running the same step swap only the one-thread kernels
 // around these: the split phase takes the global sum from the host
 // (k_set_result) or from device memory (k_finalize_sum writes a rank's local
@@ -134,8 +131,7 @@ struct alignas(16) Partial {
 };
 
 // The step's shared scalars, produced on the device by k_finalize and read by
-// the update kernel (and by the host through a mapped copy for the skip
-// decision).
+// the update kernel.
 struct alignas(16) Result {
     double sumsq;    // sum of grad16^2 (loss-scaled); non-finite iff overflow
     double norm;     // sqrt(sumsq) / loss_scale
@@ -143,7 +139,7 @@ struct alignas(16) Result {
     float mult;      // (float)(coef / loss_scale)
     int32_t skip;    // 1 = overflow: the update kernel writes nothing
     int32_t overflow;
-    uint32_t seq;    // call sequence number, echoed so the host can check freshness
+    uint32_t seq;    // call sequence number
     int32_t unused[2];
 };
 
@@ -278,8 +274,10 @@ __device__ __forceinline__ double block_sum(double x) {
 }
 
 // Norm, clipping coefficient, multiplier and skip flag from the global sum of
-// squares (all in double; the multiplier rounded once to fp32).
-__device__ __forceinline__ Result make_result(double tot, double loss_scale, double clip, uint32_t seq) {
+// squares (all in double; the multiplier rounded once to fp32).  The host
+// evaluates it too, from the sum that the device publishes; every operation is
+// correctly rounded, so both get the same bits.
+__host__ __device__ inline Result make_result(double tot, double loss_scale, double clip, uint32_t seq) {
     Result r;
     r.sumsq = tot;
     r.overflow = __builtin_isfinite(tot) ? 0 : 1;
@@ -296,6 +294,16 @@ __device__ __forceinline__ Result make_result(double tot, double loss_scale, dou
     r.seq = seq;
     r.unused[0] = r.unused[1] = 0;
     return r;
+}
+
+// The statistics total to the host's two mapped words, each with the call's
+// sequence number in its high half.  Each word is complete in itself, so the
+// host needs no order between them and the device neither a release (an L2
+// write-back) nor a wait before the sequence number.
+__device__ __forceinline__ void publish_sum(uint64_t* __restrict__ host, double tot, uint32_t seq) {
+    const uint64_t w = __builtin_bit_cast(uint64_t, tot), tag = (uint64_t)seq << 32;
+    __hip_atomic_store(host, tag | (w & 0xFFFFFFFFu), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(host + 1, tag | (w >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ---------------------------------------------------------------------------
@@ -342,9 +350,7 @@ __global__ __launch_bounds__(BLOCK) void k_stats(const uint16_t* __restrict__ g,
 // ---------------------------------------------------------------------------
 // K2: finalize.  One workgroup of kFinalBlock threads; fixed-order reduction,
 // so the result depends only on the partials (bitwise reproducible for a given
-// launch shape).  `res_host` is host-mapped and GPU-uncached; its sequence
-// number is stored last, with release semantics at system scope, so a host
-// that sees the expected sequence number sees the whole record.
+// launch shape).  `host` is two mapped, GPU-uncached words (publish_sum).
 // ---------------------------------------------------------------------------
 constexpr int kFinalBlock = 256;
 
@@ -363,18 +369,12 @@ __device__ __forceinline__ double partials_total(const Partial* __restrict__ par
 }
 
 [[maybe_unused]] static __global__ __launch_bounds__(kFinalBlock) void k_finalize(
-    const Partial* __restrict__ part, int nparts, Result* __restrict__ res, Result* __restrict__ res_host,
+    const Partial* __restrict__ part, int nparts, Result* __restrict__ res, uint64_t* __restrict__ host,
     double loss_scale, double clip, uint32_t seq) {
     const double tot = partials_total(part, nparts);
     if (threadIdx.x == 0) {
-        const Result r = make_result(tot, loss_scale, clip, seq);
-        *res = r;
-        // publish to the host: the record first, then its sequence number with a
-        // system-scope release (the host polls the sequence number)
-        Result rh = r;
-        rh.seq = 0;
-        *res_host = rh;
-        __hip_atomic_store(&res_host->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        publish_sum(host, tot, seq);
+        *res = make_result(tot, loss_scale, clip, seq);
     }
 }
 
@@ -619,229 +619,6 @@ __global__ __launch_bounds__(BLOCK) void k_adam_vec(const uint16_t* __restrict__
                     st4<NTS>(po, p + e);
                 }
             }
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// One-launch small-shard step.  The grid is small enough to be resident on
-// the device at once (the host keeps it to a fraction of the co-resident
-// capacity, so a few such steps on concurrent streams also fit together), which
-// the grid barrier below relies on.  The shard's vector layout is
-// k_adam_vec's (`head` single elements, `nvec` 4-element vectors, a tail of
-// 0..3); workgroup b owns vectors (b*V + u)*kSmallBlock + threadIdx.x for
-// u < V, so consecutive lanes touch consecutive vectors.
-//   1. Thread 0 reads its group's wake flag (its value before this launch),
-//      then the workgroup loads its gradient vectors, sums their exact squares
-//      in fp64 (workgroup 0 also takes the head and tail elements) and stores
-//      the workgroup's partial part[b].
-//   2. Arrival, in two levels so that no address takes more than a few dozen
-//      atomic additions (one address serialises them at about 12 ns each):
-//      workgroup b counts itself in group b mod kSyncGroups; the last of a
-//      group counts the group at the top; the last group's last workgroup is
-//      the last arrival.  Counters are reset by their last arrival.
-//   3. The state loads of theta, m and v are issued (they overlap the wait).
-//   4. The last arrival claims the launch, totals part[0, gridDim.x) in a
-//      fixed order, publishes the result record (device and host-mapped),
-//      then writes every group's wake flag: a launch count in the high bits,
-//      the skip flag and the fp32 multiplier in the low 33, so a waiter reads
-//      the step's scalars from the word it polls.  The others wait for their
-//      group's flag to change.
-//   5. Unless the step is skipped, the update from the registers.
-// The wait is bounded.  A workgroup that gives up tries to claim the launch
-// as aborted; the claim word makes completion and abort exclusive, so either
-// every workgroup updates or none does (then nothing is written, the record
-// is not published and the host's wait ends with an error once the stream
-// is idle).  Partials, counters, flags and the claim word are accessed with
-// agent-scope atomic operations, which the device keeps coherent across its
-// XCDs without writing back or invalidating the L2 caches; a store completes
-// (s_waitcnt) before the operation that announces it is issued.
-// ---------------------------------------------------------------------------
-constexpr int kSmallBlock = 256;
-constexpr int kSyncGroups = 16;
-constexpr int kSyncStride = 32;                        // words between sync words (256 bytes)
-constexpr uint32_t kBarrierSpinLimit = 1u << 22;       // polls of about 0.1-1 us each
-// Word offsets in the sync area (each word on its own 256-byte line).
-constexpr int kSyncGroupCtr = 0;                       // kSyncGroups group counters
-constexpr int kSyncTop = kSyncGroups;                  // the count of complete groups
-constexpr int kSyncFlag = kSyncGroups + 1;             // kSyncGroups wake flags
-constexpr int kSyncClaim = 2 * kSyncGroups + 1;        // 0 open, 1 completed, 2 aborted
-constexpr int kSyncWords = (2 * kSyncGroups + 2) * kSyncStride;
-constexpr uint64_t kFlagCount = (uint64_t)1 << 33;     // a wake flag's launch count unit
-
-__device__ __forceinline__ uint64_t* sync_word(uint64_t* sync, int k) { return sync + (int64_t)k * kSyncStride; }
-
-__device__ __forceinline__ uint64_t aload(const uint64_t* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ __forceinline__ void astore(uint64_t* p, uint64_t v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ __forceinline__ uint64_t aadd(uint64_t* p, uint64_t v) {
-    return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ __forceinline__ bool acas(uint64_t* p, uint64_t expect, uint64_t v) {
-    return __hip_atomic_compare_exchange_strong(p, &expect, v, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Waiter (thread 0 of a workgroup that is not the last arrival): true when its
-// group's flag has moved on from `flag0` (the launch completed; *word is the
-// new flag), false when the launch was aborted.  The last arrival writes every
-// flag before it reopens the claim word, so a flag that has not moved while the
-// claim reads "aborted" means a real abort.
-__device__ __forceinline__ bool small_wait(uint64_t* sync, int grp, uint64_t flag0, uint64_t* word) {
-    uint64_t* flag = sync_word(sync, kSyncFlag + grp);
-    uint64_t* claim = sync_word(sync, kSyncClaim);
-    const uint64_t count0 = flag0 / kFlagCount;
-    uint32_t polls = 0;
-    for (;;) {
-        if ((*word = aload(flag)) / kFlagCount != count0)
-            return true;
-        ++polls;
-        if ((polls & 1023) == 0 && aload(claim) == 2)
-            return (*word = aload(flag)) / kFlagCount != count0;
-        if (polls >= kBarrierSpinLimit) {
-            polls = 0;
-            if (acas(claim, 0, 2)) {
-                __builtin_amdgcn_s_waitcnt(0);
-                if ((*word = aload(flag)) / kFlagCount != count0) {
-                    astore(claim, 0);  // the launch had completed just before: undo the claim
-                    return true;
-                }
-                return false;
-            }
-            // claimed as completed (the flag follows) or as aborted (the check above sees it)
-        }
-        __builtin_amdgcn_s_sleep(2);
-    }
-}
-
-template <int V>
-__global__ __launch_bounds__(kSmallBlock) void k_small_step(
-    const uint16_t* __restrict__ g, float* __restrict__ th, float* __restrict__ m, float* __restrict__ v,
-    uint16_t* __restrict__ p, int64_t n, int64_t head, int64_t nvec, uint64_t* __restrict__ part,
-    uint64_t* __restrict__ sync, Result* __restrict__ res, Result* __restrict__ res_host, double loss_scale,
-    double clip, uint32_t seq, AdamConst c) {
-    __shared__ float s_mult;
-    __shared__ int s_state;  // 1: this workgroup is the last arrival; then 0 proceed, 1 skip, 2 abort
-    const int64_t b = blockIdx.x;
-    const int G = (int)gridDim.x;
-    const int grp = (int)(b % kSyncGroups);
-    const int ngroups = G < kSyncGroups ? G : kSyncGroups;
-    uint64_t flag0 = 0;
-    if (threadIdx.x == 0)
-        flag0 = aload(sync_word(sync, kSyncFlag + grp));  // before arriving: it cannot move until then
-
-    // 1. statistics of this workgroup's gradient vectors
-    u32x2 gq[V];
-    double a0 = 0.0, a1 = 0.0;
-#pragma unroll
-    for (int u = 0; u < V; ++u) {
-        const int64_t i = (b * V + u) * kSmallBlock + threadIdx.x;
-        gq[u] = i < nvec ? ld4<true>(g + head + 4 * i) : u32x2{0u, 0u};
-        a0 = acc_sq2(gq[u].x, a0);
-        a1 = acc_sq2(gq[u].y, a1);
-    }
-    if (b == 0) {
-        const int64_t t = threadIdx.x;
-        const int64_t tail0 = head + 4 * nvec;
-        if (t < head)
-            a0 += sq1(g[t]);
-        if (t < 4 && tail0 + t < n)
-            a1 += sq1(g[tail0 + t]);
-    }
-    const double ps = block_sum<kSmallBlock>(a0 + a1);
-
-    // 2. publish the partial and arrive (two levels)
-    if (threadIdx.x == 0) {
-        astore(part + b, __builtin_bit_cast(uint64_t, ps));
-        __builtin_amdgcn_s_waitcnt(0);
-        const uint64_t gsize = (uint64_t)((G - grp + kSyncGroups - 1) / kSyncGroups);
-        uint64_t* gctr = sync_word(sync, kSyncGroupCtr + grp);
-        int last = 0;
-        if (aadd(gctr, 1) == gsize - 1) {
-            astore(gctr, 0);  // every member has counted: ready for the next launch
-            last = aadd(sync_word(sync, kSyncTop), 1) == (uint64_t)(ngroups - 1);
-        }
-        s_state = last;
-    }
-    // 3. the state loads, overlapping the wait
-    f32x4 tq[V], mq[V], vq[V];
-#pragma unroll
-    for (int u = 0; u < V; ++u) {
-        const int64_t i = (b * V + u) * kSmallBlock + threadIdx.x;
-        if (i < nvec) {
-            const int64_t e = head + 4 * i;
-            tq[u] = ld4<true>(th + e);
-            mq[u] = ld4<true>(m + e);
-            vq[u] = ld4<true>(v + e);
-        }
-    }
-    __syncthreads();
-
-    // 4. the last arrival totals and publishes; the others wait for their flag
-    if (s_state == 1) {
-        double s0 = 0.0;
-        for (int64_t i = threadIdx.x; i < G; i += kSmallBlock)
-            s0 += __builtin_bit_cast(double, aload(part + i));
-        const double tot = block_sum<kSmallBlock>(s0);
-        if (threadIdx.x == 0) {
-            uint64_t* claim = sync_word(sync, kSyncClaim);
-            if (!acas(claim, 0, 1)) {
-                s_state = 2;  // a waiter gave up first: nobody writes
-            } else {
-                const Result r = make_result(tot, loss_scale, clip, seq);
-                *res = r;
-                Result rh = r;
-                rh.seq = 0;
-                *res_host = rh;
-                __hip_atomic_store(&res_host->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-                s_mult = r.mult;
-                s_state = r.skip;
-                astore(sync_word(sync, kSyncTop), 0);
-                // every flag is written, whatever the grid, so all of them always hold the same
-                // launch count (a waiter's group flag then always changes)
-                const uint64_t word = (flag0 / kFlagCount + 1) * kFlagCount +
-                                      ((uint64_t)__builtin_bit_cast(uint32_t, r.mult) | ((uint64_t)(uint32_t)r.skip << 32));
-                for (int k = 0; k < kSyncGroups; ++k)
-                    astore(sync_word(sync, kSyncFlag + k), word);
-                __builtin_amdgcn_s_waitcnt(0);
-                astore(claim, 0);  // after the flags: see small_wait
-            }
-        }
-    } else if (threadIdx.x == 0) {
-        uint64_t w = 0;
-        if (!small_wait(sync, grp, flag0, &w)) {
-            s_state = 2;
-        } else {
-            s_mult = __builtin_bit_cast(float, (uint32_t)w);
-            s_state = (int)((w >> 32) & 1);
-        }
-    }
-    __syncthreads();
-    if (s_state)
-        return;
-    const float mult = s_mult;
-
-    // 5. the update from the registers (workgroup 0 also takes head and tail)
-    if (b == 0)
-        adam_ends(g, th, m, v, p, n, head, nvec, mult, c);
-#pragma unroll
-    for (int u = 0; u < V; ++u) {
-        const int64_t i = (b * V + u) * kSmallBlock + threadIdx.x;
-        if (i < nvec) {
-            f32x4 to, mo, vo;
-            u32x2 po;
-            adam_vec4(gq[u], tq[u], mq[u], vq[u], mult, c, to, mo, vo, po);
-            const int64_t e = head + 4 * i;
-            st4<true>(to, th + e);
-            st4<true>(mo, m + e);
-            st4<true>(vo, v + e);
-            st4<true>(po, p + e);
         }
     }
 }

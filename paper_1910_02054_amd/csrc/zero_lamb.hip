@@ -550,7 +550,7 @@ int zero_lamb_step(const zero_lamb_plan_t* plan_, const uint16_t* grad16, float*
     if (rc || (rc = rc_done))
         return rc;
     zs::Result r;
-    if ((rc = wait_result(ctx.get(), seq, stream, &r)))
+    if ((rc = wait_result(ctx.get(), seq, stream, loss_scale, clip, &r)))
         return rc;
     set_last_stats(r, n);
     return r.skip ? ZERO_SKIPPED : ZERO_OK;

@@ -26,6 +26,7 @@
 
 #include "zero_shard.h"
 #include "shard_kernels.hpp"
+#include "small_kernels.hpp"
 #include "probe_kernels.hpp"
 #include "host_common.hpp"
 
@@ -61,18 +62,17 @@ constexpr bool kAdamNTL = true, kAdamNTS = true, kAdamXCD = false, kAdamREV = fa
 constexpr int64_t kAdamMaxBlocks = 1 << 26;
 constexpr int kCopyBlock = 64, kCopyUnroll = 1;
 constexpr bool kCopyNTL = true, kCopyNTS = true, kCopyXCD = false;
-// One-launch small-shard step (k_small_step): shards of at most kSmallMaxNumel
-// elements whose fp32 arrays share one misalignment (the fp16 arrays may start
-// at any element), on a grid of at most kSmallMaxGrid workgroups (each totals every workgroup's partial).
-#ifndef ZS_SMALL_MAX_NUMEL
-#define ZS_SMALL_MAX_NUMEL (1 << 22)
-#endif
-constexpr int64_t kSmallMaxNumel = ZS_SMALL_MAX_NUMEL;
-constexpr int64_t kSmallMaxGrid = 512;
+// One-launch small-shard step (k_small_step): shards whose fp32 arrays share
+// one misalignment (the fp16 arrays may start at any element) and that give a
+// workgroup at most zs::kSmallTiles tiles: 1.5M elements on a full grid of 256
+// workgroups, the limit that the interface states.  Up to there the grid holds
+// the chip about as well as the update's own launch and saves two launches:
+// 1.5M elements take 13.1 us a step, 15.4 in the kernel sequence.  (With more
+// tiles the gain is gone at 8M: 44.1 against 44.6 us.)
 // A grid takes at most 1/share of the device's co-resident capacity, where
 // share is the number of hardware queues the process may use (at least
 // kSmallCapShare; HIP gives a process four unless GPU_MAX_HW_QUEUES says
-// otherwise), so the barrier-waiting workgroups of small steps running at once
+// otherwise), so the waiting workgroups of small steps running at once
 // on every queue always fit on the device together.
 #ifndef ZS_SMALL_CAP_SHARE
 #define ZS_SMALL_CAP_SHARE 4
@@ -88,11 +88,6 @@ int64_t small_cap_share() {
     }
     return share;
 }
-constexpr int kSmallV[4] = {1, 2, 4, 8};
-#ifndef ZS_SMALL_FIRST_V
-#define ZS_SMALL_FIRST_V 0
-#endif
-constexpr int kSmallFirstV = ZS_SMALL_FIRST_V;  // index into kSmallV of the first variant tried
 
 // ---------------------------------------------------------------------------
 // Launch planning.  One function decides every launch shape from n and the
@@ -104,8 +99,7 @@ struct Plan {
     int64_t head, nvec;    // update: head elements, 4-element vectors
     int64_t adam_blocks;
     bool one_phase;        // the fp32 arrays share one misalignment
-    int small_v;           // one-launch small-shard step: vectors per thread (0: not taken)
-    int64_t small_grid;
+    int64_t small_grid;    // one-launch small-shard step: its workgroups (0: not taken)
 };
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -139,24 +133,13 @@ Plan plan_step(const uint16_t* g, const float* th, const float* m, const float* 
     return pl;
 }
 
-// The one-launch small-shard step when the shard qualifies: the fewest vectors
-// per thread whose grid fits both kSmallMaxGrid and the device's co-resident
-// capacity for that kernel.
-void plan_small(Plan* pl, int64_t n, const DevInfo* info) {
-    pl->small_v = 0;
-    pl->small_grid = 0;
-    if (!pl->one_phase || n > kSmallMaxNumel)
-        return;
-    for (int k = kSmallFirstV; k < 4; ++k) {
-        int64_t grid = ceil_div(pl->nvec, (int64_t)zs::kSmallBlock * kSmallV[k]);
-        if (grid < 1)
-            grid = 1;
-        if (grid <= kSmallMaxGrid && grid <= info->small_cap[k] / info->small_share) {
-            pl->small_v = kSmallV[k];
-            pl->small_grid = grid;
-            return;
-        }
-    }
+// The one-launch small-shard step when the shard qualifies: one tile per
+// workgroup while the grid fits the slots and the device's co-resident capacity,
+// up to zs::kSmallTiles in turn above.
+void plan_small(Plan* pl, const DevInfo* info) {
+    const int64_t most = std::min<int64_t>(zs::kSmallSlots, info->small_cap / info->small_share);
+    const int64_t tiles = std::max<int64_t>(1, ceil_div(pl->nvec, zs::kSmallBlock));
+    pl->small_grid = pl->one_phase && tiles <= most * zs::kSmallTiles ? std::min(most, tiles) : 0;
 }
 
 // Dynamic LDS that caps the resident workgroups of `kernel` (launched with
@@ -191,15 +174,6 @@ size_t occupancy_lds(const void* kernel, int block, int per_cu, const hipDeviceP
     }
 }
 
-const void* small_kernel(int v) {
-    switch (v) {
-    case 1: return reinterpret_cast<const void*>(zs::k_small_step<1>);
-    case 2: return reinterpret_cast<const void*>(zs::k_small_step<2>);
-    case 4: return reinterpret_cast<const void*>(zs::k_small_step<4>);
-    default: return reinterpret_cast<const void*>(zs::k_small_step<8>);
-    }
-}
-
 // ---------------------------------------------------------------------------
 // Per-device facts, computed once per device into a fixed table.
 // ---------------------------------------------------------------------------
@@ -227,15 +201,13 @@ int dev_info(int dev, const DevInfo** out) {
             d.probe_adam_lds = occupancy_lds(
                 reinterpret_cast<const void*>(zs::k_probe_adam<kAdamBlock, kAdamUnroll, kAdamNTL, kAdamNTS, kAdamXCD>),
                 kAdamBlock, kAdamPerCU, prop, &d.probe_adam_resident);
-            for (int k = 0; k < 4; ++k) {
-                int per_cu = 0;
-                if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, small_kernel(kSmallV[k]), zs::kSmallBlock,
-                                                                 0) != hipSuccess) {
-                    (void)hipGetLastError();
-                    per_cu = 0;
-                }
-                d.small_cap[k] = (int64_t)per_cu * d.ncu;
+            int per_cu = 0;
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(zs::k_small_step),
+                                                             zs::kSmallBlock, 0) != hipSuccess) {
+                (void)hipGetLastError();
+                per_cu = 0;
             }
+            d.small_cap = (int64_t)per_cu * d.ncu;
             d.small_share = small_cap_share();
             g_dev[dev] = d;
             g_dev_ready[dev].store(true, std::memory_order_release);
@@ -252,14 +224,16 @@ int dev_info(int dev, const DevInfo** out) {
 std::mutex g_ctx_mu;
 std::map<std::pair<int, hipStream_t>, std::shared_ptr<Ctx>> g_ctx;
 
+constexpr size_t kHostWords = 8;  // the two published words, on a line of their own
+
 void free_ctx_buffers(Ctx* c) {
     if (c->part) (void)hipFree(c->part);
     if (c->res) (void)hipFree(c->res);
-    if (c->sync) (void)hipFree(c->sync);
+    if (c->slots.words) (void)hipFree(c->slots.words);
     if (c->host) (void)hipHostFree(c->host);
     c->part = nullptr;
     c->res = nullptr;
-    c->sync = nullptr;
+    c->slots = Slots{};
     c->host = c->host_dev = nullptr;
 }
 
@@ -289,11 +263,11 @@ int new_ctx(int dev, hipStream_t stream, const DevInfo* info, std::shared_ptr<Ct
     c->stream = stream;
     c->info = info;
     RelaxedCapture relaxed(stream);
-    // the barrier words are zeroed on the stream before the first small-shard launch
+    // the slots are zeroed on the stream before the first small-shard launch
     bool ok = hipMalloc(reinterpret_cast<void**>(&c->part), sizeof(zs::Partial) * zs::kMaxStatsBlocks) == hipSuccess &&
               hipMalloc(reinterpret_cast<void**>(&c->res), sizeof(zs::Result)) == hipSuccess &&
-              hipMalloc(reinterpret_cast<void**>(&c->sync), sizeof(uint64_t) * zs::kSyncWords) == hipSuccess &&
-              hipHostMalloc(reinterpret_cast<void**>(&c->host), sizeof(zs::Result),
+              hipMalloc(reinterpret_cast<void**>(&c->slots.words), sizeof(uint64_t) * zs::kSlotWords) == hipSuccess &&
+              hipHostMalloc(reinterpret_cast<void**>(&c->host), kHostWords * sizeof(uint64_t),
                             hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess &&
               hipHostGetDevicePointer(reinterpret_cast<void**>(&c->host_dev), c->host, 0) == hipSuccess;
     if (!ok) {
@@ -301,7 +275,7 @@ int new_ctx(int dev, hipStream_t stream, const DevInfo* info, std::shared_ptr<Ct
         (void)hipGetLastError();
         return fail(ZERO_ENOMEM, "could not allocate the step workspace on device %d", dev);
     }
-    std::memset(c->host, 0, sizeof(zs::Result));
+    std::memset(c->host, 0, kHostWords * sizeof(uint64_t));
     *out = std::move(c);
     return ZERO_OK;
 }
@@ -591,7 +565,7 @@ zs::AdamConst adam_const(double lr, double beta1, double beta2, double eps, doub
 }
 
 // Statistics + finalize: the result record lands in res and host_dev.
-int launch_stats_into(const DevInfo* info, zs::Partial* part, zs::Result* res, zs::Result* host_dev,
+int launch_stats_into(const DevInfo* info, zs::Partial* part, zs::Result* res, uint64_t* host_dev,
                       const uint16_t* grad16, int64_t n, const Plan& pl, double loss_scale, double clip, uint32_t seq,
                       hipStream_t stream) {
     zs::k_stats<kStatsBlock, kStatsUnroll, kStatsNTL, kStatsXCD>
@@ -636,43 +610,49 @@ int launch_update(Ctx* ctx, const uint16_t* grad16, float* master32, float* m32,
     return launch_update_from(ctx->info, ctx->res, grad16, master32, m32, v32, param16_out, n, pl, c, stream);
 }
 
-// The one-launch small-shard step (pl.small_v > 0) with its partials in `part`
-// and its barrier words at `sync` (zeroed on the stream first when
-// *sync_ready is false).
-int launch_small_into(uint64_t* part, uint64_t* sync, bool* sync_ready, zs::Result* res, zs::Result* host_dev,
-                      const uint16_t* grad16, float* master32, float* m32, float* v32, uint16_t* param16_out,
-                      int64_t n, const Plan& pl, double loss_scale, double clip, uint32_t seq, const zs::AdamConst& c,
-                      hipStream_t stream) {
-    if (!*sync_ready) {
-        zs::k_zero_words<<<1, 256, 0, stream>>>(sync, zs::kSyncWords);
+// The one-launch small-shard step (pl.small_grid > 0) with its exchange slots
+// (zeroed on the stream first when they are not ready).
+int launch_small_into(Slots* slots, uint64_t* host_dev, const uint16_t* grad16, float* master32, float* m32,
+                      float* v32, uint16_t* param16_out, int64_t n, const Plan& pl, double loss_scale, double clip,
+                      uint32_t seq, const zs::AdamConst& c, hipStream_t stream) {
+    if (!slots->ready) {
+        zs::k_zero_words<<<1, 256, 0, stream>>>(slots->words, zs::kSlotWords);
         HIP_TRY(hipGetLastError());
-        *sync_ready = true;
+        slots->ready = true;
     }
-    const dim3 grid((unsigned)pl.small_grid), block(zs::kSmallBlock);
-#define ZS_SMALL_LAUNCH(V)                                                                                      \
-    zs::k_small_step<V><<<grid, block, 0, stream>>>(grad16, master32, m32, v32, param16_out, n, pl.head, pl.nvec, \
-                                                    part, sync, res, host_dev, loss_scale, clip, seq, c)
-    switch (pl.small_v) {
-    case 1: ZS_SMALL_LAUNCH(1); break;
-    case 2: ZS_SMALL_LAUNCH(2); break;
-    case 4: ZS_SMALL_LAUNCH(4); break;
-    default: ZS_SMALL_LAUNCH(8); break;
-    }
-#undef ZS_SMALL_LAUNCH
+    uint64_t* const fill = slots->words + slots->set * zs::kSmallSlots;
+    uint64_t* const empty = slots->words + (1 - slots->set) * zs::kSmallSlots;
+    zs::k_small_step<<<(unsigned)pl.small_grid, zs::kSmallBlock, 0, stream>>>(
+        grad16, master32, m32, v32, param16_out, n, pl.head, pl.nvec, fill, empty, host_dev, loss_scale, clip, seq, c);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return fail(ZERO_EHIP, "launch of the small-shard step (%lld workgroups): %s", (long long)pl.small_grid,
                     hipGetErrorString(e));
+    slots->set = 1 - slots->set;
     return ZERO_OK;
 }
 
-// Wait until the finalize kernel has published call `seq` in the host-mapped
-// record (it writes the record, then the sequence number with a system-scope
-// release), then read it.  No event is recorded on the stream for this: event
-// markers between kernels cost several microseconds of GPU idle time each.
-int wait_result(Ctx* ctx, uint32_t seq, hipStream_t stream, zs::Result* out) {
+// The sum that two published words of call `seq` carry (see publish_sum);
+// false while either is of another call.
+bool published(uint64_t w0, uint64_t w1, uint32_t seq, double* sum) {
+    if ((uint32_t)(w0 >> 32) != seq || (uint32_t)(w1 >> 32) != seq)
+        return false;
+    const uint64_t bits = (w0 & 0xFFFFFFFFu) | (w1 << 32);
+    std::memcpy(sum, &bits, sizeof *sum);
+    return true;
+}
+
+// Wait until the device has published call `seq`.  No event is recorded on the
+// stream for this: event markers between kernels cost several microseconds of
+// GPU idle time each.
+int wait_result(Ctx* ctx, uint32_t seq, hipStream_t stream, double loss_scale, double clip, zs::Result* out) {
+    double sum = 0.0;
+    const auto ready = [&] {
+        return published(__atomic_load_n(ctx->host, __ATOMIC_RELAXED), __atomic_load_n(ctx->host + 1, __ATOMIC_RELAXED),
+                         seq, &sum);
+    };
     uint64_t polls = 0;
-    while (__atomic_load_n(&ctx->host->seq, __ATOMIC_ACQUIRE) != seq) {
+    while (!ready()) {
         // spin for the usual wait (the statistics of one shard: microseconds); once the stream
         // has been busy for a few milliseconds (other work queued ahead), sleep between checks
         // instead of holding a core
@@ -683,15 +663,15 @@ int wait_result(Ctx* ctx, uint32_t seq, hipStream_t stream, zs::Result* out) {
         if ((++polls & 0xFFF) == 0 || polls > ((uint64_t)1 << 18)) {
             const hipError_t e = hipStreamQuery(stream);
             if (e == hipSuccess) {  // everything queued has finished
-                if (__atomic_load_n(&ctx->host->seq, __ATOMIC_ACQUIRE) == seq)
+                if (ready())
                     break;
-                return fail(ZERO_EHIP, "result record %u not published although the stream is idle", seq);
+                return fail(ZERO_EHIP, "statistics of call %u not published although the stream is idle", seq);
             }
             if (e != hipErrorNotReady)
                 return fail(ZERO_EHIP, "stream failed while waiting for the statistics: %s", hipGetErrorString(e));
         }
     }
-    std::memcpy(out, (const void*)ctx->host, sizeof *out);
+    *out = zs::make_result(sum, loss_scale, clip, seq);
     return ZERO_OK;
 }
 
@@ -760,16 +740,16 @@ int resident_ws(int dev, const void* state, hipStream_t stream, ResWs** out) {
 // ---------------------------------------------------------------------------
 // The allocation-free step's workspace: one fixed device array per GPU (each
 // device that loads the library holds its own copy until the process ends),
-// laid out as the statistics partials, the one-launch step's barrier words,
-// the result record and a second record that stands in for the host-mapped
-// one (the host copies it out instead).  In host code `scratch` names a
+// laid out as the statistics partials, the one-launch step's exchange slots,
+// the result record and two words that stand in for the host-mapped ones (the
+// host copies them out instead).  In host code `scratch` names a
 // host-side stand-in; the device address comes from hipGetSymbolAddress.
 // ---------------------------------------------------------------------------
 constexpr size_t kScratchPart = 0;
-constexpr size_t kScratchSync = kScratchPart + sizeof(zs::Partial) * zs::kMaxStatsBlocks;
-constexpr size_t kScratchRes = kScratchSync + sizeof(uint64_t) * zs::kSyncWords;
-constexpr size_t kScratchRes2 = kScratchRes + 256;
-constexpr size_t kScratchBytes = kScratchRes2 + 256;
+constexpr size_t kScratchSlots = kScratchPart + sizeof(zs::Partial) * zs::kMaxStatsBlocks;
+constexpr size_t kScratchRes = kScratchSlots + sizeof(uint64_t) * zs::kSlotWords;
+constexpr size_t kScratchHost = kScratchRes + 256;
+constexpr size_t kScratchBytes = kScratchHost + 256;
 static_assert(kScratchRes % 256 == 0 && sizeof(zs::Result) <= 256, "scratch layout");
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
@@ -777,7 +757,8 @@ static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 struct ScratchDev {
     std::mutex mu;           // serialises this device's allocation-free calls on the host side
     unsigned char* ptr = nullptr;  // the device's copy of `scratch`
-    bool sync_ready = true;  // the barrier words are zero (as loaded) or were cleared
+    bool slots_ready = true;  // the slots are empty (as loaded) or were emptied
+    int slots_set = 0;
     uint32_t seq = 0;
 };
 ScratchDev g_scratch[kMaxDevices];
@@ -946,7 +927,7 @@ int zero_shard_step(const uint16_t* grad16, float* master32, float* m32, float* 
         return rc;
     const zs::AdamConst c = adam_const(lr, beta1, beta2, eps, weight_decay, step);
     Plan pl = plan_step(grad16, master32, m32, v32, n, ctx->info->ncu);
-    plan_small(&pl, n, ctx->info);
+    plan_small(&pl, ctx->info);
     const uint32_t seq = next_seq(ctx.get());
 
     ProfRec pr{};
@@ -955,13 +936,12 @@ int zero_shard_step(const uint16_t* grad16, float* master32, float* m32, float* 
         return prof;
     if (prof)
         prof_record(pr.start, stream, &pr);
-    if (pl.small_v) {
+    if (pl.small_grid) {
         // one launch: its whole time counts as the update's
         if (prof)
             prof_record(pr.mid, stream, &pr);
-        rc = launch_small_into(reinterpret_cast<uint64_t*>(ctx->part), ctx->sync, &ctx->sync_ready, ctx->res,
-                               ctx->host_dev, grad16, master32, m32, v32, param16_out, n, pl, loss_scale, clip, seq,
-                               c, stream);
+        rc = launch_small_into(&ctx->slots, ctx->host_dev, grad16, master32, m32, v32, param16_out, n, pl, loss_scale,
+                               clip, seq, c, stream);
     } else {
         rc = launch_stats_into(ctx->info, ctx->part, ctx->res, ctx->host_dev, grad16, n, pl, loss_scale, clip, seq,
                                stream);
@@ -983,12 +963,12 @@ int zero_shard_step(const uint16_t* grad16, float* master32, float* m32, float* 
     }
     // The update is already queued: wait only for the statistics.
     zs::Result r;
-    if ((rc = wait_result(ctx.get(), seq, stream, &r))) {
-        if (pl.small_v)
-            ctx->sync_ready = false;  // an aborted launch's barrier words are cleared before the next
+    if ((rc = wait_result(ctx.get(), seq, stream, loss_scale, clip, &r))) {
+        if (pl.small_grid)
+            ctx->slots.ready = false;  // an aborted launch's slots are emptied before the next
         return rc;
     }
-    set_stats(r, n, pl.small_v ? 1 : 0);
+    set_stats(r, n, pl.small_grid ? 1 : 0);
     return r.skip ? ZERO_SKIPPED : ZERO_OK;
 }
 
@@ -1018,7 +998,7 @@ int zero_shard_stats(const uint16_t* grad16, int64_t n, double* local_sumsq, voi
     if ((rc = launch_stats_planned(ctx.get(), grad16, n, 1.0, 0.0, seq, stream)))
         return rc;
     zs::Result r;
-    if ((rc = wait_result(ctx.get(), seq, stream, &r)))
+    if ((rc = wait_result(ctx.get(), seq, stream, 1.0, 0.0, &r)))
         return rc;
     *local_sumsq = r.sumsq;
     return ZERO_OK;
@@ -1390,39 +1370,42 @@ int zero_shard_step_noalloc(const uint16_t* grad16, float* master32, float* m32,
     if ((rc = scratch_ptr(dev, &base)))
         return rc;
     zs::Partial* part = reinterpret_cast<zs::Partial*>(base + kScratchPart);
-    uint64_t* sync = reinterpret_cast<uint64_t*>(base + kScratchSync);
+    Slots slots{reinterpret_cast<uint64_t*>(base + kScratchSlots), sd.slots_ready, sd.slots_set};
     zs::Result* res = reinterpret_cast<zs::Result*>(base + kScratchRes);
-    zs::Result* res2 = reinterpret_cast<zs::Result*>(base + kScratchRes2);
+    uint64_t* words = reinterpret_cast<uint64_t*>(base + kScratchHost);
     const zs::AdamConst c = adam_const(lr, beta1, beta2, eps, weight_decay, step);
     Plan pl = plan_step(grad16, master32, m32, v32, n, info->ncu);
-    plan_small(&pl, n, info);
-    if (pl.stats_blocks > zs::kMaxStatsBlocks || pl.small_grid > (int64_t)zs::kMaxStatsBlocks)
+    plan_small(&pl, info);
+    if (pl.stats_blocks > zs::kMaxStatsBlocks)
         return fail(ZERO_EINVAL, "%s: launch needs more partials than the fixed workspace holds", fn);
     if (++sd.seq == 0)
         ++sd.seq;
     const uint32_t seq = sd.seq;
-    if (pl.small_v) {
-        rc = launch_small_into(reinterpret_cast<uint64_t*>(part), sync, &sd.sync_ready, res, res2, grad16, master32,
-                               m32, v32, param16_out, n, pl, loss_scale, clip, seq, c, stream);
+    if (pl.small_grid) {
+        rc = launch_small_into(&slots, words, grad16, master32, m32, v32, param16_out, n, pl, loss_scale, clip, seq, c,
+                               stream);
+        sd.slots_ready = slots.ready;
+        sd.slots_set = slots.set;
     } else {
-        rc = launch_stats_into(info, part, res, res2, grad16, n, pl, loss_scale, clip, seq, stream);
+        rc = launch_stats_into(info, part, res, words, grad16, n, pl, loss_scale, clip, seq, stream);
         if (!rc)
             rc = launch_update_from(info, res, grad16, master32, m32, v32, param16_out, n, pl, c, stream);
     }
     if (rc)
         return rc;
-    // the record comes back with a copy after the update: the call returns once the whole
-    // step has completed on the stream
-    zs::Result r;
-    std::memset(&r, 0, sizeof r);
-    HIP_TRY(hipMemcpyAsync(&r, res2, sizeof r, hipMemcpyDeviceToHost, stream));
+    // the sum comes back with a copy after the update: the call returns once the whole step has
+    // completed on the stream
+    uint64_t w[2] = {0, 0};
+    double sum = 0.0;
+    HIP_TRY(hipMemcpyAsync(w, words, sizeof w, hipMemcpyDeviceToHost, stream));
     HIP_TRY(hipStreamSynchronize(stream));
-    if (r.seq != seq) {
-        if (pl.small_v)
-            sd.sync_ready = false;  // an aborted launch's barrier words are cleared before the next
-        return fail(ZERO_EHIP, "%s: result record %u not published by the step's kernels", fn, seq);
+    if (!published(w[0], w[1], seq, &sum)) {
+        if (pl.small_grid)
+            sd.slots_ready = false;  // an aborted launch's slots are emptied before the next
+        return fail(ZERO_EHIP, "%s: statistics of call %u not published by the step's kernels", fn, seq);
     }
-    set_stats(r, n, pl.small_v ? 1 : 0);
+    const zs::Result r = zs::make_result(sum, loss_scale, clip, seq);
+    set_stats(r, n, pl.small_grid ? 1 : 0);
     return r.skip ? ZERO_SKIPPED : ZERO_OK;
 }
 

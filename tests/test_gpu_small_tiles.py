@@ -1,0 +1,52 @@
+"""GPU test of the one-launch small-shard step at the edges of its tiles (2048
+elements) and of its grid (256 workgroups, then a second and a third tile per
+workgroup), and just past its last size, where the kernel sequence takes over.
+Steps alternate between two lengths on one stream, so the exchange slots are
+filled and emptied by grids of different sizes.  Against the oracle; the update's
+fp32 operations are each correctly rounded in the oracle's order, so the bound
+is the repository's 1e-6 and the observed difference is zero bits."""
+import os
+import sys
+
+import pytest
+
+sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
+import gpu_harness as H  # noqa: E402
+
+from paper_1910_02054_amd import workloads  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+HP = (1e-3, 0.9, 0.999, 1e-8, 0.01)
+T, G = 2048, 256
+
+
+@pytest.mark.parametrize("n,overflow", [(T - 1, False), (T, False), (T + 1, False), (2 * T + 3, True), (G * T - 1, False),
+                                        (G * T, True), (G * T + 1, False), (G * T + T + 1, False),
+                                        (2 * G * T + 1, True), (3 * G * T, False), (3 * G * T + 5, False)])
+def test_small_step_tile_and_grid_edges(n, overflow):
+    import torch
+    from paper_1910_02054_amd import binding as zb
+    dev = torch.device("cuda:0")
+    dts = (torch.float16, torch.float32, torch.float32, torch.float32, torch.float16)
+    sets = []
+    for k, length in enumerate((n, T // 2)):
+        bufs = [H.Guarded(torch, length, dt, dev) for dt in dts]
+        g16, theta, m, v = workloads.random_case(81 + k, length)
+        if overflow and k == 0:
+            g16[-1] = workloads.F16_POS_INF
+        host = [g16, theta, m, v, workloads.p16_sentinel(length)]
+        for b, a in zip(bufs, host):
+            b.upload(a)
+        sets.append((bufs, g16, [a.copy() for a in host[1:]]))
+    for t in (1, 2, 3):
+        for bufs, g16, ref in sets:
+            flag = zb.zero_shard_step(*(b.view for b in bufs), *HP, t, 2.0 ** 16, 1.0)
+            skip, sc = H.oracle_step(g16, *ref, *HP, t, 2.0 ** 16, 1.0)
+            st = zb.zero_shard_last_step_stats()
+            assert flag == skip == (1 if overflow and g16.size == n else 0)
+            assert st.skipped == skip and (skip or st.mult == sc.mult)
+    torch.cuda.synchronize()
+    for bufs, _, ref in sets:
+        d = H.compare_state([b.download() for b in bufs[1:]], ref)
+        assert all(b.guards_intact() for b in bufs)
+        print("[gpu-small-tiles] n=%d %s" % (n, d), flush=True)
