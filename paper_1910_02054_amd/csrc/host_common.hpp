@@ -57,6 +57,18 @@ struct Slots {
     int set = 0;                // the set the next launch fills
 };
 
+// Slots of the statistics pass (zs::kStatsSlots words in device memory),
+// empty between launches.
+struct StatsSlots {
+    uint64_t* words = nullptr;
+    bool ready = false;         // the words have been zeroed on the stream
+};
+
+// Zeroes n slot words unless they are ready: on `stream`, or at once on a
+// stream of its own while `stream` is being captured (a graph's replays find
+// them empty, like any launch).
+int ready_slots(uint64_t* words, int64_t n, bool* ready, hipStream_t stream);
+
 // Per-(device, stream) context: the constant-size workspace of the gradient
 // statistics and the result record the update kernels read.  A context is
 // shared (std::shared_ptr) between the registry and the calls using it, so a
@@ -68,7 +80,7 @@ struct Ctx {
     std::mutex mu;
     int dev = 0;
     hipStream_t stream = nullptr;
-    zs::Partial* part = nullptr;    // kMaxStatsBlocks partial records (device)
+    StatsSlots stats;               // slots of the statistics pass (device)
     zs::Result* res = nullptr;      // result record (device), read by the update kernel
     uint64_t* host = nullptr;       // host-mapped, GPU-uncached words of the published sum
     uint64_t* host_dev = nullptr;   // their device-side address
@@ -117,8 +129,8 @@ size_t occupancy_lds(const void* kernel, int block, int per_cu, const hipDeviceP
 // The fp32 constants of the Adam moments and direction.
 zs::AdamConst adam_const(double lr, double beta1, double beta2, double eps, double wd, int64_t step);
 
-// Statistics + finalize of grad16[0, n) with the production launch shape; the
-// result record lands in ctx->res and the sum in the host-mapped ctx->host.
+// Statistics of grad16[0, n) with the production launch shape; the result
+// record lands in ctx->res and the sum in the host-mapped ctx->host.
 int launch_stats_planned(Ctx* ctx, const uint16_t* grad16, int64_t n, double loss_scale, double clip, uint32_t seq,
                          hipStream_t stream);
 

@@ -5,27 +5,24 @@
 // updates only that partition's fp32 master parameters, momentum and variance
 // (Sec. 3.1's mixed-precision Adam), then publishes the fp16 parameters.
 //
-// Three kernels run per step, all HBM-streaming (no dense contraction, so no
+// Two kernels run per step, all HBM-streaming (no dense contraction, so no
 // MFMA):
 //   k_stats     one read of the fp16 gradients; per-workgroup fp64 sum of the
-//               exact fp32 squares (wave shuffle, then LDS across waves).  The
-//               sum is non-finite iff some gradient is inf or NaN, which is the
+//               exact fp32 squares, totalled by the last workgroup.  The sum is
+//               non-finite iff some gradient is inf or NaN, which is the
 //               overflow test (every finite square is below 2^32, so no finite
-//               sum over fewer than 2^990 elements overflows fp64).
-//   k_finalize  one workgroup: fixed-order reduction of the partials; the norm
-//               of the unscaled gradient, the global-norm clipping coefficient,
-//               the fp32 gradient multiplier and the skip flag, written to
-//               device memory, and the sum to the host.
+//               sum over fewer than 2^990 elements overflows fp64).  From it the
+//               norm of the unscaled gradient, the global-norm clipping
+//               coefficient, the fp32 gradient multiplier and the skip flag go
+//               to device memory, and the sum to the host.
 //   k_adam_vec  the fused update: unscale+clip, Adam with bias correction, fp16
 //               cast; 14 bytes read and 14 bytes written per element.
 // Small shards take one launch instead (k_small_step in small_kernels.hpp).
-// The other ways of running the same step swap only the one-thread kernels
-// around these: the split phase takes the global sum from the host
-// (k_set_result) or from device memory (k_finalize_sum writes a rank's local
-// sum, k_set_result_dev reads the combined one); the resident step's
-// k_resident_begin takes the finalize's place and also derives the fp32
-// constants from a state record in device memory and runs the loss-scale
-// schedule there.
+// The other ways of running the same step change what follows the statistics
+// total (FinishStep, FinishSum, FinishResident) or where the scalars come from:
+// the split phase takes the global sum from the host (k_set_result) or from
+// device memory (k_set_result_dev), the resident step its hyperparameters and
+// loss scale from a state record in device memory.
 //
 // Numerics: every fp32 operation of the update is correctly rounded (IEEE
 // division and square root, no contraction), in the order Adam's bias-corrected
@@ -124,13 +121,7 @@ __device__ __forceinline__ int64_t logical_block() {
     return b;
 }
 
-// Per-workgroup partial of the statistics pass.
-struct alignas(16) Partial {
-    double sumsq;
-    double unused;
-};
-
-// The step's shared scalars, produced on the device by k_finalize and read by
+// The step's shared scalars, produced on the device by k_stats and read by
 // the update kernel.
 struct alignas(16) Result {
     double sumsq;    // sum of grad16^2 (loss-scaled); non-finite iff overflow
@@ -250,27 +241,49 @@ __device__ __forceinline__ double wave_sum(double x) {
     return x;
 }
 
-// Fixed-order sum of one double per thread over a workgroup of BLOCK threads;
-// the total is returned to thread 0.
-template <int BLOCK>
-__device__ __forceinline__ double block_sum(double x) {
-    __shared__ double lds[BLOCK / 64];
-    x = wave_sum(x);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if constexpr (BLOCK == 64) {
-        return x;
-    } else {
-        if (lane == 0)
-            lds[wave] = x;
-        __syncthreads();
-        double s = 0.0;
-        if (threadIdx.x == 0) {
+// A sum carried with its rounding error (each addition's error is recovered
+// exactly), so that the total of the workgroups' sums is theirs to about 2^-100
+// before its one rounding, whatever the order: the one-launch step and the
+// statistics pass cut the shard differently and report the same bits (but for a
+// tie within the sums' own last bits).
+struct Sum2 {
+    double hi, lo;
+};
+
+__device__ __forceinline__ Sum2 sum2_add(Sum2 a, Sum2 b) {
+    const double s = a.hi + b.hi, t = s - a.hi;
+    return Sum2{s, (a.lo + b.lo) + ((a.hi - (s - t)) + (b.hi - t))};
+}
+
+// An overflowed sum's error term is NaN: the sum itself is the value then.
+__device__ __forceinline__ double sum2_value(Sum2 a) { return __builtin_isfinite(a.hi) ? a.hi + a.lo : a.hi; }
+
+__device__ __forceinline__ Sum2 wave_sum2(Sum2 x) {
 #pragma unroll
-            for (int w = 0; w < BLOCK / 64; ++w)
-                s += lds[w];
-        }
-        return s;
-    }
+    for (int off = 32; off >= 1; off >>= 1)
+        x = sum2_add(x, Sum2{__shfl_xor(x.hi, off, 64), __shfl_xor(x.lo, off, 64)});
+    return x;
+}
+
+// A workgroup's sum on its way to the others of its launch: a 64-bit slot in
+// device memory that is empty (0) before the launch and is filled with the
+// sum's bits under a set sign bit (a sum of squares is never negative), so one
+// word carries the sum and that it is there.  Slots are accessed with
+// agent-scope atomic operations, which the device keeps coherent across its
+// XCDs without writing back or invalidating the L2 caches.
+constexpr uint64_t kSlotFilled = (uint64_t)1 << 63;
+constexpr uint64_t kSlotAbort = ~(uint64_t)0;          // not the bits of a sum of fp16 squares
+constexpr uint32_t kSlotSpinLimit = 1u << 22;          // polls of about 0.5-1 us each
+
+__device__ __forceinline__ uint64_t slot_word(double x) { return __builtin_bit_cast(uint64_t, x) | kSlotFilled; }
+__device__ __forceinline__ double slot_sum(uint64_t w) { return __builtin_bit_cast(double, w & ~kSlotFilled); }
+
+__device__ __forceinline__ uint64_t aload(const uint64_t* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ void astore(uint64_t* p, uint64_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Norm, clipping coefficient, multiplier and skip flag from the global sum of
@@ -306,24 +319,84 @@ __device__ __forceinline__ void publish_sum(uint64_t* __restrict__ host, double 
     __hip_atomic_store(host + 1, tag | (w >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// What becomes of the statistics total, by one lane of the last workgroup of
+// k_stats.  `before` runs at that workgroup's start, ahead of the wait for the
+// other workgroups' sums;
+// `ok` is false when that wait was given up (then nothing may be updated).
+// The fused step: the result record, and the sum to the host.
+struct FinishStep {
+    Result* res;
+    uint64_t* host;
+    double loss_scale, clip;
+    uint32_t seq;
+    __device__ __forceinline__ void before() {}
+    __device__ __forceinline__ void total(double tot, bool ok) {
+        if (ok)
+            publish_sum(host, tot, seq);
+        *res = make_result(ok ? tot : __builtin_nan(""), loss_scale, clip, seq);
+    }
+};
+
+// The asynchronous split phase: the sum into caller device memory.
+struct FinishSum {
+    double* out;
+    __device__ __forceinline__ void before() {}
+    __device__ __forceinline__ void total(double tot, bool ok) { *out = ok ? tot : __builtin_nan(""); }
+};
+
+// `own` plus the total of slots[0, count), count < 64, by one wave in a fixed
+// order: waits until each slot is filled and empties it for the next launch.
+// *ok turns false when a slot stays empty for too long or holds kSlotAbort.
+__device__ __forceinline__ double drain_slots(uint64_t* slots, int count, double own, bool* ok) {
+    const int lane = (int)threadIdx.x & 63;
+    Sum2 s{lane == 63 ? own : 0.0, 0.0};
+    bool fine = true;
+    if (lane < count) {
+        uint64_t w = aload(slots + lane);
+        for (uint32_t polls = 0; w == 0 && polls < kSlotSpinLimit; ++polls)
+            w = aload(slots + lane);
+        fine = w != 0 && w != kSlotAbort;
+        astore(slots + lane, 0);
+        s.hi = slot_sum(w);
+    }
+    *ok = *ok && __all(fine);
+    return sum2_value(wave_sum2(s));
+}
+
 // ---------------------------------------------------------------------------
 // K1: statistics.  `head` leading elements (0..63) lie before the gradient's
-// first cache line and `nvec` 8-element vectors follow; elements [head + 8*nvec, n) are the tail.
-// Grid: 1 .. kMaxStatsBlocks workgroups of BLOCK threads; workgroup b writes
-// part[b].
+// first cache line and `nvec` 8-element vectors follow; elements
+// [head + 8*nvec, n) are the tail.  Grid: 1 .. kMaxStatsBlocks workgroups of one
+// wave.  The workgroups' sums meet in two levels, each a fixed-order sum
+// (bitwise reproducible for a given launch shape): workgroup b fills slot b, the
+// last workgroup of every 64 drains its group's slots and fills the group's
+// slot, and the last workgroup of all drains those and finishes (FIN).  A
+// workgroup waits only for workgroups before it, which need nothing from it, so
+// every wait ends however few are resident; it is bounded all the same.
+// Reading the gradient bounds the pass on large shards; the total costs two
+// round trips at its end, where a kernel of its own (of one workgroup) took 3.5
+// to 4.6 us a step.  (One level, the last workgroup draining all 2047 slots,
+// took 4 us more than that kernel.)  Steps before and after: resident 1M 14.9 ->
+// 13.3 us and 20K 14.8 -> 11.4, fused 5.9M 36.1 -> 35.3, 94M 420 -> 417.5, 250M
+// 1116 -> 1115.
 // ---------------------------------------------------------------------------
-template <int BLOCK, int U, bool NTL, bool XCD>
-__global__ __launch_bounds__(BLOCK) void k_stats(const uint16_t* __restrict__ g, int64_t n, int64_t head,
-                                                 int64_t nvec, Partial* __restrict__ part) {
+constexpr int kStatsSlots = kMaxStatsBlocks + kMaxStatsBlocks / 64;  // the workgroups', then the groups'
+static_assert(kMaxStatsBlocks <= 64 * 64, "one wave drains the groups");
+
+template <int U, bool NTL, bool XCD, typename FIN>
+__global__ __launch_bounds__(64) void k_stats(const uint16_t* __restrict__ g, int64_t n, int64_t head, int64_t nvec,
+                                              uint64_t* __restrict__ part, FIN fin) {
+    if (blockIdx.x == gridDim.x - 1)
+        fin.before();
     double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
     const u32x4* __restrict__ gv = reinterpret_cast<const u32x4*>(g + head);
-    const int64_t tile = (int64_t)BLOCK * U;
+    const int64_t tile = (int64_t)64 * U;
     const int64_t stride = (int64_t)gridDim.x * tile;
     for (int64_t base = logical_block<XCD>() * tile + threadIdx.x; base < nvec; base += stride) {
         u32x4 q[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t i = base + (int64_t)u * BLOCK;
+            const int64_t i = base + (int64_t)u * 64;
             q[u] = i < nvec ? ld<NTL>(gv + i) : u32x4{0u, 0u, 0u, 0u};
         }
 #pragma unroll
@@ -342,40 +415,24 @@ __global__ __launch_bounds__(BLOCK) void k_stats(const uint16_t* __restrict__ g,
         if (t < 8 && tail0 + t < n)
             a1 += sq1(g[tail0 + t]);
     }
-    const double s = block_sum<BLOCK>((a0 + a1) + (a2 + a3));
+    const double s = wave_sum((a0 + a1) + (a2 + a3));
+    const int b = (int)blockIdx.x, last = (int)gridDim.x - 1, member = b & 63;
+    if (member != 63 && b != last) {
+        if (threadIdx.x == 0)
+            astore(part + b, slot_word(s));
+        return;
+    }
+    bool ok = true;
+    if (b != last) {
+        const double t = drain_slots(part + (b - member), member, s, &ok);
+        if (threadIdx.x == 0)
+            astore(part + kMaxStatsBlocks + b / 64, ok ? slot_word(t) : kSlotAbort);
+        return;
+    }
+    double tot = drain_slots(part + (b - member), member, s, &ok);
+    tot = drain_slots(part + kMaxStatsBlocks, b / 64, tot, &ok);
     if (threadIdx.x == 0)
-        part[blockIdx.x].sumsq = s;
-}
-
-// ---------------------------------------------------------------------------
-// K2: finalize.  One workgroup of kFinalBlock threads; fixed-order reduction,
-// so the result depends only on the partials (bitwise reproducible for a given
-// launch shape).  `host` is two mapped, GPU-uncached words (publish_sum).
-// ---------------------------------------------------------------------------
-constexpr int kFinalBlock = 256;
-
-// The total of part[0, nparts) in a fixed order (every thread of the
-// kFinalBlock-thread workgroup returns it); 0 for nparts = 0.
-__device__ __forceinline__ double partials_total(const Partial* __restrict__ part, int nparts) {
-    double s0 = 0.0, s1 = 0.0;
-    int i = threadIdx.x;
-    for (; i + kFinalBlock < nparts; i += 2 * kFinalBlock) {
-        s0 += part[i].sumsq;
-        s1 += part[i + kFinalBlock].sumsq;
-    }
-    if (i < nparts)
-        s0 += part[i].sumsq;
-    return block_sum<kFinalBlock>(s0 + s1);
-}
-
-[[maybe_unused]] static __global__ __launch_bounds__(kFinalBlock) void k_finalize(
-    const Partial* __restrict__ part, int nparts, Result* __restrict__ res, uint64_t* __restrict__ host,
-    double loss_scale, double clip, uint32_t seq) {
-    const double tot = partials_total(part, nparts);
-    if (threadIdx.x == 0) {
-        publish_sum(host, tot, seq);
-        *res = make_result(tot, loss_scale, clip, seq);
-    }
+        fin.total(tot, ok);
 }
 
 // One double into device memory (the empty shard's local sum, enqueued in order).
@@ -388,15 +445,6 @@ __device__ __forceinline__ double partials_total(const Partial* __restrict__ par
 [[maybe_unused]] static __global__ __launch_bounds__(256) void k_zero_words(uint64_t* __restrict__ out, int64_t n) {
     for (int64_t i = threadIdx.x; i < n; i += 256)
         out[i] = 0;
-}
-
-// Statistics total into caller device memory (the asynchronous split phase:
-// no result record, no host copy).
-[[maybe_unused]] static __global__ __launch_bounds__(kFinalBlock) void k_finalize_sum(
-    const Partial* __restrict__ part, int nparts, double* __restrict__ out) {
-    const double tot = partials_total(part, nparts);
-    if (threadIdx.x == 0)
-        *out = tot;
 }
 
 // Result record from a global sum of squares in device memory (the
@@ -418,16 +466,6 @@ __device__ __forceinline__ double partials_total(const Partial* __restrict__ par
     }
 }
 
-// Resident step, before the update, in one workgroup: the statistics total
-// (as k_finalize forms it), the result record from it and the state record's
-// loss scale and clip, the fp32 constants from the record's hyperparameters
-// and t (make_adam_const, the host's definition), and then the loss-scale
-// schedule on the record: after an overflow the scale halves (not below
-// min_scale) and t stays; otherwise t and the good-step count advance and the
-// scale doubles after `window` good steps.  The update kernel reads only the
-// result record and the constants, so the schedule need not wait for it.  A
-// record outside the accepted ranges (resident_record_ok) is left unchanged
-// except for skipped = -1, and the step writes nothing.
 // The resident step's decision from the statistics total and the record `s`
 // read before the step: the result record, and the record's new scaler fields
 // written to *st (skipped = -1 and nothing else for a record out of range).
@@ -458,16 +496,33 @@ __device__ __forceinline__ Result resident_advance(zero_resident_state_t* __rest
     return r;
 }
 
-[[maybe_unused]] static __global__ __launch_bounds__(kFinalBlock) void k_resident_begin(
-    const Partial* __restrict__ part, int nparts, zero_resident_state_t* __restrict__ st, Result* __restrict__ res,
-    AdamConst* __restrict__ cout, uint32_t seq) {
-    const double tot = partials_total(part, nparts);
-    if (threadIdx.x == 0) {
-        const zero_resident_state_t s = *st;
-        *cout = make_adam_const(s.lr, s.beta1, s.beta2, s.eps, s.weight_decay, s.t);
+// The resident step: the result record from the total and the state record's
+// loss scale and clip, the fp32 constants from the record's hyperparameters and
+// t (make_adam_const, the host's definition), and the loss-scale schedule on
+// the record: after an overflow the scale halves (not below min_scale) and t
+// stays; otherwise t and the good-step count advance and the scale doubles after
+// `window` good steps.  The update kernel reads only the result record and the
+// constants, so the schedule need not wait for it.  A record outside the
+// accepted ranges (resident_record_ok) is left unchanged except for
+// skipped = -1, and the step writes nothing.
+struct FinishResident {
+    zero_resident_state_t* st;
+    Result* res;
+    AdamConst* cout;
+    uint32_t seq;
+    zero_resident_state_t s;  // the record before the step
+    __device__ __forceinline__ void before() {
+        s = *st;
+        const AdamConst c = make_adam_const(s.lr, s.beta1, s.beta2, s.eps, s.weight_decay, s.t);
+        if (threadIdx.x == 0)
+            *cout = c;
+    }
+    __device__ __forceinline__ void total(double tot, bool ok) {
+        if (!ok)
+            s.t = 0;  // given up: as a record out of range
         *res = resident_advance(st, s, tot, seq);
     }
-}
+};
 
 // Result record from a global sum of squares supplied by the caller (the
 // split-phase step: each rank's local sums combined outside the library).

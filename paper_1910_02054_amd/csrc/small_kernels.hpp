@@ -35,34 +35,19 @@ namespace zs {
 // in hand (20.3 against 19.5 us on 3M), gained nothing; loading the gradient
 // tile by tile instead of at once costs 0.7 us on 600K and more.
 //
-// A slot is empty (0) before the launch and is filled once, by a
-// compare-and-swap, with the sum's bits under a set sign bit (a sum of squares
-// is never negative).  Two sets of slots alternate from launch to launch of a
+// A slot (see shard_kernels.hpp) is filled once, by a compare-and-swap.  Two sets of slots alternate from launch to launch of a
 // stream, and each launch empties the other set.  The wait is bounded: a
 // workgroup that gives up on an empty slot fills it with kSlotAbort in the
 // owner's place.  Each slot has one final value that everybody reads, so either
 // every workgroup updates or none does; then nothing is written, the total is
 // not published and the host's wait ends with an error once the stream is
-// idle.  Slots are accessed with agent-scope atomic operations, which the
-// device keeps coherent across its XCDs without writing back or invalidating
-// the L2 caches.
+// idle.
 // ---------------------------------------------------------------------------
 constexpr int kSmallBlock = 512;
 constexpr int kSmallSlots = 256;                       // the largest grid
 constexpr int kSmallTiles = 3;                         // the most tiles per workgroup
 constexpr int kSlotWords = 2 * kSmallSlots;            // two sets
-constexpr uint32_t kSlotSpinLimit = 1u << 22;          // polls of about 0.5-1 us each
-constexpr uint64_t kSlotFilled = (uint64_t)1 << 63;
-constexpr uint64_t kSlotAbort = ~(uint64_t)0;          // not the bits of a sum of fp16 squares
 static_assert(kSmallSlots <= kSmallBlock, "a thread reads at most one slot");
-
-__device__ __forceinline__ uint64_t aload(const uint64_t* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ __forceinline__ void astore(uint64_t* p, uint64_t v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 
 // Fills an empty slot; a filled one keeps its value.
 __device__ __forceinline__ void slot_fill(uint64_t* slot, uint64_t v) {
@@ -70,8 +55,6 @@ __device__ __forceinline__ void slot_fill(uint64_t* slot, uint64_t v) {
     (void)__hip_atomic_compare_exchange_strong(slot, &empty, v, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                __HIP_MEMORY_SCOPE_AGENT);
 }
-
-__device__ __forceinline__ double slot_sum(uint64_t w) { return __builtin_bit_cast(double, w & ~kSlotFilled); }
 
 // The value of a slot, waiting until it is filled (with kSlotAbort by this
 // thread if that takes too long).
@@ -106,7 +89,8 @@ __device__ __forceinline__ double small_block_total(double x, double* lds) {
     uint16_t* __restrict__ p, int64_t n, int64_t head, int64_t nvec, uint64_t* __restrict__ slots,
     uint64_t* __restrict__ other, uint64_t* __restrict__ host, double loss_scale, double clip, uint32_t seq,
     AdamConst c) {
-    __shared__ double lds[2][kSmallBlock / 64];
+    __shared__ double lds[kSmallBlock / 64];
+    __shared__ Sum2 lds2[kSmallSlots / 64];
     __shared__ int s_abort;
     const int64_t b = blockIdx.x;
     const int G = (int)gridDim.x;
@@ -139,9 +123,9 @@ __device__ __forceinline__ double small_block_total(double x, double* lds) {
     }
     if (tid == 0)
         s_abort = 0;
-    double tot = small_block_total(a0 + a1, lds[0]);
+    double tot = small_block_total(a0 + a1, lds);
     if (G > 1 && tid == 0)
-        slot_fill(slots + b, __builtin_bit_cast(uint64_t, tot) | kSlotFilled);
+        slot_fill(slots + b, slot_word(tot));
 
     // 2. the first tile's state, overlapping the wait
     f32x4 tq{}, mq{}, vq{};
@@ -156,14 +140,24 @@ __device__ __forceinline__ double small_block_total(double x, double* lds) {
 
     // 3. the total of all workgroups
     if (G > 1) {
-        double x = 0.0;
-        if (tid < G) {
-            const uint64_t w = slot_wait(slots + tid);
-            if (w == kSlotAbort)
-                s_abort = 1;
-            x = slot_sum(w);
+        if (tid < kSmallSlots) {
+            Sum2 x{0.0, 0.0};
+            if (tid < G) {
+                const uint64_t w = slot_wait(slots + tid);
+                if (w == kSlotAbort)
+                    s_abort = 1;
+                x.hi = slot_sum(w);
+            }
+            x = wave_sum2(x);
+            if ((tid & 63) == 0)
+                lds2[tid >> 6] = x;
         }
-        tot = small_block_total(x, lds[1]);
+        __syncthreads();
+        Sum2 x = lds2[0];
+#pragma unroll
+        for (int w = 1; w < kSmallSlots / 64; ++w)
+            x = sum2_add(x, lds2[w]);
+        tot = sum2_value(x);
         if (s_abort)
             return;
     }

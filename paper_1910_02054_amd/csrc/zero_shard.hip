@@ -55,7 +55,7 @@ int fail(int code, const char* fmt, ...) {
 // workgroups per CU.  The statistics pass uses cache-allocating loads, which
 // leaves part of the gradient in the Infinity Cache for the update.
 // ---------------------------------------------------------------------------
-constexpr int kStatsBlock = 64, kStatsUnroll = 4, kStatsPerCU = 8;
+constexpr int kStatsBlock = 64, kStatsUnroll = 4, kStatsPerCU = 8;  // one wave per workgroup
 constexpr bool kStatsNTL = false, kStatsXCD = false;
 constexpr int kAdamBlock = 64, kAdamUnroll = 1, kAdamPerCU = 12;
 constexpr bool kAdamNTL = true, kAdamNTS = true, kAdamXCD = false, kAdamREV = false;
@@ -192,7 +192,7 @@ int dev_info(int dev, const DevInfo** out) {
             DevInfo d;
             d.ncu = prop.multiProcessorCount;
             d.stats_lds = occupancy_lds(
-                reinterpret_cast<const void*>(zs::k_stats<kStatsBlock, kStatsUnroll, kStatsNTL, kStatsXCD>),
+                reinterpret_cast<const void*>(zs::k_stats<kStatsUnroll, kStatsNTL, kStatsXCD, zs::FinishStep>),
                 kStatsBlock, kStatsPerCU, prop, &d.stats_resident);
             d.adam_lds = occupancy_lds(
                 reinterpret_cast<const void*>(
@@ -227,11 +227,11 @@ std::map<std::pair<int, hipStream_t>, std::shared_ptr<Ctx>> g_ctx;
 constexpr size_t kHostWords = 8;  // the two published words, on a line of their own
 
 void free_ctx_buffers(Ctx* c) {
-    if (c->part) (void)hipFree(c->part);
+    if (c->stats.words) (void)hipFree(c->stats.words);
     if (c->res) (void)hipFree(c->res);
     if (c->slots.words) (void)hipFree(c->slots.words);
     if (c->host) (void)hipHostFree(c->host);
-    c->part = nullptr;
+    c->stats = StatsSlots{};
     c->res = nullptr;
     c->slots = Slots{};
     c->host = c->host_dev = nullptr;
@@ -263,8 +263,8 @@ int new_ctx(int dev, hipStream_t stream, const DevInfo* info, std::shared_ptr<Ct
     c->stream = stream;
     c->info = info;
     RelaxedCapture relaxed(stream);
-    // the slots are zeroed on the stream before the first small-shard launch
-    bool ok = hipMalloc(reinterpret_cast<void**>(&c->part), sizeof(zs::Partial) * zs::kMaxStatsBlocks) == hipSuccess &&
+    // the slots are zeroed on the stream before the first launch that uses them
+    bool ok = hipMalloc(reinterpret_cast<void**>(&c->stats.words), sizeof(uint64_t) * zs::kStatsSlots) == hipSuccess &&
               hipMalloc(reinterpret_cast<void**>(&c->res), sizeof(zs::Result)) == hipSuccess &&
               hipMalloc(reinterpret_cast<void**>(&c->slots.words), sizeof(uint64_t) * zs::kSlotWords) == hipSuccess &&
               hipHostMalloc(reinterpret_cast<void**>(&c->host), kHostWords * sizeof(uint64_t),
@@ -454,8 +454,7 @@ bool is_fin(double x) { return std::isfinite(x); }
 
 bool overlaps(uintptr_t a, size_t an, uintptr_t b, size_t bn) { return a < b + bn && b < a + an; }
 
-// Call sequence numbers skip 0: the finalize kernel writes the host record with
-// sequence number 0 before publishing the real one.
+// Call sequence numbers skip 0, the published words' first value.
 uint32_t next_seq(Ctx* ctx) {
     if (++ctx->seq == 0)
         ++ctx->seq;
@@ -564,14 +563,38 @@ zs::AdamConst adam_const(double lr, double beta1, double beta2, double eps, doub
     return zs::make_adam_const(lr, beta1, beta2, eps, wd, step);
 }
 
-// Statistics + finalize: the result record lands in res and host_dev.
-int launch_stats_into(const DevInfo* info, zs::Partial* part, zs::Result* res, uint64_t* host_dev,
-                      const uint16_t* grad16, int64_t n, const Plan& pl, double loss_scale, double clip, uint32_t seq,
-                      hipStream_t stream) {
-    zs::k_stats<kStatsBlock, kStatsUnroll, kStatsNTL, kStatsXCD>
-        <<<pl.stats_blocks, kStatsBlock, info->stats_lds, stream>>>(grad16, n, pl.ghead, pl.gvec, part);
-    HIP_TRY(hipGetLastError());
-    zs::k_finalize<<<1, zs::kFinalBlock, 0, stream>>>(part, pl.stats_blocks, res, host_dev, loss_scale, clip, seq);
+int ready_slots(uint64_t* words, int64_t n, bool* ready, hipStream_t stream) {
+    if (*ready)
+        return ZERO_OK;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(stream, &cap));
+    if (cap == hipStreamCaptureStatusNone) {
+        zs::k_zero_words<<<1, 256, 0, stream>>>(words, n);
+        HIP_TRY(hipGetLastError());
+    } else {
+        RelaxedCapture relaxed(stream);
+        hipStream_t own = nullptr;
+        HIP_TRY(hipStreamCreateWithFlags(&own, hipStreamNonBlocking));
+        zs::k_zero_words<<<1, 256, 0, own>>>(words, n);
+        hipError_t e = hipGetLastError();
+        if (e == hipSuccess)
+            e = hipStreamSynchronize(own);
+        (void)hipStreamDestroy(own);
+        HIP_TRY(e);
+    }
+    *ready = true;
+    return ZERO_OK;
+}
+
+// The statistics pass over grad16[0, n) (an empty shard's total is 0), finished by `fin`.
+template <typename FIN>
+int launch_stats_into(const DevInfo* info, StatsSlots* slots, const uint16_t* grad16, int64_t n, const Plan& pl,
+                      const FIN& fin, hipStream_t stream) {
+    const int rc = ready_slots(slots->words, zs::kStatsSlots, &slots->ready, stream);
+    if (rc)
+        return rc;
+    zs::k_stats<kStatsUnroll, kStatsNTL, kStatsXCD>
+        <<<pl.stats_blocks, kStatsBlock, info->stats_lds, stream>>>(grad16, n, pl.ghead, pl.gvec, slots->words, fin);
     HIP_TRY(hipGetLastError());
     return ZERO_OK;
 }
@@ -579,8 +602,8 @@ int launch_stats_into(const DevInfo* info, zs::Partial* part, zs::Result* res, u
 int launch_stats_planned(Ctx* ctx, const uint16_t* grad16, int64_t n, double loss_scale, double clip, uint32_t seq,
                          hipStream_t stream) {
     const Plan pl = plan_step(grad16, nullptr, nullptr, nullptr, n, ctx->info->ncu);
-    return launch_stats_into(ctx->info, ctx->part, ctx->res, ctx->host_dev, grad16, n, pl, loss_scale, clip, seq,
-                             stream);
+    return launch_stats_into(ctx->info, &ctx->stats, grad16, n, pl,
+                             zs::FinishStep{ctx->res, ctx->host_dev, loss_scale, clip, seq}, stream);
 }
 
 int prof_every() {
@@ -615,11 +638,9 @@ int launch_update(Ctx* ctx, const uint16_t* grad16, float* master32, float* m32,
 int launch_small_into(Slots* slots, uint64_t* host_dev, const uint16_t* grad16, float* master32, float* m32,
                       float* v32, uint16_t* param16_out, int64_t n, const Plan& pl, double loss_scale, double clip,
                       uint32_t seq, const zs::AdamConst& c, hipStream_t stream) {
-    if (!slots->ready) {
-        zs::k_zero_words<<<1, 256, 0, stream>>>(slots->words, zs::kSlotWords);
-        HIP_TRY(hipGetLastError());
-        slots->ready = true;
-    }
+    const int rc = ready_slots(slots->words, zs::kSlotWords, &slots->ready, stream);
+    if (rc)
+        return rc;
     uint64_t* const fill = slots->words + slots->set * zs::kSmallSlots;
     uint64_t* const empty = slots->words + (1 - slots->set) * zs::kSmallSlots;
     zs::k_small_step<<<(unsigned)pl.small_grid, zs::kSmallBlock, 0, stream>>>(
@@ -665,6 +686,8 @@ int wait_result(Ctx* ctx, uint32_t seq, hipStream_t stream, double loss_scale, d
             if (e == hipSuccess) {  // everything queued has finished
                 if (ready())
                     break;
+                // a wait on the device was given up: its slots are emptied before the next launch
+                ctx->slots.ready = ctx->stats.ready = false;
                 return fail(ZERO_EHIP, "statistics of call %u not published although the stream is idle", seq);
             }
             if (e != hipErrorNotReady)
@@ -693,7 +716,7 @@ void set_stats(const zs::Result& r, int64_t n, int32_t path) {
 // workspace, so steps with different records never share one.
 // ---------------------------------------------------------------------------
 struct ResWs {
-    zs::Partial* part = nullptr;
+    StatsSlots stats;
     zs::Result* res = nullptr;
     zs::AdamConst* dconst = nullptr;
     uint32_t seq = 0;          // call counter echoed in the result record
@@ -705,7 +728,7 @@ std::mutex g_res_mu;
 std::map<std::pair<int, const void*>, ResWs> g_res;  // node addresses stay valid until erased
 
 void free_res_ws(ResWs* w) {
-    if (w->part) (void)hipFree(w->part);
+    if (w->stats.words) (void)hipFree(w->stats.words);
     if (w->res) (void)hipFree(w->res);
     if (w->dconst) (void)hipFree(w->dconst);
     *w = ResWs{};
@@ -724,7 +747,7 @@ int resident_ws(int dev, const void* state, hipStream_t stream, ResWs** out) {
     }
     RelaxedCapture relaxed(stream);
     ResWs w;
-    const bool ok = hipMalloc(reinterpret_cast<void**>(&w.part), sizeof(zs::Partial) * zs::kMaxStatsBlocks) ==
+    const bool ok = hipMalloc(reinterpret_cast<void**>(&w.stats.words), sizeof(uint64_t) * zs::kStatsSlots) ==
                         hipSuccess &&
                     hipMalloc(reinterpret_cast<void**>(&w.res), sizeof(zs::Result)) == hipSuccess &&
                     hipMalloc(reinterpret_cast<void**>(&w.dconst), sizeof(zs::AdamConst)) == hipSuccess;
@@ -740,13 +763,13 @@ int resident_ws(int dev, const void* state, hipStream_t stream, ResWs** out) {
 // ---------------------------------------------------------------------------
 // The allocation-free step's workspace: one fixed device array per GPU (each
 // device that loads the library holds its own copy until the process ends),
-// laid out as the statistics partials, the one-launch step's exchange slots,
+// laid out as the statistics slots, the one-launch step's exchange slots,
 // the result record and two words that stand in for the host-mapped ones (the
 // host copies them out instead).  In host code `scratch` names a
 // host-side stand-in; the device address comes from hipGetSymbolAddress.
 // ---------------------------------------------------------------------------
-constexpr size_t kScratchPart = 0;
-constexpr size_t kScratchSlots = kScratchPart + sizeof(zs::Partial) * zs::kMaxStatsBlocks;
+constexpr size_t kScratchStats = 0;
+constexpr size_t kScratchSlots = kScratchStats + sizeof(uint64_t) * zs::kStatsSlots;
 constexpr size_t kScratchRes = kScratchSlots + sizeof(uint64_t) * zs::kSlotWords;
 constexpr size_t kScratchHost = kScratchRes + 256;
 constexpr size_t kScratchBytes = kScratchHost + 256;
@@ -757,7 +780,7 @@ static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 struct ScratchDev {
     std::mutex mu;           // serialises this device's allocation-free calls on the host side
     unsigned char* ptr = nullptr;  // the device's copy of `scratch`
-    bool slots_ready = true;  // the slots are empty (as loaded) or were emptied
+    bool stats_ready = true, slots_ready = true;  // the slots are empty (as loaded) or were emptied
     int slots_set = 0;
     uint32_t seq = 0;
 };
@@ -943,8 +966,8 @@ int zero_shard_step(const uint16_t* grad16, float* master32, float* m32, float* 
         rc = launch_small_into(&ctx->slots, ctx->host_dev, grad16, master32, m32, v32, param16_out, n, pl, loss_scale,
                                clip, seq, c, stream);
     } else {
-        rc = launch_stats_into(ctx->info, ctx->part, ctx->res, ctx->host_dev, grad16, n, pl, loss_scale, clip, seq,
-                               stream);
+        rc = launch_stats_into(ctx->info, &ctx->stats, grad16, n, pl,
+                               zs::FinishStep{ctx->res, ctx->host_dev, loss_scale, clip, seq}, stream);
         if (!rc && prof)
             prof_record(pr.mid, stream, &pr);
         if (!rc)
@@ -963,11 +986,8 @@ int zero_shard_step(const uint16_t* grad16, float* master32, float* m32, float* 
     }
     // The update is already queued: wait only for the statistics.
     zs::Result r;
-    if ((rc = wait_result(ctx.get(), seq, stream, loss_scale, clip, &r))) {
-        if (pl.small_grid)
-            ctx->slots.ready = false;  // an aborted launch's slots are emptied before the next
+    if ((rc = wait_result(ctx.get(), seq, stream, loss_scale, clip, &r)))
         return rc;
-    }
     set_stats(r, n, pl.small_grid ? 1 : 0);
     return r.skip ? ZERO_SKIPPED : ZERO_OK;
 }
@@ -1077,12 +1097,7 @@ int zero_shard_stats_async(const uint16_t* grad16, int64_t n, double* local_sums
         return ZERO_OK;
     }
     const Plan pl = plan_step(grad16, nullptr, nullptr, nullptr, n, ctx->info->ncu);
-    zs::k_stats<kStatsBlock, kStatsUnroll, kStatsNTL, kStatsXCD>
-        <<<pl.stats_blocks, kStatsBlock, ctx->info->stats_lds, stream>>>(grad16, n, pl.ghead, pl.gvec, ctx->part);
-    HIP_TRY(hipGetLastError());
-    zs::k_finalize_sum<<<1, zs::kFinalBlock, 0, stream>>>(ctx->part, pl.stats_blocks, local_sumsq);
-    HIP_TRY(hipGetLastError());
-    return ZERO_OK;
+    return launch_stats_into(ctx->info, &ctx->stats, grad16, n, pl, zs::FinishSum{local_sumsq}, stream);
 }
 
 int zero_shard_apply_async(const uint16_t* grad16, float* master32, float* m32, float* v32, uint16_t* param16_out,
@@ -1223,19 +1238,10 @@ int zero_shard_step_resident(const uint16_t* grad16, float* master32, float* m32
         return prof;
     if (prof)
         prof_record(pr.start, stream, &pr);
-    // statistics, then one workgroup that totals them, fills the result record and the
-    // constants and advances the state record's loss-scale schedule (an empty shard has no
-    // partials: its total is 0), then the update
-    if (n > 0) {
-        zs::k_stats<kStatsBlock, kStatsUnroll, kStatsNTL, kStatsXCD>
-            <<<pl.stats_blocks, kStatsBlock, info->stats_lds, stream>>>(grad16, n, pl.ghead, pl.gvec, ws->part);
-        rc = hipGetLastError() == hipSuccess ? ZERO_OK : fail(ZERO_EHIP, "%s: statistics launch failed", fn);
-    }
-    if (!rc) {
-        zs::k_resident_begin<<<1, zs::kFinalBlock, 0, stream>>>(ws->part, n > 0 ? pl.stats_blocks : 0, state,
-                                                                ws->res, ws->dconst, seq);
-        rc = hipGetLastError() == hipSuccess ? ZERO_OK : fail(ZERO_EHIP, "%s: record kernel launch failed", fn);
-    }
+    // statistics, whose last workgroup fills the result record and the constants and advances the
+    // state record's loss-scale schedule (an empty shard's total is 0), then the update
+    rc = launch_stats_into(info, &ws->stats, grad16, n, pl, zs::FinishResident{state, ws->res, ws->dconst, seq, {}},
+                           stream);
     if (!rc && prof)
         prof_record(pr.mid, stream, &pr);
     if (!rc && n > 0)
@@ -1369,7 +1375,7 @@ int zero_shard_step_noalloc(const uint16_t* grad16, float* master32, float* m32,
     unsigned char* base = nullptr;
     if ((rc = scratch_ptr(dev, &base)))
         return rc;
-    zs::Partial* part = reinterpret_cast<zs::Partial*>(base + kScratchPart);
+    StatsSlots stats{reinterpret_cast<uint64_t*>(base + kScratchStats), sd.stats_ready};
     Slots slots{reinterpret_cast<uint64_t*>(base + kScratchSlots), sd.slots_ready, sd.slots_set};
     zs::Result* res = reinterpret_cast<zs::Result*>(base + kScratchRes);
     uint64_t* words = reinterpret_cast<uint64_t*>(base + kScratchHost);
@@ -1387,7 +1393,8 @@ int zero_shard_step_noalloc(const uint16_t* grad16, float* master32, float* m32,
         sd.slots_ready = slots.ready;
         sd.slots_set = slots.set;
     } else {
-        rc = launch_stats_into(info, part, res, words, grad16, n, pl, loss_scale, clip, seq, stream);
+        rc = launch_stats_into(info, &stats, grad16, n, pl, zs::FinishStep{res, words, loss_scale, clip, seq}, stream);
+        sd.stats_ready = stats.ready;
         if (!rc)
             rc = launch_update_from(info, res, grad16, master32, m32, v32, param16_out, n, pl, c, stream);
     }
@@ -1400,8 +1407,8 @@ int zero_shard_step_noalloc(const uint16_t* grad16, float* master32, float* m32,
     HIP_TRY(hipMemcpyAsync(w, words, sizeof w, hipMemcpyDeviceToHost, stream));
     HIP_TRY(hipStreamSynchronize(stream));
     if (!published(w[0], w[1], seq, &sum)) {
-        if (pl.small_grid)
-            sd.slots_ready = false;  // an aborted launch's slots are emptied before the next
+        // a wait on the device was given up: its slots are emptied before the next launch
+        sd.stats_ready = sd.slots_ready = false;
         return fail(ZERO_EHIP, "%s: statistics of call %u not published by the step's kernels", fn, seq);
     }
     const zs::Result r = zs::make_result(sum, loss_scale, clip, seq);
