@@ -410,7 +410,7 @@ int zero_model_state_bytes(double psi, double nd, int32_t stage, double k, doubl
  * 256 elements plus 32 bytes per layer, and the work lists, built per array
  * alignment on first use); zero_lamb_plan_destroy waits for the plan's own
  * queued work and frees it.  Calls on one plan are serialised by the library:
- * each call records a plan-owned event after its kernels, and a call on a
+ * each call's last kernel completes a plan-owned event, and a call on a
  * different stream from the plan's previous one makes its stream wait for
  * that event on the device (no host wait, no other stream affected; the
  * event stays valid if the previous stream has been destroyed).
@@ -460,7 +460,7 @@ typedef struct {
     int64_t steps;      /* steps timed                                  */
     double stats_ms;    /* statistics + finalize kernels                */
     double moments_ms;  /* k_lamb_moments                               */
-    double layer_ms;    /* k_lamb_layer                                 */
+    double layer_ms;    /* k_lamb_sums                                  */
     double apply_ms;    /* k_lamb_apply                                 */
 } zero_lamb_profile_t;
 

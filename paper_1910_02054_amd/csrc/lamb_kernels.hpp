@@ -8,8 +8,7 @@
 // streaming passes after the gradient statistics:
 //   k_lamb_moments  reads g16, theta, m, v; writes m, v; one fp64 partial
 //                   (sum theta^2, sum u^2) per work item (22 bytes/element).
-//   k_lamb_chunks,  fixed-order two-level sum of each layer's partials.
-//   k_lamb_layer
+//   k_lamb_sums     fixed-order two-level sum of each layer's partials.
 //   k_lamb_apply    reads theta, m, v; recomputes u from the stored moments
 //                   (the same fp32 operations, so the same bits); writes
 //                   theta - step*u and its fp16 copy (18 bytes/element).
@@ -135,16 +134,17 @@ __device__ __forceinline__ int64_t tile_range(int64_t b, int64_t head, int64_t n
 // to cache lines, the other arrays' may be unaligned (as k_adam_vec's);
 // the partial vectors at the shard's ends go element by element.
 // ---------------------------------------------------------------------------
-template <int BLOCK, int U, bool NTL, bool NTS, bool XCD>
+template <int BLOCK, int U, bool NTL, bool NTS, bool XCD, typename SRC>
 __global__ __launch_bounds__(BLOCK) void k_lamb_moments(const uint16_t* __restrict__ g, const float* __restrict__ th,
                                                         float* __restrict__ m, float* __restrict__ v,
                                                         const LambItem* __restrict__ items,
                                                         const int64_t* __restrict__ tile_first, int64_t ntiles,
-                                                        int64_t n, int64_t head, const Result* __restrict__ res,
-                                                        AdamConst c, LayerSums* __restrict__ part) {
-    if (res->skip)
+                                                        int64_t n, int64_t head, SRC src,
+                                                        LayerSums* __restrict__ part) {
+    float mult;
+    AdamConst c;
+    if (!src.get(mult, c))
         return;
-    const float mult = res->mult;
     for (int64_t b = logical_block<XCD>(); b < ntiles; b += gridDim.x) {
         int64_t ts, te;
         const int64_t base = tile_range<BLOCK, U>(b, head, n, &ts, &te);
@@ -216,69 +216,79 @@ __global__ __launch_bounds__(BLOCK) void k_lamb_moments(const uint16_t* __restri
 }
 
 // ---------------------------------------------------------------------------
-// Layer sums, two levels in a fixed order.  Level 1: workgroup c adds the
-// partials of item chunk c, items [chunk[c], chunk[c+1]) (a chunk never
-// spans two layers).  Level 2: workgroup s adds the chunk sums of layer s,
-// chunks [chunk_first[s], chunk_first[s+1]).
+// Layer sums, two levels in a fixed order.  Workgroup c adds the partials of
+// item chunk c, items [chunk[c], chunk[c+1]) (a chunk never spans two layers),
+// and passes the sums on in its two slots (slot_word: neither sum is negative);
+// the workgroup of a layer's last chunk drains the others' and writes the
+// layer's sums.  It waits only for workgroups before it, which wait for nobody
+// it must make room for, so the wait ends however few are resident.  The second
+// level in a kernel of its own cost 4.7 us a step.
 // ---------------------------------------------------------------------------
 constexpr int kChunkBlock = 256;
-constexpr int kChunkItems = 1024;   // items per level-1 chunk (4 per thread)
-constexpr int kLayerBlock = 64;
+constexpr int kChunkItems = 1024;   // items per chunk (4 per thread)
 
-__global__ __launch_bounds__(kChunkBlock) void k_lamb_chunks(const LayerSums* __restrict__ part,
-                                                             const int64_t* __restrict__ chunk, int64_t n_chunks,
-                                                             LayerSums* __restrict__ cpart,
-                                                             const Result* __restrict__ res) {
-    if (res->skip)
+__global__ __launch_bounds__(kChunkBlock) void k_lamb_sums(const LayerSums* __restrict__ part,
+                                                           const int64_t* __restrict__ chunk,
+                                                           const int32_t* __restrict__ chunk_layer,
+                                                           const int64_t* __restrict__ chunk_first,
+                                                           uint64_t* __restrict__ slots, LayerSums* __restrict__ sums,
+                                                           const Result* __restrict__ res) {
+    if (res && res->skip)
         return;
-    for (int64_t cb = blockIdx.x; cb < n_chunks; cb += gridDim.x) {
-        const int64_t a = chunk[cb], e = chunk[cb + 1];
-        double w = 0.0, u = 0.0;
-        for (int64_t i = a + threadIdx.x; i < e; i += kChunkBlock) {
-            const LayerSums p = part[i];
-            w += p.wsq;
-            u += p.usq;
-        }
-        block_sum2<kChunkBlock>(w, u);
-        if (threadIdx.x == 0)
-            cpart[cb] = LayerSums{w, u};
+    const int64_t cb = blockIdx.x;
+    const int64_t a = chunk[cb], e = chunk[cb + 1];
+    double w = 0.0, u = 0.0;
+    for (int64_t i = a + threadIdx.x; i < e; i += kChunkBlock) {
+        const LayerSums p = part[i];
+        w += p.wsq;
+        u += p.usq;
     }
-}
-
-__global__ __launch_bounds__(kLayerBlock) void k_lamb_layer(const LayerSums* __restrict__ cpart,
-                                                            const int64_t* __restrict__ chunk_first,
-                                                            int64_t n_layers, LayerSums* __restrict__ sums,
-                                                            const Result* __restrict__ res) {
-    if (res->skip)
+    block_sum2<kChunkBlock>(w, u);
+    const int32_t s = chunk_layer[cb];
+    const int64_t first = chunk_first[s];
+    if (cb != chunk_first[s + 1] - 1) {
+        if (threadIdx.x == 0) {
+            astore(slots + 2 * cb, slot_word(w));
+            astore(slots + 2 * cb + 1, slot_word(u));
+        }
         return;
-    for (int64_t s = blockIdx.x; s < n_layers; s += gridDim.x) {
-        const int64_t a = chunk_first[s], e = chunk_first[s + 1];
-        double w = 0.0, u = 0.0;
-        for (int64_t i = a + threadIdx.x; i < e; i += kLayerBlock) {
-            const LayerSums p = cpart[i];
-            w += p.wsq;
-            u += p.usq;
-        }
-        block_sum2<kLayerBlock>(w, u);
-        if (threadIdx.x == 0)
-            sums[s] = LayerSums{w, u};
     }
+    if (threadIdx.x >= 64)
+        return;
+    if (threadIdx.x != 0)
+        w = u = 0.0;
+    for (int64_t i = first + threadIdx.x; i < cb; i += 64) {
+        uint64_t x = 0, y = 0;
+        for (uint32_t polls = 0; (x == 0 || y == 0) && polls < kSlotSpinLimit; ++polls) {
+            x = aload(slots + 2 * i);
+            y = aload(slots + 2 * i + 1);
+        }
+        astore(slots + 2 * i, 0);
+        astore(slots + 2 * i + 1, 0);
+        w += x ? slot_sum(x) : __builtin_nan("");
+        u += y ? slot_sum(y) : __builtin_nan("");
+    }
+    w = wave_sum(w);
+    u = wave_sum(u);
+    if (threadIdx.x == 0)
+        sums[s] = LayerSums{w, u};
 }
 
 // ---------------------------------------------------------------------------
 // Apply pass: same tile walk as the moments pass; each element moves by its
 // layer piece's step size (theta <- theta - step*u) and gets its fp16 copy.
 // ---------------------------------------------------------------------------
-template <int BLOCK, int U, bool NTL, bool NTS, bool XCD>
+template <int BLOCK, int U, bool NTL, bool NTS, bool XCD, typename SRC>
 __global__ __launch_bounds__(BLOCK) void k_lamb_apply(float* __restrict__ th, const float* __restrict__ m,
                                                       const float* __restrict__ v, uint16_t* __restrict__ p,
                                                       const LambItem* __restrict__ items,
                                                       const int64_t* __restrict__ tile_first, int64_t ntiles,
                                                       int64_t n, int64_t head, const LayerSums* __restrict__ sums,
-                                                      const Result* __restrict__ res, AdamConst c, double lr,
-                                                      double phi_lo, double phi_hi) {
+                                                      SRC src, double lr, double phi_lo, double phi_hi) {
 #pragma clang fp contract(off)
-    if (res->skip)
+    float mult;
+    AdamConst c;
+    if (!src.get(mult, c))
         return;
     for (int64_t b = logical_block<XCD>(); b < ntiles; b += gridDim.x) {
         int64_t ts, te;

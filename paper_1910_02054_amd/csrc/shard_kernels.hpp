@@ -19,10 +19,10 @@
 //               cast; 14 bytes read and 14 bytes written per element.
 // Small shards take one launch instead (k_small_step in small_kernels.hpp).
 // The other ways of running the same step change what follows the statistics
-// total (FinishStep, FinishSum, FinishResident) or where the scalars come from:
-// the split phase takes the global sum from the host (k_set_result) or from
-// device memory (k_set_result_dev), the resident step its hyperparameters and
-// loss scale from a state record in device memory.
+// total (FinishStep, FinishSum, FinishResident) or where the update's scalars come from:
+// the split phase takes the global sum from the host or from device memory, the
+// resident step its hyperparameters and loss scale from a state record in device
+// memory (FromResult, FromHost, FromSum, FromResident).
 //
 // Numerics: every fp32 operation of the update is correctly rounded (IEEE
 // division and square root, no contraction), in the order Adam's bias-corrected
@@ -447,6 +447,9 @@ __global__ __launch_bounds__(64) void k_stats(const uint16_t* __restrict__ g, in
         out[i] = 0;
 }
 
+// A caller's global sum of squares; +inf for what cannot be one.
+__device__ __forceinline__ double sum_of_squares(double g) { return g >= 0.0 ? g : __builtin_inf(); }
+
 // Result record from a global sum of squares in device memory (the
 // asynchronous split phase); the skip flag also goes to `skipped` when given
 // (device or host-mapped memory).
@@ -456,10 +459,7 @@ __global__ __launch_bounds__(64) void k_stats(const uint16_t* __restrict__ g, in
                                                                                 int32_t* __restrict__ skipped,
                                                                                 uint32_t seq) {
     if (threadIdx.x == 0) {
-        double g = *global;
-        if (!(g >= 0.0))
-            g = __builtin_inf();  // negative or NaN: not a sum of squares, skip like an overflow
-        const Result r = make_result(g, loss_scale, clip, seq);
+        const Result r = make_result(sum_of_squares(*global), loss_scale, clip, seq);
         *res = r;
         if (skipped)
             *skipped = r.skip;
@@ -524,14 +524,63 @@ struct FinishResident {
     }
 };
 
-// Result record from a global sum of squares supplied by the caller (the
-// split-phase step: each rank's local sums combined outside the library).
-[[maybe_unused]] static __global__ __launch_bounds__(64) void k_set_result(Result* __restrict__ res,
-                                                                            double global_sumsq, double loss_scale,
-                                                                            double clip, uint32_t seq) {
-    if (threadIdx.x == 0)
-        *res = make_result(global_sumsq, loss_scale, clip, seq);
-}
+// Where an update takes its multiplier and constants from; false: the step is
+// skipped and nothing may be written.
+// A result record written by an earlier kernel of the stream.
+struct FromResult {
+    const Result* res;
+    AdamConst consts;
+    __device__ __forceinline__ bool get(float& mult, AdamConst& c) const {
+        if (res->skip)
+            return false;
+        mult = res->mult;
+        c = consts;
+        return true;
+    }
+};
+
+// The resident step: the constants, too, come from an earlier kernel.
+struct FromResident {
+    const Result* res;
+    const AdamConst* consts;
+    __device__ __forceinline__ bool get(float& mult, AdamConst& c) const {
+        if (res->skip)
+            return false;
+        mult = res->mult;
+        c = *consts;
+        return true;
+    }
+};
+
+// The split phase with a global sum that the host holds (it does not launch a
+// skipped update).
+struct FromHost {
+    float multiplier;
+    AdamConst consts;
+    __device__ __forceinline__ bool get(float& mult, AdamConst& c) const {
+        mult = multiplier;
+        c = consts;
+        return true;
+    }
+};
+
+// The asynchronous split phase: a global sum in device memory, which every wave
+// turns into the multiplier (a negative sum or NaN is not a sum of squares and
+// skips like an overflow); the first workgroup stores the skip flag.
+struct FromSum {
+    const double* sum;
+    double loss_scale, clip;
+    int32_t* skipped;
+    AdamConst consts;
+    __device__ __forceinline__ bool get(float& mult, AdamConst& c) const {
+        const Result r = make_result(sum_of_squares(*sum), loss_scale, clip, 0);
+        if (skipped && blockIdx.x == 0 && threadIdx.x == 0)
+            *skipped = r.skip;
+        mult = r.mult;
+        c = consts;
+        return !r.skip;
+    }
+};
 
 // ---------------------------------------------------------------------------
 // The per-element update: one definition for the vectors and for the single
@@ -613,21 +662,16 @@ __device__ __forceinline__ void adam_vec4(u32x2 gq, f32x4 tq, f32x4 mq, f32x4 vq
 // test for the loads and for the rest).  Elements [head + 4*nvec, n) are the
 // tail (0..3).  The last workgroup takes head and tail; the host gives them a
 // workgroup without a tile, so that no workgroup has both latencies in a row.
-// Any grid size is valid (tiles are strided by it).  The fp32
-// constants come by value, or with CDEV from device memory (the resident step
-// computes them on the device).
-template <int BLOCK, int U, bool NTL, bool NTS, bool XCD, bool REV, bool CDEV>
+// Any grid size is valid (tiles are strided by it).
+template <int BLOCK, int U, bool NTL, bool NTS, bool XCD, bool REV, typename SRC>
 __global__ __launch_bounds__(BLOCK) void k_adam_vec(const uint16_t* __restrict__ g, float* __restrict__ th,
                                                     float* __restrict__ m, float* __restrict__ v,
                                                     uint16_t* __restrict__ p, int64_t n, int64_t head, int64_t nvec,
-                                                    const Result* __restrict__ res, AdamConst c_arg,
-                                                    const AdamConst* __restrict__ cdev) {
-    if (res->skip)
+                                                    SRC src) {
+    float mult;
+    AdamConst c;
+    if (!src.get(mult, c))
         return;
-    const float mult = res->mult;
-    AdamConst c = c_arg;
-    if constexpr (CDEV)
-        c = *cdev;
     if (blockIdx.x == gridDim.x - 1)
         adam_ends(g, th, m, v, p, n, head, nvec, mult, c);
     const int64_t tile = (int64_t)BLOCK * U;

@@ -6,6 +6,7 @@
 // adaptive optimizers whose state ZeRO's partitioning (Sec. 5.1-5.2) makes
 // affordable; the fp32 state per parameter is Adam's (Sec. 3.1, K = 12).
 #include <hip/hip_runtime.h>
+#include <hip/hip_ext.h>
 
 #include <cmath>
 #include <cstring>
@@ -32,6 +33,11 @@ constexpr int kLambBlock = 128, kLambUnroll = 1, kLambPerCU = 16;
 constexpr bool kLambNTL = true, kLambNTS = true, kLambXCD = true;
 constexpr int64_t kLambTile = 4 * (int64_t)kLambBlock * kLambUnroll;  // elements per tile
 constexpr int64_t kLambMaxBlocks = 1 << 26;
+// The event after a call orders streams of one device, for which a device-scope
+// release is enough; up to this many elements leaving out the system-scope one
+// pays (5.9M: 54.4 against 56.1 us a step), on larger shards it costs a little
+// (20M: 150.2 against 147.9; 94M: 629 against 626).
+constexpr int64_t kLambNoFenceNumel = 1 << 23;
 constexpr int kHeads = zs::kMaxHead + 1;  // one work list per head (elements before the master array's first cache line)
 }  // namespace
 
@@ -39,12 +45,13 @@ using namespace zsh;
 
 // The work lists of one array alignment, on the device: the items (tile pieces
 // inside one layer, with the end sentinel), the first item of every tile, the
-// level-1 chunks of the layer sums (item ranges inside one layer) and the first
-// chunk of every layer (each list with its end sentinel).
+// chunks of the layer sums (item ranges inside one layer), each chunk's layer
+// and the first chunk of every layer (the ranges with their end sentinels).
 struct LambWork {
     zs::LambItem* items = nullptr;
     int64_t* tile_first = nullptr;
     int64_t* chunk = nullptr;
+    int32_t* chunk_layer = nullptr;
     int64_t* chunk_first = nullptr;
     int64_t n_items = 0, ntiles = 0, n_chunks = 0;
     bool built = false;
@@ -62,7 +69,8 @@ struct zero_lamb_plan {
     std::vector<int64_t> seg_off;
     LambWork work[kHeads];
     zs::LayerSums* part = nullptr;   // one partial per item (sized for the longest list)
-    zs::LayerSums* cpart = nullptr;  // one partial per level-1 chunk
+    uint64_t* slots = nullptr;       // two exchange slots per chunk
+    bool slots_ready = false;        // the slots have been zeroed
     zs::LayerSums* sums = nullptr;   // per-layer sums of zero_lamb_step
     int64_t max_items = 0, max_chunks = 0;
     hipEvent_t done = nullptr;       // recorded after each call's kernels (ordering across streams)
@@ -80,14 +88,14 @@ std::vector<hipEvent_t> g_lprof_pool;
 zero_lamb_profile_t g_lprof_acc = {0, 0.0, 0.0, 0.0, 0.0};
 
 const void* moments_kernel() {
-    return reinterpret_cast<const void*>(zs::k_lamb_moments<kLambBlock, kLambUnroll, kLambNTL, kLambNTS, kLambXCD>);
+    return reinterpret_cast<const void*>(zs::k_lamb_moments<kLambBlock, kLambUnroll, kLambNTL, kLambNTS, kLambXCD, zs::FromResult>);
 }
 template <int PASS>
 const void* probe_kernel() {
     return reinterpret_cast<const void*>(zs::k_probe_lamb<kLambBlock, kLambUnroll, kLambNTL, kLambNTS, kLambXCD, PASS>);
 }
 const void* apply_kernel() {
-    return reinterpret_cast<const void*>(zs::k_lamb_apply<kLambBlock, kLambUnroll, kLambNTL, kLambNTS, kLambXCD>);
+    return reinterpret_cast<const void*>(zs::k_lamb_apply<kLambBlock, kLambUnroll, kLambNTL, kLambNTS, kLambXCD, zs::FromResult>);
 }
 
 // Upper bound on the items of any alignment: one per tile the shard touches
@@ -95,7 +103,7 @@ const void* apply_kernel() {
 // plus one per interior layer boundary.
 int64_t max_items_for(int64_t n, int32_t n_seg) { return n / kLambTile + 2 + (int64_t)n_seg; }
 
-// Level-1 chunks: each layer's items cut into runs of at most kChunkItems.
+// Chunks: each layer's items cut into runs of at most kChunkItems.
 int64_t max_chunks_for(int64_t max_items, int32_t n_seg) { return max_items / zs::kChunkItems + 1 + (int64_t)n_seg; }
 
 // Tiles (as the kernels' tile_range defines them): [0, head) when head > 0,
@@ -116,11 +124,12 @@ struct HostWork {
     std::vector<zs::LambItem> items;  // with the end sentinel
     std::vector<int64_t> tile_first;  // ntiles + 1
     std::vector<int64_t> chunk;       // n_chunks + 1 item indices
+    std::vector<int32_t> chunk_layer; // n_chunks layers
     std::vector<int64_t> chunk_first; // n_seg + 1 chunk indices
 };
 
 // Cut [0, n) at the tile boundaries and at the layer boundaries; index the
-// pieces by tile, and each layer's pieces by level-1 chunk.
+// pieces by tile, and each layer's pieces by chunk.
 void build_work(const std::vector<int64_t>& off, int32_t n_seg, int64_t head, HostWork* w) {
     const int64_t n = n_seg ? off[n_seg] : 0;
     w->items.clear();
@@ -147,11 +156,14 @@ void build_work(const std::vector<int64_t>& off, int32_t n_seg, int64_t head, Ho
             w->tile_first[next++] = k;
     }
     w->chunk.clear();
+    w->chunk_layer.clear();
     w->chunk_first.assign((size_t)n_seg + 1, 0);
     for (int32_t s = 0; s < n_seg; ++s) {
         w->chunk_first[s] = (int64_t)w->chunk.size();
-        for (int64_t k = first[s]; k < first[s + 1]; k += zs::kChunkItems)
+        for (int64_t k = first[s]; k < first[s + 1]; k += zs::kChunkItems) {
             w->chunk.push_back(k);
+            w->chunk_layer.push_back(s);
+        }
     }
     w->chunk_first[n_seg] = (int64_t)w->chunk.size();
     w->chunk.push_back(n_items);
@@ -181,7 +193,8 @@ int get_work(zero_lamb_plan* plan, int head, LambWork** out) {
                         (long long)n_items, (long long)n_chunks);
         int rc;
         if ((rc = upload(h.items, &w.items)) || (rc = upload(h.tile_first, &w.tile_first)) ||
-            (rc = upload(h.chunk, &w.chunk)) || (rc = upload(h.chunk_first, &w.chunk_first)))
+            (rc = upload(h.chunk, &w.chunk)) || (rc = upload(h.chunk_layer, &w.chunk_layer)) ||
+            (rc = upload(h.chunk_first, &w.chunk_first)))
             return rc;
         w.n_items = n_items;
         w.ntiles = (int64_t)h.tile_first.size() - 1;
@@ -261,15 +274,26 @@ int switch_stream(zero_lamb_plan* plan, hipStream_t stream) {
     return ZERO_OK;
 }
 
-// Marks the end of this call's kernels on `stream` (see switch_stream).
-int mark_done(zero_lamb_plan* plan, hipStream_t stream) {
-    HIP_TRY(hipEventRecord(plan->done, stream));
+// The launch of a call's last kernel, whose completion is the event `done` (see
+// switch_stream).  The kernel's own completion signal serves as the event: a
+// record after it puts a marker into the stream (1M elements: 23.4 us a step
+// against 25.9; the split phase, two calls a step, on 5.9M: 64.3 against 69.9).
+// A stream that is being captured takes the record (a captured launch carries
+// no event).
+template <typename F, typename... A>
+int launch_last(zero_lamb_plan* plan, F* kernel, unsigned grid, int block, size_t lds, hipStream_t stream, A... args) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(stream, &cap));
+    if (cap == hipStreamCaptureStatusNone) {
+        hipExtLaunchKernelGGL(kernel, dim3(grid), dim3((unsigned)block), (uint32_t)lds, stream, nullptr, plan->done, 0,
+                              args...);
+        HIP_TRY(hipGetLastError());
+    } else {
+        kernel<<<grid, block, lds, stream>>>(args...);
+        HIP_TRY(hipGetLastError());
+        HIP_TRY(hipEventRecord(plan->done, stream));
+    }
     return ZERO_OK;
-}
-
-unsigned grid_for(int64_t n_items) {
-    int64_t b = n_items < 1 ? 1 : n_items;
-    return (unsigned)(b > kLambMaxBlocks ? kLambMaxBlocks : b);
 }
 
 // Grid of the tile passes: a multiple of 8 (the XCD count) so that the XCD
@@ -280,36 +304,41 @@ unsigned tile_grid(int64_t ntiles) {
     return (unsigned)((b + 7) / 8 * 8);
 }
 
+template <typename SRC>
 int launch_moments(zero_lamb_plan* plan, const LambWork& w, int head, const uint16_t* g, const float* th, float* m,
-                   float* v, const zs::Result* res, const zs::AdamConst& c, hipStream_t stream) {
-    const unsigned grid = tile_grid(w.ntiles);
-    zs::k_lamb_moments<kLambBlock, kLambUnroll, kLambNTL, kLambNTS, kLambXCD>
-        <<<grid, kLambBlock, plan->lds[0], stream>>>(g, th, m, v, w.items, w.tile_first, w.ntiles, plan->n, head, res,
-                                                     c, plan->part);
+                   float* v, const SRC& src, hipStream_t stream) {
+    zs::k_lamb_moments<kLambBlock, kLambUnroll, kLambNTL, kLambNTS, kLambXCD, SRC>
+        <<<tile_grid(w.ntiles), kLambBlock, plan->lds[0], stream>>>(g, th, m, v, w.items, w.tile_first, w.ntiles,
+                                                                    plan->n, head, src, plan->part);
     HIP_TRY(hipGetLastError());
     return ZERO_OK;
 }
 
-int launch_layer(zero_lamb_plan* plan, const LambWork& w, zs::LayerSums* sums, const zs::Result* res,
-                 hipStream_t stream) {
-    zs::k_lamb_chunks<<<grid_for(w.n_chunks), zs::kChunkBlock, 0, stream>>>(plan->part, w.chunk, w.n_chunks,
-                                                                            plan->cpart, res);
-    HIP_TRY(hipGetLastError());
-    zs::k_lamb_layer<<<grid_for(plan->n_seg), zs::kLayerBlock, 0, stream>>>(plan->cpart, w.chunk_first,
-                                                                            plan->n_seg, sums, res);
+// The layer sums into `sums`; `res`: the record whose skip flag applies, or NULL.
+int launch_sums(zero_lamb_plan* plan, const LambWork& w, zs::LayerSums* sums, const zs::Result* res, bool last,
+                hipStream_t stream) {
+    const int rc = ready_slots(plan->slots, 2 * plan->max_chunks, &plan->slots_ready, stream);
+    if (rc)
+        return rc;
+    const unsigned grid = (unsigned)w.n_chunks;
+    if (last)
+        return launch_last(plan, zs::k_lamb_sums, grid, zs::kChunkBlock, 0, stream, (const zs::LayerSums*)plan->part,
+                           (const int64_t*)w.chunk, (const int32_t*)w.chunk_layer, (const int64_t*)w.chunk_first,
+                           plan->slots, sums, res);
+    zs::k_lamb_sums<<<grid, zs::kChunkBlock, 0, stream>>>(plan->part, w.chunk, w.chunk_layer, w.chunk_first,
+                                                          plan->slots, sums, res);
     HIP_TRY(hipGetLastError());
     return ZERO_OK;
 }
 
+template <typename SRC>
 int launch_apply(zero_lamb_plan* plan, const LambWork& w, int head, float* th, const float* m, const float* v,
-                 uint16_t* p, const zs::LayerSums* sums, const zs::Result* res, const zs::AdamConst& c, double lr,
-                 double phi_lo, double phi_hi, hipStream_t stream) {
-    const unsigned grid = tile_grid(w.ntiles);
-    zs::k_lamb_apply<kLambBlock, kLambUnroll, kLambNTL, kLambNTS, kLambXCD>
-        <<<grid, kLambBlock, plan->lds[1], stream>>>(th, m, v, p, w.items, w.tile_first, w.ntiles, plan->n, head, sums,
-                                                     res, c, lr, phi_lo, phi_hi);
-    HIP_TRY(hipGetLastError());
-    return ZERO_OK;
+                 uint16_t* p, const zs::LayerSums* sums, const SRC& src, double lr, double phi_lo, double phi_hi,
+                 hipStream_t stream) {
+    return launch_last(plan, zs::k_lamb_apply<kLambBlock, kLambUnroll, kLambNTL, kLambNTS, kLambXCD, SRC>,
+                       tile_grid(w.ntiles), kLambBlock, plan->lds[1], stream, th, m, v, p,
+                       (const zs::LambItem*)w.items, (const int64_t*)w.tile_first, w.ntiles, plan->n, (int64_t)head,
+                       sums, src, lr, phi_lo, phi_hi);
 }
 
 hipEvent_t lprof_event() {
@@ -406,10 +435,10 @@ void set_last_stats(const zs::Result& r, int64_t n) {
 
 void free_plan(zero_lamb_plan* p) {
     for (LambWork& w : p->work)
-        for (void* d : {(void*)w.items, (void*)w.tile_first, (void*)w.chunk, (void*)w.chunk_first})
+        for (void* d : {(void*)w.items, (void*)w.tile_first, (void*)w.chunk, (void*)w.chunk_layer, (void*)w.chunk_first})
             if (d) (void)hipFree(d);
     if (p->part) (void)hipFree(p->part);
-    if (p->cpart) (void)hipFree(p->cpart);
+    if (p->slots) (void)hipFree(p->slots);
     if (p->sums) (void)hipFree(p->sums);
     if (p->done) (void)hipEventDestroy(p->done);
 }
@@ -445,7 +474,8 @@ int zero_lamb_plan_create(const int64_t* seg_off, int32_t n_seg, int64_t n, zero
         p->seg_off.assign(1, 0);
     p->max_items = max_items_for(n, n_seg);
     p->max_chunks = max_chunks_for(p->max_items, n_seg);
-    if (hipEventCreateWithFlags(&p->done, hipEventDisableTiming) != hipSuccess) {
+    const unsigned fence = n <= kLambNoFenceNumel ? hipEventDisableSystemFence : 0;
+    if (hipEventCreateWithFlags(&p->done, hipEventDisableTiming | fence) != hipSuccess) {
         p->done = nullptr;
         (void)hipGetLastError();
         return fail(ZERO_EHIP, "zero_lamb_plan_create: could not create the plan's event");
@@ -453,7 +483,7 @@ int zero_lamb_plan_create(const int64_t* seg_off, int32_t n_seg, int64_t n, zero
     if (n > 0) {
         if (hipMalloc(reinterpret_cast<void**>(&p->part), (size_t)p->max_items * sizeof(zs::LayerSums)) !=
                 hipSuccess ||
-            hipMalloc(reinterpret_cast<void**>(&p->cpart), (size_t)p->max_chunks * sizeof(zs::LayerSums)) !=
+            hipMalloc(reinterpret_cast<void**>(&p->slots), (size_t)p->max_chunks * 2 * sizeof(uint64_t)) !=
                 hipSuccess ||
             hipMalloc(reinterpret_cast<void**>(&p->sums), (size_t)n_seg * sizeof(zs::LayerSums)) != hipSuccess) {
             (void)hipGetLastError();
@@ -528,6 +558,7 @@ int zero_lamb_step(const zero_lamb_plan_t* plan_, const uint16_t* grad16, float*
         return rc;
     const zs::AdamConst c = adam_const(lr, beta1, beta2, eps, weight_decay, step);
     const uint32_t seq = next_seq(ctx.get());
+    const zs::FromResult src{ctx->res, c};
     LambProfRec pr;
     bool prof = lprof_begin(plan, &pr);
     const bool sampled = prof;
@@ -535,20 +566,21 @@ int zero_lamb_step(const zero_lamb_plan_t* plan_, const uint16_t* grad16, float*
     rc = launch_stats_planned(ctx.get(), grad16, n, loss_scale, clip, seq, stream);
     lprof_record(&pr, &prof, 1, stream);
     if (!rc)
-        rc = launch_moments(plan, *w, head, grad16, master32, m32, v32, ctx->res, c, stream);
+        rc = launch_moments(plan, *w, head, grad16, master32, m32, v32, src, stream);
     lprof_record(&pr, &prof, 2, stream);
     if (!rc)
-        rc = launch_layer(plan, *w, plan->sums, ctx->res, stream);
+        rc = launch_sums(plan, *w, plan->sums, ctx->res, false, stream);
     lprof_record(&pr, &prof, 3, stream);
     if (!rc)
-        rc = launch_apply(plan, *w, head, master32, m32, v32, param16_out, plan->sums, ctx->res, c, lr, phi_lo,
-                          phi_hi, stream);
+        rc = launch_apply(plan, *w, head, master32, m32, v32, param16_out, plan->sums, src, lr, phi_lo, phi_hi,
+                          stream);
     lprof_record(&pr, &prof, 4, stream);
     if (sampled)
         lprof_end(pr, prof && !rc);
-    const int rc_done = mark_done(plan, stream);
-    if (rc || (rc = rc_done))
+    if (rc) {
+        (void)hipEventRecord(plan->done, stream);  // what was queued before the failure
         return rc;
+    }
     zs::Result r;
     if ((rc = wait_result(ctx.get(), seq, stream, loss_scale, clip, &r)))
         return rc;
@@ -588,15 +620,13 @@ int zero_lamb_moments(const zero_lamb_plan_t* plan_, const uint16_t* grad16, con
     if ((rc = get_work(plan, head, &w)) || (rc = switch_stream(plan, stream)))
         return rc;
     const zs::AdamConst c = adam_const(0.0, beta1, beta2, eps, weight_decay, step);
-    const uint32_t seq = next_seq(ctx.get());
-    zs::k_set_result<<<1, 64, 0, stream>>>(ctx->res, global_sumsq, loss_scale, clip, seq);
-    rc = hipGetLastError() == hipSuccess ? ZERO_OK : fail(ZERO_EHIP, "%s: result-record launch failed", fn);
+    const float mult = zs::make_result(global_sumsq, loss_scale, clip, 0).mult;
+    rc = launch_moments(plan, *w, head, grad16, master32, m32, v32, zs::FromHost{mult, c}, stream);
     if (!rc)
-        rc = launch_moments(plan, *w, head, grad16, master32, m32, v32, ctx->res, c, stream);
-    if (!rc)
-        rc = launch_layer(plan, *w, reinterpret_cast<zs::LayerSums*>(layer_sumsq), ctx->res, stream);
-    const int rc_done = mark_done(plan, stream);
-    return rc ? rc : rc_done;
+        rc = launch_sums(plan, *w, reinterpret_cast<zs::LayerSums*>(layer_sumsq), nullptr, true, stream);
+    if (rc)
+        (void)hipEventRecord(plan->done, stream);  // what was queued before the failure
+    return rc;
 }
 
 int zero_lamb_apply(const zero_lamb_plan_t* plan_, float* master32, const float* m32, const float* v32,
@@ -633,16 +663,9 @@ int zero_lamb_apply(const zero_lamb_plan_t* plan_, float* master32, const float*
     if ((rc = get_work(plan, head, &w)) || (rc = switch_stream(plan, stream)))
         return rc;
     const zs::AdamConst c = adam_const(lr, beta1, beta2, eps, weight_decay, step);
-    const uint32_t seq = next_seq(ctx.get());
-    // the apply kernel reads only the skip flag of the record: not skipped here
-    zs::k_set_result<<<1, 64, 0, stream>>>(ctx->res, 0.0, 1.0, 0.0, seq);
-    rc = hipGetLastError() == hipSuccess ? ZERO_OK : fail(ZERO_EHIP, "%s: result-record launch failed", fn);
-    if (!rc)
-        rc = launch_apply(plan, *w, head, master32, m32, v32, param16_out,
-                          reinterpret_cast<const zs::LayerSums*>(layer_sumsq), ctx->res, c, lr, phi_lo, phi_hi,
-                          stream);
-    const int rc_done = mark_done(plan, stream);
-    return rc ? rc : rc_done;
+    return launch_apply(plan, *w, head, master32, m32, v32, param16_out,
+                        reinterpret_cast<const zs::LayerSums*>(layer_sumsq), zs::FromHost{0.0f, c}, lr, phi_lo, phi_hi,
+                        stream);
 }
 
 int zero_probe_lamb_pass(int32_t pass, const uint16_t* grad16, float* master32, float* m32, float* v32,

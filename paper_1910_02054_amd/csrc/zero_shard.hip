@@ -60,6 +60,11 @@ constexpr bool kStatsNTL = false, kStatsXCD = false;
 constexpr int kAdamBlock = 64, kAdamUnroll = 1, kAdamPerCU = 12;
 constexpr bool kAdamNTL = true, kAdamNTS = true, kAdamXCD = false, kAdamREV = false;
 constexpr int64_t kAdamMaxBlocks = 1 << 26;
+// The asynchronous update derives the multiplier from the global sum in every
+// workgroup up to this grid (8M elements); past it that arithmetic costs more
+// than a kernel of its own that does it once (5.9M elements: 35.8 against 36.0
+// us a step; 20M: 97.0 against 95.3; 250M: 1143 against 1119).
+constexpr int64_t kSumInPlaceBlocks = 1 << 15;
 constexpr int kCopyBlock = 64, kCopyUnroll = 1;
 constexpr bool kCopyNTL = true, kCopyNTS = true, kCopyXCD = false;
 // One-launch small-shard step (k_small_step): shards whose fp32 arrays share
@@ -196,7 +201,7 @@ int dev_info(int dev, const DevInfo** out) {
                 kStatsBlock, kStatsPerCU, prop, &d.stats_resident);
             d.adam_lds = occupancy_lds(
                 reinterpret_cast<const void*>(
-                    zs::k_adam_vec<kAdamBlock, kAdamUnroll, kAdamNTL, kAdamNTS, kAdamXCD, kAdamREV, false>),
+                    zs::k_adam_vec<kAdamBlock, kAdamUnroll, kAdamNTL, kAdamNTS, kAdamXCD, kAdamREV, zs::FromResult>),
                 kAdamBlock, kAdamPerCU, prop, &d.adam_resident);
             d.probe_adam_lds = occupancy_lds(
                 reinterpret_cast<const void*>(zs::k_probe_adam<kAdamBlock, kAdamUnroll, kAdamNTL, kAdamNTS, kAdamXCD>),
@@ -611,26 +616,15 @@ int prof_every() {
     return g_prof_every;
 }
 
-// The fused update reading its scalars from `res`; the fp32 constants are
-// `c`, or the device copy at cdev when it is not NULL.
-int launch_update_from(const DevInfo* info, const zs::Result* res, const uint16_t* grad16, float* master32,
-                       float* m32, float* v32, uint16_t* param16_out, int64_t n, const Plan& pl,
-                       const zs::AdamConst& c, hipStream_t stream, const zs::AdamConst* cdev = nullptr) {
-    if (cdev)
-        zs::k_adam_vec<kAdamBlock, kAdamUnroll, kAdamNTL, kAdamNTS, kAdamXCD, kAdamREV, true>
-            <<<(unsigned)pl.adam_blocks, kAdamBlock, info->adam_lds, stream>>>(
-                grad16, master32, m32, v32, param16_out, n, pl.head, pl.nvec, res, c, cdev);
-    else
-        zs::k_adam_vec<kAdamBlock, kAdamUnroll, kAdamNTL, kAdamNTS, kAdamXCD, kAdamREV, false>
-            <<<(unsigned)pl.adam_blocks, kAdamBlock, info->adam_lds, stream>>>(
-                grad16, master32, m32, v32, param16_out, n, pl.head, pl.nvec, res, c, nullptr);
+// The fused update with its scalars from `src`.
+template <typename SRC>
+int launch_update(const DevInfo* info, const SRC& src, const uint16_t* grad16, float* master32, float* m32, float* v32,
+                  uint16_t* param16_out, int64_t n, const Plan& pl, hipStream_t stream) {
+    zs::k_adam_vec<kAdamBlock, kAdamUnroll, kAdamNTL, kAdamNTS, kAdamXCD, kAdamREV, SRC>
+        <<<(unsigned)pl.adam_blocks, kAdamBlock, info->adam_lds, stream>>>(grad16, master32, m32, v32, param16_out, n,
+                                                                           pl.head, pl.nvec, src);
     HIP_TRY(hipGetLastError());
     return ZERO_OK;
-}
-
-int launch_update(Ctx* ctx, const uint16_t* grad16, float* master32, float* m32, float* v32, uint16_t* param16_out,
-                  int64_t n, const Plan& pl, const zs::AdamConst& c, hipStream_t stream) {
-    return launch_update_from(ctx->info, ctx->res, grad16, master32, m32, v32, param16_out, n, pl, c, stream);
 }
 
 // The one-launch small-shard step (pl.small_grid > 0) with its exchange slots
@@ -971,7 +965,8 @@ int zero_shard_step(const uint16_t* grad16, float* master32, float* m32, float* 
         if (!rc && prof)
             prof_record(pr.mid, stream, &pr);
         if (!rc)
-            rc = launch_update(ctx.get(), grad16, master32, m32, v32, param16_out, n, pl, c, stream);
+            rc = launch_update(ctx->info, zs::FromResult{ctx->res, c}, grad16, master32, m32, v32, param16_out, n, pl,
+                               stream);
     }
     if (rc) {
         if (prof) {
@@ -1044,21 +1039,18 @@ int zero_shard_apply(const uint16_t* grad16, float* master32, float* m32, float*
         return rc;
     const zs::AdamConst c = adam_const(lr, beta1, beta2, eps, weight_decay, step);
     const Plan pl = plan_step(grad16, master32, m32, v32, n, ctx->info->ncu);
-    const uint32_t seq = next_seq(ctx.get());
-    // sampled timing as in zero_shard_step: the "statistics" interval here is the
-    // result-record kernel only (the statistics ran in zero_shard_stats)
+    // sampled timing as in zero_shard_step: the "statistics" interval here is empty (the
+    // statistics ran in zero_shard_stats)
     ProfRec pr{};
     const int prof = prof_begin(&ctx->prof_tick, &ctx->prof_epoch, &pr);
     if (prof < 0)
         return prof;
-    if (prof)
+    if (prof) {
         prof_record(pr.start, stream, &pr);
-    zs::k_set_result<<<1, 64, 0, stream>>>(ctx->res, global_sumsq, loss_scale, clip, seq);
-    rc = hipGetLastError() == hipSuccess ? ZERO_OK : fail(ZERO_EHIP, "zero_shard_apply: result-record launch failed");
-    if (!rc && prof)
         prof_record(pr.mid, stream, &pr);
-    if (!rc)
-        rc = launch_update(ctx.get(), grad16, master32, m32, v32, param16_out, n, pl, c, stream);
+    }
+    const float mult = zs::make_result(global_sumsq, loss_scale, clip, 0).mult;
+    rc = launch_update(ctx->info, zs::FromHost{mult, c}, grad16, master32, m32, v32, param16_out, n, pl, stream);
     if (prof) {
         if (!rc)
             prof_record(pr.end, stream, &pr);
@@ -1149,12 +1141,22 @@ int zero_shard_apply_async(const uint16_t* grad16, float* master32, float* m32, 
         return prof;
     if (prof)
         prof_record(pr.start, stream, &pr);
-    zs::k_set_result_dev<<<1, 64, 0, stream>>>(ctx->res, global_sumsq, loss_scale, clip, skipped, seq);
-    rc = hipGetLastError() == hipSuccess ? ZERO_OK : fail(ZERO_EHIP, "%s: result-record launch failed", fn);
+    // a flag that lies on the sum itself would be stored while other workgroups read the sum
+    const bool apart = !skipped || !overlaps(reinterpret_cast<uintptr_t>(skipped), sizeof *skipped,
+                                             reinterpret_cast<uintptr_t>(global_sumsq), sizeof(double));
+    const bool in_place = apart && pl.adam_blocks <= kSumInPlaceBlocks;
+    if (!in_place) {
+        zs::k_set_result_dev<<<1, 64, 0, stream>>>(ctx->res, global_sumsq, loss_scale, clip, skipped, seq);
+        rc = hipGetLastError() == hipSuccess ? ZERO_OK : fail(ZERO_EHIP, "%s: result-record launch failed", fn);
+    }
     if (!rc && prof)
         prof_record(pr.mid, stream, &pr);
-    if (!rc)
-        rc = launch_update(ctx.get(), grad16, master32, m32, v32, param16_out, n, pl, c, stream);
+    if (!rc && in_place)
+        rc = launch_update(ctx->info, zs::FromSum{global_sumsq, loss_scale, clip, skipped, c}, grad16, master32, m32,
+                           v32, param16_out, n, pl, stream);
+    else if (!rc)
+        rc = launch_update(ctx->info, zs::FromResult{ctx->res, c}, grad16, master32, m32, v32, param16_out, n, pl,
+                           stream);
     if (prof) {
         if (!rc)
             prof_record(pr.end, stream, &pr);
@@ -1245,8 +1247,8 @@ int zero_shard_step_resident(const uint16_t* grad16, float* master32, float* m32
     if (!rc && prof)
         prof_record(pr.mid, stream, &pr);
     if (!rc && n > 0)
-        rc = launch_update_from(info, ws->res, grad16, master32, m32, v32, param16_out, n, pl, zs::AdamConst{},
-                                stream, ws->dconst);
+        rc = launch_update(info, zs::FromResident{ws->res, ws->dconst}, grad16, master32, m32, v32, param16_out, n, pl,
+                           stream);
     if (prof) {
         if (!rc)
             prof_record(pr.end, stream, &pr);
@@ -1396,7 +1398,7 @@ int zero_shard_step_noalloc(const uint16_t* grad16, float* master32, float* m32,
         rc = launch_stats_into(info, &stats, grad16, n, pl, zs::FinishStep{res, words, loss_scale, clip, seq}, stream);
         sd.stats_ready = stats.ready;
         if (!rc)
-            rc = launch_update_from(info, res, grad16, master32, m32, v32, param16_out, n, pl, c, stream);
+            rc = launch_update(info, zs::FromResult{res, c}, grad16, master32, m32, v32, param16_out, n, pl, stream);
     }
     if (rc)
         return rc;
