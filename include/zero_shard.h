@@ -289,8 +289,8 @@ typedef struct {
     float mult;       /* fp32 multiplier applied to grad16: (float)(coef/scale)   */
     int32_t overflow; /* 1 if any grad16 element was inf or NaN                   */
     int32_t skipped;  /* equals overflow                                          */
-    int32_t path;     /* 1: the one-launch small-shard step; 0: statistics kernels
-                         and update kernel                                        */
+    int32_t path;     /* 1: the one-launch small-shard step; 0: statistics pass
+                         and the passes after it                                  */
     int64_t n;        /* elements of that call                                    */
 } zero_step_stats_t;
 
@@ -425,7 +425,9 @@ int zero_lamb_plan_destroy(zero_lamb_plan_t* plan);
  * that cuts its flat buffer at layer boundaries).  Arrays, checks, skip
  * semantics, return values and zero_shard_last_stats as for zero_shard_step,
  * with n taken from the plan; phi_lo >= 0, phi_hi >= phi_lo (may be +inf),
- * neither NaN.  The library's per-layer sums live in the plan. */
+ * neither NaN.  Shards of up to about a million elements whose layers are not
+ * too fine (a workgroup of 1024 to 4096 elements meets at most 8) take a single
+ * launch, as zero_shard_step's small shards do and under the same residency.  The library's per-layer sums live in the plan. */
 int zero_lamb_step(const zero_lamb_plan_t* plan, const uint16_t* grad16, float* master32, float* m32, float* v32,
                    uint16_t* param16_out, double lr, double beta1, double beta2, double eps, double weight_decay,
                    int64_t step, double loss_scale, double clip, double phi_lo, double phi_hi, void* stream);
@@ -453,7 +455,8 @@ int zero_lamb_apply(const zero_lamb_plan_t* plan, float* master32, const float* 
 
 /* Kernel timing of sampled zero_lamb_step calls (the sampling period is the
  * one zero_profile_enable sets): events before the statistics, moments,
- * layer-sum and apply kernels and after the last.  zero_lamb_profile_read
+ * layer-sum and apply kernels and after the last (a one-launch step counts as
+ * the apply kernel).  zero_lamb_profile_read
  * waits for the recorded work, returns the sums since the last read and resets
  * them; a deferred profiling failure is reported as by zero_profile_read. */
 typedef struct {

@@ -71,7 +71,8 @@ __device__ __forceinline__ uint64_t slot_wait(uint64_t* slot) {
 }
 
 // Fixed-order sum of one double per thread, returned to every thread.
-// `lds`: kSmallBlock / 64 doubles that no earlier call of the kernel used.
+// `lds`: BLOCK / 64 doubles that no earlier call of the kernel used.
+template <int BLOCK>
 __device__ __forceinline__ double small_block_total(double x, double* lds) {
     x = wave_sum(x);
     if ((threadIdx.x & 63) == 0)
@@ -79,9 +80,33 @@ __device__ __forceinline__ double small_block_total(double x, double* lds) {
     __syncthreads();
     double s = 0.0;
 #pragma unroll
-    for (int w = 0; w < kSmallBlock / 64; ++w)
+    for (int w = 0; w < BLOCK / 64; ++w)
         s += lds[w];
     return s;
+}
+
+// The total of the launch's G slots, the same bits in every workgroup; ends
+// with a barrier, after which *abort is 1 if some slot holds kSlotAbort.
+__device__ __forceinline__ double small_exchange(uint64_t* slots, int G, Sum2* lds2, int* abort) {
+    const int tid = (int)threadIdx.x;
+    if (tid < kSmallSlots) {
+        Sum2 x{0.0, 0.0};
+        if (tid < G) {
+            const uint64_t w = slot_wait(slots + tid);
+            if (w == kSlotAbort)
+                *abort = 1;
+            x.hi = slot_sum(w);
+        }
+        x = wave_sum2(x);
+        if ((tid & 63) == 0)
+            lds2[tid >> 6] = x;
+    }
+    __syncthreads();
+    Sum2 x = lds2[0];
+#pragma unroll
+    for (int w = 1; w < kSmallSlots / 64; ++w)
+        x = sum2_add(x, lds2[w]);
+    return sum2_value(x);
 }
 
 [[maybe_unused]] static __global__ __launch_bounds__(kSmallBlock, 8) void k_small_step(
@@ -123,7 +148,7 @@ __device__ __forceinline__ double small_block_total(double x, double* lds) {
     }
     if (tid == 0)
         s_abort = 0;
-    double tot = small_block_total(a0 + a1, lds);
+    double tot = small_block_total<kSmallBlock>(a0 + a1, lds);
     if (G > 1 && tid == 0)
         slot_fill(slots + b, slot_word(tot));
 
@@ -140,24 +165,7 @@ __device__ __forceinline__ double small_block_total(double x, double* lds) {
 
     // 3. the total of all workgroups
     if (G > 1) {
-        if (tid < kSmallSlots) {
-            Sum2 x{0.0, 0.0};
-            if (tid < G) {
-                const uint64_t w = slot_wait(slots + tid);
-                if (w == kSlotAbort)
-                    s_abort = 1;
-                x.hi = slot_sum(w);
-            }
-            x = wave_sum2(x);
-            if ((tid & 63) == 0)
-                lds2[tid >> 6] = x;
-        }
-        __syncthreads();
-        Sum2 x = lds2[0];
-#pragma unroll
-        for (int w = 1; w < kSmallSlots / 64; ++w)
-            x = sum2_add(x, lds2[w]);
-        tot = sum2_value(x);
+        tot = small_exchange(slots, G, lds2, &s_abort);
         if (s_abort)
             return;
     }

@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <memory>
@@ -17,6 +18,7 @@
 #include "zero_shard.h"
 #include "shard_kernels.hpp"
 #include "lamb_kernels.hpp"
+#include "lamb_small.hpp"
 #include "host_common.hpp"
 
 // ---------------------------------------------------------------------------
@@ -43,12 +45,28 @@ constexpr int kHeads = zs::kMaxHead + 1;  // one work list per head (elements be
 
 using namespace zsh;
 
+constexpr int kLambSmallV[3] = {1, 2, 4};  // tiles per workgroup of the one-launch step
+constexpr int64_t kLambSmallNumel =
+    4 * (int64_t)zs::kLambSmallBlock * 4 * zs::kSmallSlots + zs::kMaxHead + 3;  // the most it can take
+
+// The work lists of the one-launch step for one array alignment, on the device:
+// the layer pieces of its workgroups (with the end sentinel), the first piece of
+// every workgroup and of every layer (each list with its end sentinel).
+struct LambSmall {
+    zs::LambItem* items = nullptr;   // start of the one allocation behind the three lists
+    int64_t* wg_first = nullptr;
+    int64_t* layer_first = nullptr;
+    int v = 0;                       // tiles per workgroup (0: the shard does not fit)
+    unsigned grid = 0;
+    bool built = false;
+};
+
 // The work lists of one array alignment, on the device: the items (tile pieces
 // inside one layer, with the end sentinel), the first item of every tile, the
 // chunks of the layer sums (item ranges inside one layer), each chunk's layer
 // and the first chunk of every layer (the ranges with their end sentinels).
 struct LambWork {
-    zs::LambItem* items = nullptr;
+    zs::LambItem* items = nullptr;   // start of the one allocation behind the five lists
     int64_t* tile_first = nullptr;
     int64_t* chunk = nullptr;
     int32_t* chunk_layer = nullptr;
@@ -68,6 +86,9 @@ struct zero_lamb_plan {
     int32_t n_seg = 0;
     std::vector<int64_t> seg_off;
     LambWork work[kHeads];
+    LambSmall small[kHeads];
+    Slots small_slots;               // exchange slots of the one-launch step (n at most kLambSmallNumel)
+    int64_t small_most[3] = {};      // workgroups of k_lamb_small<1, 2, 4> that the launch may take
     zs::LayerSums* part = nullptr;   // one partial per item (sized for the longest list)
     uint64_t* slots = nullptr;       // two exchange slots per chunk
     bool slots_ready = false;        // the slots have been zeroed
@@ -169,16 +190,33 @@ void build_work(const std::vector<int64_t>& off, int32_t n_seg, int64_t head, Ho
     w->chunk.push_back(n_items);
 }
 
-template <typename T>
-int upload(const std::vector<T>& h, T** d) {
-    if (hipMalloc(reinterpret_cast<void**>(d), h.size() * sizeof(T)) != hipSuccess) {
-        *d = nullptr;
-        (void)hipGetLastError();
-        return fail(ZERO_ENOMEM, "zero_lamb: could not allocate a work list of %zu entries", h.size());
+// Host lists packed for one allocation and one copy to the device (each list on
+// a 16-byte boundary).
+struct Packer {
+    std::vector<unsigned char> bytes;
+    template <typename T>
+    size_t add(const std::vector<T>& h) {
+        const size_t at = (bytes.size() + 15) / 16 * 16;
+        bytes.resize(at + h.size() * sizeof(T));
+        if (!h.empty())
+            std::memcpy(bytes.data() + at, h.data(), h.size() * sizeof(T));
+        return at;
     }
-    HIP_TRY(hipMemcpy(*d, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice));
-    return ZERO_OK;
-}
+    int upload(unsigned char** d) const {
+        if (hipMalloc(reinterpret_cast<void**>(d), bytes.size()) != hipSuccess) {
+            *d = nullptr;
+            (void)hipGetLastError();
+            return fail(ZERO_ENOMEM, "zero_lamb: could not allocate work lists of %zu bytes", bytes.size());
+        }
+        const hipError_t e = hipMemcpy(*d, bytes.data(), bytes.size(), hipMemcpyHostToDevice);
+        if (e != hipSuccess) {
+            (void)hipFree(*d);
+            *d = nullptr;
+            return fail(ZERO_EHIP, "zero_lamb: copying work lists: %s", hipGetErrorString(e));
+        }
+        return ZERO_OK;
+    }
+};
 
 // The work list of `head`, built and uploaded on first use.  Caller holds
 // plan->mu.
@@ -191,17 +229,92 @@ int get_work(zero_lamb_plan* plan, int head, LambWork** out) {
         if (n_items > plan->max_items || n_chunks > plan->max_chunks)
             return fail(ZERO_EHIP, "zero_lamb: work lists (%lld items, %lld chunks) exceed their bounds",
                         (long long)n_items, (long long)n_chunks);
-        int rc;
-        if ((rc = upload(h.items, &w.items)) || (rc = upload(h.tile_first, &w.tile_first)) ||
-            (rc = upload(h.chunk, &w.chunk)) || (rc = upload(h.chunk_layer, &w.chunk_layer)) ||
-            (rc = upload(h.chunk_first, &w.chunk_first)))
+        Packer pk;
+        const size_t at[5] = {pk.add(h.items), pk.add(h.tile_first), pk.add(h.chunk), pk.add(h.chunk_layer),
+                              pk.add(h.chunk_first)};
+        unsigned char* d = nullptr;
+        const int rc = pk.upload(&d);
+        if (rc)
             return rc;
+        w.items = reinterpret_cast<zs::LambItem*>(d + at[0]);
+        w.tile_first = reinterpret_cast<int64_t*>(d + at[1]);
+        w.chunk = reinterpret_cast<int64_t*>(d + at[2]);
+        w.chunk_layer = reinterpret_cast<int32_t*>(d + at[3]);
+        w.chunk_first = reinterpret_cast<int64_t*>(d + at[4]);
         w.n_items = n_items;
         w.ntiles = (int64_t)h.tile_first.size() - 1;
         w.n_chunks = n_chunks;
         w.built = true;
     }
     *out = &w;
+    return ZERO_OK;
+}
+
+const void* small_kernel(int v) {
+    switch (v) {
+    case 1: return reinterpret_cast<const void*>(zs::k_lamb_small<1>);
+    case 2: return reinterpret_cast<const void*>(zs::k_lamb_small<2>);
+    default: return reinterpret_cast<const void*>(zs::k_lamb_small<4>);
+    }
+}
+
+// The one-launch step's shape and work lists for `head`, decided and uploaded
+// on first use: the fewest tiles per workgroup whose grid fits the exchange slots
+// and the plan's share of the device, if no workgroup meets more than kLambPieces
+// layer pieces (v = 0 otherwise).  Caller holds plan->mu.
+int get_small(zero_lamb_plan* plan, int head, LambSmall** out) {
+    LambSmall& w = plan->small[head];
+    *out = &w;
+    if (w.built)
+        return ZERO_OK;
+    const int64_t n = plan->n, nvec = n > head ? (n - head) / 4 : 0;
+    int v = 0;
+    int64_t grid = 0;
+    for (int k = 0; k < 3 && !v && plan->small_slots.words; ++k) {
+        grid = (nvec + zs::kLambSmallBlock * kLambSmallV[k] - 1) / (zs::kLambSmallBlock * kLambSmallV[k]);
+        grid = grid < 1 ? 1 : grid;
+        if (grid <= plan->small_most[k])
+            v = kLambSmallV[k];
+    }
+    if (v) {
+        const int64_t span = 4 * (int64_t)zs::kLambSmallBlock * v;
+        std::vector<zs::LambItem> items;
+        std::vector<int64_t> wg_first, layer_first((size_t)plan->n_seg + 1, 0);
+        int32_t s = 0;       // the layer at pos
+        int64_t pos = 0;
+        for (int64_t b = 0; b < grid && v; ++b) {
+            const int64_t end = b == grid - 1 ? n : head + span * (b + 1);
+            wg_first.push_back((int64_t)items.size());
+            while (pos < end) {
+                if (pos == plan->seg_off[s])
+                    layer_first[s] = (int64_t)items.size();
+                items.push_back(zs::LambItem{pos, s, 0});
+                pos = plan->seg_off[s + 1] < end ? plan->seg_off[s + 1] : end;
+                if (pos == plan->seg_off[s + 1])
+                    ++s;
+            }
+            if ((int64_t)items.size() - wg_first.back() > zs::kLambPieces ||
+                (int64_t)items.size() > zs::kLambSmallItems)
+                v = 0;
+        }
+        if (v) {
+            wg_first.push_back((int64_t)items.size());
+            layer_first[plan->n_seg] = (int64_t)items.size();
+            items.push_back(zs::LambItem{n, -1, 0});
+            Packer pk;
+            const size_t at[3] = {pk.add(items), pk.add(wg_first), pk.add(layer_first)};
+            unsigned char* d = nullptr;
+            const int rc = pk.upload(&d);
+            if (rc)
+                return rc;
+            w.items = reinterpret_cast<zs::LambItem*>(d + at[0]);
+            w.wg_first = reinterpret_cast<int64_t*>(d + at[1]);
+            w.layer_first = reinterpret_cast<int64_t*>(d + at[2]);
+        }
+    }
+    w.v = v;
+    w.grid = (unsigned)grid;
+    w.built = true;
     return ZERO_OK;
 }
 
@@ -341,6 +454,30 @@ int launch_apply(zero_lamb_plan* plan, const LambWork& w, int head, float* th, c
                        sums, src, lr, phi_lo, phi_hi);
 }
 
+// The one-launch step.
+int launch_small(zero_lamb_plan* plan, const LambSmall& w, int head, const uint16_t* g, float* th, float* m, float* v,
+                 uint16_t* p, uint64_t* host_dev, double loss_scale, double clip, uint32_t seq, const zs::AdamConst& c,
+                 double lr, double phi_lo, double phi_hi, hipStream_t stream) {
+    Slots& sl = plan->small_slots;
+    int rc = ready_slots(sl.words, 2 * zs::kLambSmallWords, &sl.ready, stream);
+    if (rc)
+        return rc;
+    uint64_t* const set = sl.words + sl.set * zs::kLambSmallWords;
+    uint64_t* const other = sl.words + (1 - sl.set) * zs::kLambSmallWords;
+    const int n = (int)plan->n, h = head < n ? head : n, nvec = (n - h) / 4;
+    const auto launch = [&](auto kernel) {
+        return launch_last(plan, kernel, w.grid, zs::kLambSmallBlock, 0, stream, g, th, m, v, p, n, h, nvec,
+                           (const zs::LambItem*)w.items, (const int64_t*)w.wg_first, (const int64_t*)w.layer_first,
+                           set, other, host_dev, loss_scale, clip, seq, c, lr, phi_lo, phi_hi);
+    };
+    rc = w.v == 1   ? launch(zs::k_lamb_small<1>)
+         : w.v == 2 ? launch(zs::k_lamb_small<2>)
+                    : launch(zs::k_lamb_small<4>);
+    if (!rc)
+        sl.set = 1 - sl.set;
+    return rc;
+}
+
 hipEvent_t lprof_event() {
     if (!g_lprof_pool.empty()) {
         hipEvent_t e = g_lprof_pool.back();
@@ -421,22 +558,24 @@ void lprof_end(const LambProfRec& rec, bool ok) {
         lprof_drain_locked();
 }
 
-void set_last_stats(const zs::Result& r, int64_t n) {
+void set_last_stats(const zs::Result& r, int64_t n, int32_t path) {
     t_stats.sumsq = r.sumsq;
     t_stats.norm = r.norm;
     t_stats.coef = r.coef;
     t_stats.mult = r.mult;
     t_stats.overflow = r.overflow;
     t_stats.skipped = r.skip;
-    t_stats.path = 0;
+    t_stats.path = path;
     t_stats.n = n;
     t_have_stats = true;
 }
 
 void free_plan(zero_lamb_plan* p) {
     for (LambWork& w : p->work)
-        for (void* d : {(void*)w.items, (void*)w.tile_first, (void*)w.chunk, (void*)w.chunk_layer, (void*)w.chunk_first})
-            if (d) (void)hipFree(d);
+        if (w.items) (void)hipFree(w.items);
+    for (LambSmall& w : p->small)
+        if (w.items) (void)hipFree(w.items);
+    if (p->small_slots.words) (void)hipFree(p->small_slots.words);
     if (p->part) (void)hipFree(p->part);
     if (p->slots) (void)hipFree(p->slots);
     if (p->sums) (void)hipFree(p->sums);
@@ -496,6 +635,29 @@ int zero_lamb_plan_create(const int64_t* seg_off, int32_t n_seg, int64_t n, zero
             free_plan(p.get());
             return fail(ZERO_EHIP, "zero_lamb_plan_create: hipGetDeviceProperties failed");
         }
+        const DevInfo* info = nullptr;
+        int rc = dev_info(p->dev, &info);
+        if (!rc && n <= kLambSmallNumel) {
+            for (int k = 0; k < 3; ++k) {
+                int per_cu = 0;
+                if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, small_kernel(kLambSmallV[k]),
+                                                                 zs::kLambSmallBlock, 0) != hipSuccess) {
+                    (void)hipGetLastError();
+                    per_cu = 0;
+                }
+                p->small_most[k] = std::min<int64_t>(zs::kSmallSlots, (int64_t)per_cu * info->ncu / info->small_share);
+            }
+            if (hipMalloc(reinterpret_cast<void**>(&p->small_slots.words),
+                          2 * zs::kLambSmallWords * sizeof(uint64_t)) != hipSuccess) {
+                (void)hipGetLastError();
+                p->small_slots.words = nullptr;
+                rc = fail(ZERO_ENOMEM, "zero_lamb_plan_create: could not allocate the plan workspace");
+            }
+        }
+        if (rc) {
+            free_plan(p.get());
+            return rc;
+        }
         int resident = 0;
         p->lds[0] = occupancy_lds(moments_kernel(), kLambBlock, kLambPerCU, prop, &resident);
         p->lds[1] = occupancy_lds(apply_kernel(), kLambBlock, kLambPerCU, prop, &resident);
@@ -553,8 +715,10 @@ int zero_lamb_step(const zero_lamb_plan_t* plan_, const uint16_t* grad16, float*
     if ((rc = lock_ctx(stream, &ctx)))
         return rc;
     const int head = (int)line_head(master32, sizeof(float));
+    LambSmall* sm = nullptr;
     LambWork* w = nullptr;
-    if ((rc = get_work(plan, head, &w)) || (rc = switch_stream(plan, stream)))
+    if ((rc = get_small(plan, head, &sm)) || (!sm->v && (rc = get_work(plan, head, &w))) ||
+        (rc = switch_stream(plan, stream)))
         return rc;
     const zs::AdamConst c = adam_const(lr, beta1, beta2, eps, weight_decay, step);
     const uint32_t seq = next_seq(ctx.get());
@@ -563,15 +727,19 @@ int zero_lamb_step(const zero_lamb_plan_t* plan_, const uint16_t* grad16, float*
     bool prof = lprof_begin(plan, &pr);
     const bool sampled = prof;
     lprof_record(&pr, &prof, 0, stream);
-    rc = launch_stats_planned(ctx.get(), grad16, n, loss_scale, clip, seq, stream);
+    if (!sm->v)
+        rc = launch_stats_planned(ctx.get(), grad16, n, loss_scale, clip, seq, stream);
     lprof_record(&pr, &prof, 1, stream);
-    if (!rc)
+    if (!rc && !sm->v)
         rc = launch_moments(plan, *w, head, grad16, master32, m32, v32, src, stream);
     lprof_record(&pr, &prof, 2, stream);
-    if (!rc)
+    if (!rc && !sm->v)
         rc = launch_sums(plan, *w, plan->sums, ctx->res, false, stream);
     lprof_record(&pr, &prof, 3, stream);
-    if (!rc)
+    if (!rc && sm->v)
+        rc = launch_small(plan, *sm, head, grad16, master32, m32, v32, param16_out, ctx->host_dev, loss_scale, clip,
+                          seq, c, lr, phi_lo, phi_hi, stream);
+    else if (!rc)
         rc = launch_apply(plan, *w, head, master32, m32, v32, param16_out, plan->sums, src, lr, phi_lo, phi_hi,
                           stream);
     lprof_record(&pr, &prof, 4, stream);
@@ -582,9 +750,11 @@ int zero_lamb_step(const zero_lamb_plan_t* plan_, const uint16_t* grad16, float*
         return rc;
     }
     zs::Result r;
-    if ((rc = wait_result(ctx.get(), seq, stream, loss_scale, clip, &r)))
+    if ((rc = wait_result(ctx.get(), seq, stream, loss_scale, clip, &r))) {
+        plan->slots_ready = plan->small_slots.ready = false;  // a given-up launch's slots are emptied before the next
         return rc;
-    set_last_stats(r, n);
+    }
+    set_last_stats(r, n, sm->v ? 1 : 0);
     return r.skip ? ZERO_SKIPPED : ZERO_OK;
 }
 
