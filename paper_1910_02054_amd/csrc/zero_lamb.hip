@@ -79,6 +79,15 @@ struct LambProfRec {
     hipEvent_t e[5];
 };
 
+// Per-device launch facts, computed once per device: the occupancy reservations
+// of the moments and apply kernels and the workgroups of k_lamb_small<1, 2, 4>
+// that a launch may take.
+struct LambDev {
+    size_t lds[2] = {0, 0};
+    int64_t small_most[3] = {};
+    bool ready = false;
+};
+
 struct zero_lamb_plan {
     std::mutex mu;
     int dev = 0;
@@ -88,7 +97,7 @@ struct zero_lamb_plan {
     LambWork work[kHeads];
     LambSmall small[kHeads];
     Slots small_slots;               // exchange slots of the one-launch step (n at most kLambSmallNumel)
-    int64_t small_most[3] = {};      // workgroups of k_lamb_small<1, 2, 4> that the launch may take
+    unsigned char* ws = nullptr;     // the one allocation behind the next four
     zs::LayerSums* part = nullptr;   // one partial per item (sized for the longest list)
     uint64_t* slots = nullptr;       // two exchange slots per chunk
     bool slots_ready = false;        // the slots have been zeroed
@@ -98,7 +107,7 @@ struct zero_lamb_plan {
     hipStream_t last_stream = nullptr;
     bool used = false;
     uint64_t prof_tick = 0;
-    size_t lds[2] = {0, 0};  // occupancy reservations of the moments and apply kernels
+    const LambDev* facts = nullptr;
 };
 
 namespace {
@@ -258,6 +267,38 @@ const void* small_kernel(int v) {
     }
 }
 
+std::mutex g_lamb_dev_mu;
+LambDev g_lamb_dev[kMaxDevices];
+
+// The facts of device `dev`, filled on first use.
+int lamb_dev(int dev, const LambDev** out) {
+    const DevInfo* info = nullptr;
+    const int rc = dev_info(dev, &info);  // checks dev
+    if (rc)
+        return rc;
+    std::lock_guard<std::mutex> lk(g_lamb_dev_mu);
+    LambDev& d = g_lamb_dev[dev];
+    if (!d.ready) {
+        hipDeviceProp_t prop;
+        HIP_TRY(hipGetDeviceProperties(&prop, dev));
+        int resident = 0;
+        d.lds[0] = occupancy_lds(moments_kernel(), kLambBlock, kLambPerCU, prop, &resident);
+        d.lds[1] = occupancy_lds(apply_kernel(), kLambBlock, kLambPerCU, prop, &resident);
+        for (int k = 0; k < 3; ++k) {
+            int per_cu = 0;
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, small_kernel(kLambSmallV[k]),
+                                                             zs::kLambSmallBlock, 0) != hipSuccess) {
+                (void)hipGetLastError();
+                per_cu = 0;
+            }
+            d.small_most[k] = std::min<int64_t>(zs::kSmallSlots, (int64_t)per_cu * info->ncu / info->small_share);
+        }
+        d.ready = true;
+    }
+    *out = &d;
+    return ZERO_OK;
+}
+
 // The one-launch step's shape and work lists for `head`, decided and uploaded
 // on first use: the fewest tiles per workgroup whose grid fits the exchange slots
 // and the plan's share of the device, if no workgroup meets more than kLambPieces
@@ -273,7 +314,7 @@ int get_small(zero_lamb_plan* plan, int head, LambSmall** out) {
     for (int k = 0; k < 3 && !v && plan->small_slots.words; ++k) {
         grid = (nvec + zs::kLambSmallBlock * kLambSmallV[k] - 1) / (zs::kLambSmallBlock * kLambSmallV[k]);
         grid = grid < 1 ? 1 : grid;
-        if (grid <= plan->small_most[k])
+        if (grid <= plan->facts->small_most[k])
             v = kLambSmallV[k];
     }
     if (v) {
@@ -421,7 +462,7 @@ template <typename SRC>
 int launch_moments(zero_lamb_plan* plan, const LambWork& w, int head, const uint16_t* g, const float* th, float* m,
                    float* v, const SRC& src, hipStream_t stream) {
     zs::k_lamb_moments<kLambBlock, kLambUnroll, kLambNTL, kLambNTS, kLambXCD, SRC>
-        <<<tile_grid(w.ntiles), kLambBlock, plan->lds[0], stream>>>(g, th, m, v, w.items, w.tile_first, w.ntiles,
+        <<<tile_grid(w.ntiles), kLambBlock, plan->facts->lds[0], stream>>>(g, th, m, v, w.items, w.tile_first, w.ntiles,
                                                                     plan->n, head, src, plan->part);
     HIP_TRY(hipGetLastError());
     return ZERO_OK;
@@ -449,7 +490,7 @@ int launch_apply(zero_lamb_plan* plan, const LambWork& w, int head, float* th, c
                  uint16_t* p, const zs::LayerSums* sums, const SRC& src, double lr, double phi_lo, double phi_hi,
                  hipStream_t stream) {
     return launch_last(plan, zs::k_lamb_apply<kLambBlock, kLambUnroll, kLambNTL, kLambNTS, kLambXCD, SRC>,
-                       tile_grid(w.ntiles), kLambBlock, plan->lds[1], stream, th, m, v, p,
+                       tile_grid(w.ntiles), kLambBlock, plan->facts->lds[1], stream, th, m, v, p,
                        (const zs::LambItem*)w.items, (const int64_t*)w.tile_first, w.ntiles, plan->n, (int64_t)head,
                        sums, src, lr, phi_lo, phi_hi);
 }
@@ -575,10 +616,7 @@ void free_plan(zero_lamb_plan* p) {
         if (w.items) (void)hipFree(w.items);
     for (LambSmall& w : p->small)
         if (w.items) (void)hipFree(w.items);
-    if (p->small_slots.words) (void)hipFree(p->small_slots.words);
-    if (p->part) (void)hipFree(p->part);
-    if (p->slots) (void)hipFree(p->slots);
-    if (p->sums) (void)hipFree(p->sums);
+    if (p->ws) (void)hipFree(p->ws);
     if (p->done) (void)hipEventDestroy(p->done);
 }
 
@@ -620,47 +658,25 @@ int zero_lamb_plan_create(const int64_t* seg_off, int32_t n_seg, int64_t n, zero
         return fail(ZERO_EHIP, "zero_lamb_plan_create: could not create the plan's event");
     }
     if (n > 0) {
-        if (hipMalloc(reinterpret_cast<void**>(&p->part), (size_t)p->max_items * sizeof(zs::LayerSums)) !=
-                hipSuccess ||
-            hipMalloc(reinterpret_cast<void**>(&p->slots), (size_t)p->max_chunks * 2 * sizeof(uint64_t)) !=
-                hipSuccess ||
-            hipMalloc(reinterpret_cast<void**>(&p->sums), (size_t)n_seg * sizeof(zs::LayerSums)) != hipSuccess) {
+        int rc = lamb_dev(p->dev, &p->facts);
+        const bool small = n <= kLambSmallNumel;
+        const size_t part = 0, sums = part + (size_t)p->max_items * sizeof(zs::LayerSums),
+                     slots = sums + (size_t)n_seg * sizeof(zs::LayerSums),
+                     small_slots = slots + (size_t)p->max_chunks * 2 * sizeof(uint64_t),
+                     bytes = small_slots + (small ? 2 * zs::kLambSmallWords * sizeof(uint64_t) : 0);
+        if (!rc && hipMalloc(reinterpret_cast<void**>(&p->ws), bytes) != hipSuccess) {
+            p->ws = nullptr;
             (void)hipGetLastError();
-            free_plan(p.get());
-            return fail(ZERO_ENOMEM, "zero_lamb_plan_create: could not allocate the plan workspace");
-        }
-        hipDeviceProp_t prop;
-        if (hipGetDeviceProperties(&prop, p->dev) != hipSuccess) {
-            (void)hipGetLastError();
-            free_plan(p.get());
-            return fail(ZERO_EHIP, "zero_lamb_plan_create: hipGetDeviceProperties failed");
-        }
-        const DevInfo* info = nullptr;
-        int rc = dev_info(p->dev, &info);
-        if (!rc && n <= kLambSmallNumel) {
-            for (int k = 0; k < 3; ++k) {
-                int per_cu = 0;
-                if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, small_kernel(kLambSmallV[k]),
-                                                                 zs::kLambSmallBlock, 0) != hipSuccess) {
-                    (void)hipGetLastError();
-                    per_cu = 0;
-                }
-                p->small_most[k] = std::min<int64_t>(zs::kSmallSlots, (int64_t)per_cu * info->ncu / info->small_share);
-            }
-            if (hipMalloc(reinterpret_cast<void**>(&p->small_slots.words),
-                          2 * zs::kLambSmallWords * sizeof(uint64_t)) != hipSuccess) {
-                (void)hipGetLastError();
-                p->small_slots.words = nullptr;
-                rc = fail(ZERO_ENOMEM, "zero_lamb_plan_create: could not allocate the plan workspace");
-            }
+            rc = fail(ZERO_ENOMEM, "zero_lamb_plan_create: could not allocate the plan workspace");
         }
         if (rc) {
             free_plan(p.get());
             return rc;
         }
-        int resident = 0;
-        p->lds[0] = occupancy_lds(moments_kernel(), kLambBlock, kLambPerCU, prop, &resident);
-        p->lds[1] = occupancy_lds(apply_kernel(), kLambBlock, kLambPerCU, prop, &resident);
+        p->part = reinterpret_cast<zs::LayerSums*>(p->ws + part);
+        p->sums = reinterpret_cast<zs::LayerSums*>(p->ws + sums);
+        p->slots = reinterpret_cast<uint64_t*>(p->ws + slots);
+        p->small_slots.words = small ? reinterpret_cast<uint64_t*>(p->ws + small_slots) : nullptr;
     }
     *out = p.release();
     return ZERO_OK;
