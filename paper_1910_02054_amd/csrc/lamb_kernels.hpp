@@ -36,28 +36,6 @@ struct alignas(16) LayerSums {
     double usq;
 };
 
-// Adam's moments of one element (the same fp32 sequence as adam_elem); m and v
-// are updated in place.
-__device__ __forceinline__ void lamb_moments_elem(uint32_t g16, float mult, float& m, float& v, const AdamConst& c) {
-#pragma clang fp contract(off)
-    const float g = f16_to_f32(g16) * mult;
-    m = c.b1 * m + c.omb1 * g;
-    v = c.b2 * v + c.omb2 * (g * g);
-}
-
-// The update direction from the new moments and the old parameter: bias
-// correction, eps outside the square root, decoupled weight decay.
-__device__ __forceinline__ float lamb_dir(float m, float v, float th, const AdamConst& c) {
-#pragma clang fp contract(off)
-    const float mhat = m / c.bc1;
-    const float vhat = v / c.bc2;
-    const float denom = __builtin_sqrtf(vhat) + c.eps;
-    float u = mhat / denom;
-    if (c.wd != 0.0f)
-        u = u + c.wd * th;
-    return u;
-}
-
 // The layer's fp32 step size lr * phi(||theta||) / ||u|| (1 for the ratio when
 // either norm is zero), computed in double and rounded once.
 __device__ __forceinline__ float lamb_step_size(LayerSums s, double lr, double phi_lo, double phi_hi) {
@@ -163,10 +141,14 @@ __global__ __launch_bounds__(BLOCK) void k_lamb_moments(const uint16_t* __restri
                 const float t4[4] = {tq.x, tq.y, tq.z, tq.w};
                 float m4[4] = {mq.x, mq.y, mq.z, mq.w};
                 float v4[4] = {vq.x, vq.y, vq.z, vq.w};
+                float d4[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    moments_elem(gw[j], mult, m4[j], v4[j], c);
+                direction4(m4, v4, c, d4);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    lamb_moments_elem(gw[j], mult, m4[j], v4[j], c);
-                    const double ud = (double)lamb_dir(m4[j], v4[j], t4[j], c);
+                    const double ud = (double)decayed(d4[j], t4[j], c);
                     const double td = (double)t4[j];
                     w2[u][j] = td * td;
                     u2[u][j] = ud * ud;
@@ -182,8 +164,8 @@ __global__ __launch_bounds__(BLOCK) void k_lamb_moments(const uint16_t* __restri
                     if (i >= ts && i < te) {
                         float mm = m[i], vv = v[i];
                         const float t = th[i];
-                        lamb_moments_elem(g[i], mult, mm, vv, c);
-                        const double ud = (double)lamb_dir(mm, vv, t, c);
+                        moments_elem(g[i], mult, mm, vv, c);
+                        const double ud = (double)decayed(direction(mm, vv, c), t, c);
                         const double td = (double)t;
                         w2[u][j] = td * td;
                         u2[u][j] = ud * ud;
@@ -308,10 +290,12 @@ __global__ __launch_bounds__(BLOCK) void k_lamb_apply(float* __restrict__ th, co
                 const float tt[4] = {tq.x, tq.y, tq.z, tq.w};
                 const float mm[4] = {mq.x, mq.y, mq.z, mq.w};
                 const float vv[4] = {vq.x, vq.y, vq.z, vq.w};
+                float d4[4];
+                direction4(mm, vv, c, d4);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     t4[u][j] = tt[j];
-                    u4[u][j] = lamb_dir(mm[j], vv[j], tt[j], c);
+                    u4[u][j] = decayed(d4[j], tt[j], c);
                 }
             } else {
 #pragma unroll
@@ -321,7 +305,7 @@ __global__ __launch_bounds__(BLOCK) void k_lamb_apply(float* __restrict__ th, co
                     u4[u][j] = 0.0f;
                     if (i >= ts && i < te) {
                         t4[u][j] = th[i];
-                        u4[u][j] = lamb_dir(m[i], v[i], t4[u][j], c);
+                        u4[u][j] = decayed(direction(m[i], v[i], c), t4[u][j], c);
                     }
                 }
             }

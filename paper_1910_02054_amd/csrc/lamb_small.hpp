@@ -123,27 +123,28 @@ __global__ __launch_bounds__(kLambSmallBlock, lamb_small_waves(V)) void k_lamb_s
         const int i = i0 + k * 64;
         if (i < nvec) {
             const uint32_t gw[4] = {gq[k].x & 0xFFFFu, gq[k].x >> 16, gq[k].y & 0xFFFFu, gq[k].y >> 16};
+            float mm[4], vv[4], d4[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                float mm = mq[k][j], vv = vq[k][j];
-                lamb_moments_elem(gw[j], r.mult, mm, vv, c);
-                mq[k][j] = mm;
-                vq[k][j] = vv;
+                mm[j] = mq[k][j];
+                vv[j] = vq[k][j];
+                moments_elem(gw[j], r.mult, mm[j], vv[j], c);
             }
             const int e = head + 4 * i;
-            st4<true>(mq[k], m + e);
-            st4<true>(vq[k], v + e);
+            st4<true>(f32x4{mm[0], mm[1], mm[2], mm[3]}, m + e);
+            st4<true>(f32x4{vv[0], vv[1], vv[2], vv[3]}, v + e);
+            direction4(mm, vv, c, d4);
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                mq[k][j] = lamb_dir(mq[k][j], vq[k][j], tq[k][j], c);
+                mq[k][j] = decayed(d4[j], tq[k][j], c);
         }
         __builtin_amdgcn_sched_barrier(0);  // one vector's arithmetic at a time: registers
     }
     if (one >= 0) {
-        lamb_moments_elem(g1, r.mult, m1, v1, c);
+        moments_elem(g1, r.mult, m1, v1, c);
         m[one] = m1;
         v[one] = v1;
-        m1 = lamb_dir(m1, v1, t1, c);
+        m1 = decayed(direction(m1, v1, c), t1, c);
     }
 
     // 3. layer sums of the workgroup's pieces
