@@ -461,7 +461,7 @@ int zero_lamb_apply(const zero_lamb_plan_t* plan, float* master32, const float* 
  * them; a deferred profiling failure is reported as by zero_profile_read. */
 typedef struct {
     int64_t steps;      /* steps timed                                  */
-    double stats_ms;    /* statistics + finalize kernels                */
+    double stats_ms;    /* the statistics pass (with its total)          */
     double moments_ms;  /* k_lamb_moments                               */
     double layer_ms;    /* k_lamb_sums                                  */
     double apply_ms;    /* k_lamb_apply                                 */
@@ -493,7 +493,7 @@ const char* zero_last_error(void);
  * ZERO_EINVAL for every < 0. */
 typedef struct {
     int64_t steps;      /* steps timed                                        */
-    double stats_ms;    /* total time of the statistics + finalize kernels    */
+    double stats_ms;    /* total time of the statistics pass                  */
     double update_ms;   /* total time of the fused update kernel              */
 } zero_profile_t;
 
