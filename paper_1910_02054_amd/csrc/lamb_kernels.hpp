@@ -100,6 +100,47 @@ __device__ __forceinline__ int64_t tile_range(int64_t b, int64_t head, int64_t n
 }
 
 // ---------------------------------------------------------------------------
+// Work items: [0, n) cut at the tile boundaries and at the layer boundaries
+// off[0..n_seg].  One thread per tile: its items come after one item per earlier
+// tile and per earlier layer that begins inside a tile (inner[s]: how many of the
+// layers 1..s do), and are the tile's start and the layers that begin inside it.
+// The thread after the last tile writes the end sentinels.  Runs once per plan
+// and alignment: the binary search over the layers is all that it waits for.
+// ---------------------------------------------------------------------------
+constexpr int kItemsBlock = 256;
+
+[[maybe_unused]] static __global__ __launch_bounds__(kItemsBlock) void k_lamb_items(
+    const int64_t* __restrict__ off, const int64_t* __restrict__ inner, int32_t n_seg, int64_t head, int64_t ntiles,
+    int64_t tile, LambItem* __restrict__ items, int64_t* __restrict__ tile_first) {
+    const int64_t b = (int64_t)blockIdx.x * kItemsBlock + threadIdx.x;
+    if (b > ntiles)
+        return;
+    const int64_t n = off[n_seg];
+    if (b == ntiles) {
+        const int64_t k = ntiles + inner[n_seg - 1];
+        tile_first[b] = k;
+        items[k] = LambItem{n, -1, 0};
+        return;
+    }
+    const int64_t hs = head > 0 ? 1 : 0;
+    const int64_t ts = b < hs ? 0 : head + (b - hs) * tile;
+    const int64_t end = b < hs ? head : ts + tile, te = end < n ? end : n;
+    int32_t s = 0, hi = n_seg;  // off[s] <= ts < off[hi]
+    while (hi - s > 1) {
+        const int32_t mid = s + (hi - s) / 2;
+        if (off[mid] <= ts)
+            s = mid;
+        else
+            hi = mid;
+    }
+    int64_t k = b + inner[s];
+    tile_first[b] = k;
+    items[k] = LambItem{ts, s, 0};
+    for (++s; s < n_seg && off[s] < te; ++s)
+        items[++k] = LambItem{off[s], s, 0};
+}
+
+// ---------------------------------------------------------------------------
 // Moments pass.  Workgroup b (grid-strided over the tiles; with XCD, remapped so
 // that each XCD walks a contiguous run of tiles and the tiles' descriptors,
 // which neighbouring tiles share cache lines of, stay in one L2) owns tile b: thread

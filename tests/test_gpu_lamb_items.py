@@ -1,0 +1,54 @@
+"""GPU test of the LAMB work items that the device makes (a tile's start and the
+layers that begin inside its 512 elements): layers that begin on a tile's edge and
+one element before and after it, inside the head before the first tile, tiles of
+many layers, shards shorter than the head and of one tile, at several positions of
+the first tile.  The layer sums of the split phase are compared with exact ones
+(1e-13: a few thousand fp64 additions, each off by at most 2^-53) and the state
+with the oracle."""
+import os
+import sys
+
+import numpy as np
+import pytest
+
+sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
+import gpu_harness as H  # noqa: E402
+
+from paper_1910_02054_amd import workloads  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+HP = (1e-3, 0.9, 0.999, 1e-8, 0.01)
+T = 512
+
+
+@pytest.mark.parametrize("shift", [0, 1, 16, 31])
+@pytest.mark.parametrize("n,edges", [(1, []), (20, [5, 19]), (40, [31, 32, 33]), (T, [1, 2, 3]), (T + 1, []),
+                                     (5 * T + 7, [T, 2 * T, 3 * T]), (256 * T, list(range(T, 200 * T, T))),
+                                     (700 * T + 3, [1, 300 * T])])
+def test_items_at_tile_edges(n, edges, shift):
+    import torch
+    from paper_1910_02054_amd import binding as zb
+    head = -shift % 32
+    cuts = {head} | {head + e + d for e in edges for d in (-1, 0, 1)} | set(edges[:3])
+    seg = np.array([0] + sorted(c for c in cuts if 0 < c < n) + [n], dtype=np.int64)
+    dts = (torch.float16, torch.float32, torch.float32, torch.float32, torch.float16)
+    bufs = [H.Guarded(torch, n, dt, torch.device("cuda:0"), shift=shift) for dt in dts]
+    g16, theta, m, v = workloads.random_case(103, n)
+    for b, a in zip(bufs, [g16, theta, m, v, workloads.p16_sentinel(n)]):
+        b.upload(a)
+    ref = [theta.copy(), m.copy(), v.copy(), workloads.p16_sentinel(n)]
+    out = torch.zeros(2 * (seg.size - 1), dtype=torch.float64, device="cuda")
+    with zb.LambPlan(seg) as plan:
+        for t in (1, 2):
+            views = [b.view for b in bufs]
+            total = zb.zero_shard_stats(views[0])
+            zb.zero_lamb_moments(plan, *views[:4], total, *HP[1:], t, 2.0 ** 16, 1.0, out)
+            zb.zero_lamb_apply(plan, *views[1:], total, out, *HP, t)
+            torch.cuda.synchronize()
+            got = out.cpu().numpy().reshape(-1, 2)[:, 0]
+            want = np.add.reduceat(np.square(ref[0].astype(np.longdouble)), seg[:-1]).astype(np.float64)
+            assert np.all(np.abs(got - want) <= 1e-13 * want)
+            H.oracle_lamb_step(g16, *ref, seg, *HP, t, 2.0 ** 16, 1.0)
+    d = H.compare_state([b.download() for b in bufs[1:]], ref)
+    assert all(b.guards_intact() for b in bufs)
+    print("[gpu-lamb-items] n=%d layers=%d shift=%d %s" % (n, seg.size - 1, shift, d), flush=True)
