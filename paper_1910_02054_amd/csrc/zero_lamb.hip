@@ -24,14 +24,20 @@
 // ---------------------------------------------------------------------------
 // Launch policy of the two LAMB streaming passes (template knobs in
 // lamb_kernels.hpp): one tile of BLOCK*U 4-element vectors per workgroup, at
-// most kLambPerCU resident workgroups per CU (an LDS reservation).  Measured on
-// MI355X over 250M-element shards: both passes run best with about 32 resident
-// waves per CU (128 threads x 16 workgroups, one vector per thread), unlike
-// the Adam update, whose optimum is 12 single-wave workgroups; each workgroup
-// here also reads its tile's layer pieces and reduces a partial sum.
+// most kLambPerCU resident workgroups per CU (an LDS reservation).  Fewer streams
+// in flight suit the DRAM better, as for the Adam update (12 waves), but each
+// wave here also waits for its tile's layer pieces and adds fp64 sums, so about
+// 24 waves are needed to keep the streams busy.  MI355X, 250M elements, us of the
+// moments and the apply pass by resident workgroups: 10: 855, 701; 11: 841, 707;
+// 12: 835, 715; 13: 838, 718; 14: 842, 720; 16: 846, 720 (what the passes had
+// before direction4 halved the arithmetic that more waves hid).  64-thread
+// workgroups, 12: 1049, 933; 24: 832, 729; 256-thread ones, 6: 843, 706.  Tiles in
+// the dispatcher's order, 128 x 12: 853, 733.  Whole steps, 16 against 12: 20M
+// 150.5 -> 149.3, 94M 640 -> 634, 150M 1007 -> 987, 250M 1657 -> 1644.  (10 for the
+// apply pass alone gains on 250M and costs 8 us on 94M.)
 // ---------------------------------------------------------------------------
 namespace {
-constexpr int kLambBlock = 128, kLambUnroll = 1, kLambPerCU = 16;
+constexpr int kLambBlock = 128, kLambUnroll = 1, kLambPerCU = 12;
 constexpr bool kLambNTL = true, kLambNTS = true, kLambXCD = true;
 constexpr int64_t kLambTile = 4 * (int64_t)kLambBlock * kLambUnroll;  // elements per tile
 constexpr int64_t kLambMaxBlocks = 1 << 26;
