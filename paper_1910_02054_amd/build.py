@@ -17,6 +17,9 @@ DEPS = SOURCES + [os.path.join(CSRC, f) for f in ("shard_kernels.hpp", "small_ke
                                                   "lamb_small.hpp", "probe_kernels.hpp", "host_common.hpp")] + \
     [os.path.join(ROOT, "include", "zero_shard.h")]
 LIB = os.path.join(PKG, "libzeroshard.so")
+# The same sources with waits that end at once (shard_kernels.hpp), for the tests of what follows then.
+IMPATIENT_LIB = os.path.join(PKG, "libzeroshard_impatient.so")
+IMPATIENT_FLAGS = ["-DZS_CLOSE_POLLS=0u", "-DZS_SMALL_POLLS=4u"]
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [
@@ -33,13 +36,19 @@ def hipcc() -> str:
 
 
 def build(verbose: bool = False, extra_flags=()) -> str:
-    """Compile the library in-tree; returns its path."""
-    tmp = LIB + ".tmp%d" % os.getpid()
-    cmd = [hipcc(), *HIPCC_FLAGS, *extra_flags, *SOURCES, "-o", tmp]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
-    os.replace(tmp, LIB)
+    """Compile the library, and the tests' build of it, in-tree; returns the library's path."""
+    runs = []
+    for lib, flags in ((LIB, []), (IMPATIENT_LIB, IMPATIENT_FLAGS)):
+        tmp = lib + ".tmp%d" % os.getpid()
+        cmd = [hipcc(), *HIPCC_FLAGS, *flags, *extra_flags, *SOURCES, "-o", tmp]
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        runs.append((cmd, tmp, lib, subprocess.Popen(cmd)))
+    codes = [run[3].wait() for run in runs]
+    for (cmd, tmp, lib, _), code in zip(runs, codes):
+        if code:
+            raise subprocess.CalledProcessError(code, cmd)
+        os.replace(tmp, lib)
     return LIB
 
 

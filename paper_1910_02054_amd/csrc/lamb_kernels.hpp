@@ -282,7 +282,7 @@ __global__ __launch_bounds__(kChunkBlock) void k_lamb_sums(const LayerSums* __re
         w = u = 0.0;
     for (int64_t i = first + threadIdx.x; i < cb; i += 64) {
         uint64_t x = 0, y = 0;
-        for (uint32_t polls = 0; (x == 0 || y == 0) && polls < kSlotSpinLimit; ++polls) {
+        for (uint32_t polls = 0; (x == 0 || y == 0) && polls < kSmallPolls; ++polls) {
             x = aload(slots + 2 * i);
             y = aload(slots + 2 * i + 1);
         }

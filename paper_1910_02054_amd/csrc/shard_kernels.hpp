@@ -322,9 +322,21 @@ __device__ __forceinline__ Sum2 wave_sum2(Sum2 x) {
 // word carries the sum and that it is there.  Slots are accessed with
 // agent-scope atomic operations, which the device keeps coherent across its
 // XCDs without writing back or invalidating the L2 caches.
+//
+// Polls of an empty slot (about 0.5-1 us each) after which a workgroup stops
+// waiting: a closing workgroup then hands over (close_slots), a workgroup of a
+// one-launch step gives the step up (slot_wait).  A build for tests sets both
+// low, so that both happen all the time.
+#ifndef ZS_CLOSE_POLLS
+#define ZS_CLOSE_POLLS (1u << 10)
+#endif
+#ifndef ZS_SMALL_POLLS
+#define ZS_SMALL_POLLS (1u << 22)
+#endif
 constexpr uint64_t kSlotFilled = (uint64_t)1 << 63;
-constexpr uint64_t kSlotAbort = ~(uint64_t)0;          // not the bits of a sum of fp16 squares
-constexpr uint32_t kSlotSpinLimit = 1u << 22;          // polls of about 0.5-1 us each
+constexpr uint64_t kSlotMark = ~(uint64_t)0;           // not the bits of a sum of squares
+constexpr uint32_t kClosePolls = ZS_CLOSE_POLLS;
+constexpr uint32_t kSmallPolls = ZS_SMALL_POLLS;
 
 __device__ __forceinline__ uint64_t slot_word(double x) { return __builtin_bit_cast(uint64_t, x) | kSlotFilled; }
 __device__ __forceinline__ double slot_sum(uint64_t w) { return __builtin_bit_cast(double, w & ~kSlotFilled); }
@@ -335,6 +347,112 @@ __device__ __forceinline__ uint64_t aload(const uint64_t* p) {
 
 __device__ __forceinline__ void astore(uint64_t* p, uint64_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Fills an empty slot, a filled one keeps its value; returns what it held.
+__device__ __forceinline__ uint64_t slot_fill(uint64_t* slot, uint64_t v) {
+    uint64_t held = 0;
+    (void)__hip_atomic_compare_exchange_strong(slot, &held, v, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+    return held;
+}
+
+// The value of a 64-bit word in the wave's first active lane.
+__device__ __forceinline__ uint64_t first_lane(uint64_t x) {
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x) |
+           (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32)) << 32;
+}
+
+// The W sums of each of `count` members, brought together by one of them.  Each
+// member calls this once, with one whole wave and its own sums (read from lane
+// 0); slots[W * i .. W * i + W) are member i's.  It returns true for exactly one
+// member, with sums[k] in every lane: this lane's share (members lane, lane +
+// 64, ...) of the k-th sums, added in a fixed order.  All slots are empty again
+// then.  MANY: there may be more than 64 members.
+//
+// The last member closes: it polls the others' slots, which they normally fill
+// before it gets there or within microseconds.  It must not rely on that:
+// they may not even have been dispatched while other work fills part of the
+// device.  So after kClosePolls it leaves its own sums in its slots, puts
+// kSlotMark into a slot that is still empty and returns; that slot's owner finds
+// the mark when it comes to fill it (the compare-and-swap decides which of the
+// two was first) and closes in its place, or hands over to another late member
+// in turn.  Nobody waits for longer, every launch's total is produced whatever
+// the dispatch order, and no slot is filled after the one that closes emptied
+// it, whether or not a host looks on.
+template <int W, bool MANY>
+__device__ __forceinline__ bool close_slots(uint64_t* slots, int count, int me, const double (&mine)[W],
+                                            double (&sums)[W]) {
+    const int lane = (int)threadIdx.x & 63;
+    uint64_t own[W];
+#pragma unroll
+    for (int k = 0; k < W; ++k)
+        own[k] = slot_word(__builtin_bit_cast(double, first_lane(__builtin_bit_cast(uint64_t, mine[k]))));
+    if (me != count - 1) {
+        bool mark = false;
+        if (lane == 0) {
+            uint64_t held[W];
+#pragma unroll
+            for (int k = 0; k < W; ++k)
+                held[k] = slot_fill(slots + W * me + k, own[k]);
+#pragma unroll
+            for (int k = 0; k < W; ++k)
+                mark = mark || held[k] == kSlotMark;
+        }
+        if (__builtin_expect(!__any(mark), 1))
+            return false;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    }
+    for (;;) {
+        int empty = -1;
+#pragma unroll
+        for (int k = 0; k < W; ++k)
+            sums[k] = 0.0;
+        int i = lane;
+        do {
+            if (i < count) {
+                uint64_t w[W];
+#pragma unroll
+                for (int k = 0; k < W; ++k)
+                    w[k] = i == me ? own[k] : aload(slots + W * i + k);
+#pragma unroll
+                for (int k = 0; k < W; ++k) {
+                    for (uint32_t polls = 0; w[k] == 0 && polls < kClosePolls; ++polls)
+                        w[k] = aload(slots + W * i + k);
+                    if (w[k] == 0)
+                        empty = W * i + k;
+                    sums[k] += slot_sum(w[k]);
+                }
+            }
+            i += 64;
+        } while (MANY && i - lane < count);
+        const uint64_t late = __ballot(empty >= 0);
+        if (__builtin_expect(late == 0, 1))
+            break;
+        const int target = __builtin_amdgcn_readlane(empty, __builtin_ctzll(late));
+        bool handed = false;
+        if (lane == 0) {
+#pragma unroll
+            for (int k = 0; k < W; ++k)
+                astore(slots + W * me + k, own[k]);
+            // the release: whoever finds the mark finds this member's sums, too
+            uint64_t held = 0;
+            handed = __hip_atomic_compare_exchange_strong(slots + target, &held, kSlotMark, __ATOMIC_RELEASE,
+                                                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (__any(handed))
+            return false;
+    }
+    int i = lane;
+    do {
+        if (i < count) {
+#pragma unroll
+            for (int k = 0; k < W; ++k)
+                astore(slots + W * i + k, 0);
+        }
+        i += 64;
+    } while (MANY && i - lane < count);
+    return true;
 }
 
 // Norm, clipping coefficient, multiplier and skip flag from the global sum of
@@ -370,10 +488,9 @@ __device__ __forceinline__ void publish_sum(uint64_t* __restrict__ host, double 
     __hip_atomic_store(host + 1, tag | (w >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// What becomes of the statistics total, by one lane of the last workgroup of
-// k_stats.  `before` runs at that workgroup's start, ahead of the wait for the
-// other workgroups' sums;
-// `ok` is false when that wait was given up (then nothing may be updated).
+// What becomes of the statistics total, by one lane of the workgroup of k_stats
+// that closes its sums.  `before` is called once by that workgroup ahead of
+// `total`; by the last one, which closes them as a rule, at its start.
 // The fused step: the result record, and the sum to the host.
 struct FinishStep {
     Result* res;
@@ -381,10 +498,9 @@ struct FinishStep {
     double loss_scale, clip;
     uint32_t seq;
     __device__ __forceinline__ void before() {}
-    __device__ __forceinline__ void total(double tot, bool ok) {
-        if (ok)
-            publish_sum(host, tot, seq);
-        *res = make_result(ok ? tot : __builtin_nan(""), loss_scale, clip, seq);
+    __device__ __forceinline__ void total(double tot) {
+        publish_sum(host, tot, seq);
+        *res = make_result(tot, loss_scale, clip, seq);
     }
 };
 
@@ -392,26 +508,20 @@ struct FinishStep {
 struct FinishSum {
     double* out;
     __device__ __forceinline__ void before() {}
-    __device__ __forceinline__ void total(double tot, bool ok) { *out = ok ? tot : __builtin_nan(""); }
+    __device__ __forceinline__ void total(double tot) { *out = tot; }
 };
 
-// `own` plus the total of slots[0, count), count < 64, by one wave in a fixed
-// order: waits until each slot is filled and empties it for the next launch.
-// *ok turns false when a slot stays empty for too long or holds kSlotAbort.
-__device__ __forceinline__ double drain_slots(uint64_t* slots, int count, double own, bool* ok) {
-    const int lane = (int)threadIdx.x & 63;
-    Sum2 s{lane == 63 ? own : 0.0, 0.0};
-    bool fine = true;
-    if (lane < count) {
-        uint64_t w = aload(slots + lane);
-        for (uint32_t polls = 0; w == 0 && polls < kSlotSpinLimit; ++polls)
-            w = aload(slots + lane);
-        fine = w != 0 && w != kSlotAbort;
-        astore(slots + lane, 0);
-        s.hi = slot_sum(w);
-    }
-    *ok = *ok && __all(fine);
-    return sum2_value(wave_sum2(s));
+// The total of the sums of `count` <= 64 members (close_slots), by the one member
+// for which this returns true.
+__device__ __forceinline__ bool close_total(uint64_t* slots, int count, int me, double& sum) {
+    if (count == 1)
+        return true;
+    const double mine[1] = {sum};
+    double share[1];
+    if (!close_slots<1, false>(slots, count, me, mine, share))
+        return false;
+    sum = sum2_value(wave_sum2(Sum2{share[0], 0.0}));
+    return true;
 }
 
 // ---------------------------------------------------------------------------
@@ -419,17 +529,18 @@ __device__ __forceinline__ double drain_slots(uint64_t* slots, int count, double
 // first cache line and `nvec` 8-element vectors follow; elements
 // [head + 8*nvec, n) are the tail.  Grid: 1 .. kMaxStatsBlocks workgroups of one
 // wave.  The workgroups' sums meet in two levels, each a fixed-order sum
-// (bitwise reproducible for a given launch shape): workgroup b fills slot b, the
-// last workgroup of every 64 drains its group's slots and fills the group's
-// slot, and the last workgroup of all drains those and finishes (FIN).  A
-// workgroup waits only for workgroups before it, which need nothing from it, so
-// every wait ends however few are resident; it is bounded all the same.
+// (bitwise reproducible for a given launch shape): workgroup b fills slot b, one
+// workgroup of every 64 closes its group's slots (close_slots: the last one, or
+// one that came late) and fills the group's slot, and one of those closes the
+// groups' and finishes (FIN).
 // Reading the gradient bounds the pass on large shards; the total costs two
 // round trips at its end, where a kernel of its own (of one workgroup) took 3.5
 // to 4.6 us a step.  (One level, the last workgroup draining all 2047 slots,
 // took 4 us more than that kernel.)  Steps before and after: resident 1M 14.9 ->
 // 13.3 us and 20K 14.8 -> 11.4, fused 5.9M 36.1 -> 35.3, 94M 420 -> 417.5, 250M
-// 1116 -> 1115.
+// 1116 -> 1115.  That a late workgroup can take the closing over, where a bounded
+// wait was given up with a wrong or missing total, costs 0.25 us (resident 1M
+// 12.45 -> 12.70); the code that is skipped for it takes most of that.
 // ---------------------------------------------------------------------------
 constexpr int kStatsSlots = kMaxStatsBlocks + kMaxStatsBlocks / 64;  // the workgroups', then the groups'
 static_assert(kMaxStatsBlocks <= 64 * 64, "one wave drains the groups");
@@ -467,23 +578,16 @@ __global__ __launch_bounds__(64) void k_stats(const uint16_t* __restrict__ g, in
             a1 += sq1(g[tail0 + t]);
     }
     const double s = wave_sum((a0 + a1) + (a2 + a3));
-    const int b = (int)blockIdx.x, last = (int)gridDim.x - 1, member = b & 63;
-    if (member != 63 && b != last) {
-        if (threadIdx.x == 0)
-            astore(part + b, slot_word(s));
+    const int b = (int)blockIdx.x, last = (int)gridDim.x - 1, group = b >> 6, groups = (last >> 6) + 1;
+    const int count = group == groups - 1 ? (last & 63) + 1 : 64;
+    double tot = s;
+    if (!close_total(part + (b & ~63), count, b & 63, tot) ||
+        !close_total(part + kMaxStatsBlocks, groups, group, tot))
         return;
-    }
-    bool ok = true;
-    if (b != last) {
-        const double t = drain_slots(part + (b - member), member, s, &ok);
-        if (threadIdx.x == 0)
-            astore(part + kMaxStatsBlocks + b / 64, ok ? slot_word(t) : kSlotAbort);
-        return;
-    }
-    double tot = drain_slots(part + (b - member), member, s, &ok);
-    tot = drain_slots(part + kMaxStatsBlocks, b / 64, tot, &ok);
+    if (b != last)
+        fin.before();
     if (threadIdx.x == 0)
-        fin.total(tot, ok);
+        fin.total(tot);
 }
 
 // One double into device memory (the empty shard's local sum, enqueued in order).
@@ -568,9 +672,7 @@ struct FinishResident {
         if (threadIdx.x == 0)
             *cout = c;
     }
-    __device__ __forceinline__ void total(double tot, bool ok) {
-        if (!ok)
-            s.t = 0;  // given up: as a record out of range
+    __device__ __forceinline__ void total(double tot) {
         *res = resident_advance(st, s, tot, seq);
     }
 };

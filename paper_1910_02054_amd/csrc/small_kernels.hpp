@@ -37,7 +37,7 @@ namespace zs {
 //
 // A slot (see shard_kernels.hpp) is filled once, by a compare-and-swap.  Two sets of slots alternate from launch to launch of a
 // stream, and each launch empties the other set.  The wait is bounded: a
-// workgroup that gives up on an empty slot fills it with kSlotAbort in the
+// workgroup that gives up on an empty slot fills it with kSlotMark in the
 // owner's place.  Each slot has one final value that everybody reads, so either
 // every workgroup updates or none does; then nothing is written, the total is
 // not published and the host's wait ends with an error once the stream is
@@ -49,14 +49,7 @@ constexpr int kSmallTiles = 3;                         // the most tiles per wor
 constexpr int kSlotWords = 2 * kSmallSlots;            // two sets
 static_assert(kSmallSlots <= kSmallBlock, "a thread reads at most one slot");
 
-// Fills an empty slot; a filled one keeps its value.
-__device__ __forceinline__ void slot_fill(uint64_t* slot, uint64_t v) {
-    uint64_t empty = 0;
-    (void)__hip_atomic_compare_exchange_strong(slot, &empty, v, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// The value of a slot, waiting until it is filled (with kSlotAbort by this
+// The value of a slot, waiting until it is filled (with kSlotMark by this
 // thread if that takes too long).
 __device__ __forceinline__ uint64_t slot_wait(uint64_t* slot) {
     uint32_t polls = 0;
@@ -64,8 +57,8 @@ __device__ __forceinline__ uint64_t slot_wait(uint64_t* slot) {
         const uint64_t w = aload(slot);
         if (w != 0)
             return w;
-        if (++polls >= kSlotSpinLimit)
-            slot_fill(slot, kSlotAbort);
+        if (++polls >= kSmallPolls)
+            (void)slot_fill(slot, kSlotMark);
         __builtin_amdgcn_s_sleep(1);
     }
 }
@@ -86,14 +79,14 @@ __device__ __forceinline__ double small_block_total(double x, double* lds) {
 }
 
 // The total of the launch's G slots, the same bits in every workgroup; ends
-// with a barrier, after which *abort is 1 if some slot holds kSlotAbort.
+// with a barrier, after which *abort is 1 if some slot holds kSlotMark.
 __device__ __forceinline__ double small_exchange(uint64_t* slots, int G, Sum2* lds2, int* abort) {
     const int tid = (int)threadIdx.x;
     if (tid < kSmallSlots) {
         Sum2 x{0.0, 0.0};
         if (tid < G) {
             const uint64_t w = slot_wait(slots + tid);
-            if (w == kSlotAbort)
+            if (w == kSlotMark)
                 *abort = 1;
             x.hi = slot_sum(w);
         }

@@ -680,8 +680,8 @@ int wait_result(Ctx* ctx, uint32_t seq, hipStream_t stream, double loss_scale, d
             if (e == hipSuccess) {  // everything queued has finished
                 if (ready())
                     break;
-                // a wait on the device was given up: its slots are emptied before the next launch
-                ctx->slots.ready = ctx->stats.ready = false;
+                // a one-launch step was given up: its slots are emptied before the next launch
+                ctx->slots.ready = false;
                 return fail(ZERO_EHIP, "statistics of call %u not published although the stream is idle", seq);
             }
             if (e != hipErrorNotReady)
@@ -774,7 +774,7 @@ static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 struct ScratchDev {
     std::mutex mu;           // serialises this device's allocation-free calls on the host side
     unsigned char* ptr = nullptr;  // the device's copy of `scratch`
-    bool stats_ready = true, slots_ready = true;  // the slots are empty (as loaded) or were emptied
+    bool slots_ready = true;  // the exchange slots are empty (as loaded) or were emptied
     int slots_set = 0;
     uint32_t seq = 0;
 };
@@ -1377,7 +1377,7 @@ int zero_shard_step_noalloc(const uint16_t* grad16, float* master32, float* m32,
     unsigned char* base = nullptr;
     if ((rc = scratch_ptr(dev, &base)))
         return rc;
-    StatsSlots stats{reinterpret_cast<uint64_t*>(base + kScratchStats), sd.stats_ready};
+    StatsSlots stats{reinterpret_cast<uint64_t*>(base + kScratchStats), true};  // empty as loaded
     Slots slots{reinterpret_cast<uint64_t*>(base + kScratchSlots), sd.slots_ready, sd.slots_set};
     zs::Result* res = reinterpret_cast<zs::Result*>(base + kScratchRes);
     uint64_t* words = reinterpret_cast<uint64_t*>(base + kScratchHost);
@@ -1396,7 +1396,6 @@ int zero_shard_step_noalloc(const uint16_t* grad16, float* master32, float* m32,
         sd.slots_set = slots.set;
     } else {
         rc = launch_stats_into(info, &stats, grad16, n, pl, zs::FinishStep{res, words, loss_scale, clip, seq}, stream);
-        sd.stats_ready = stats.ready;
         if (!rc)
             rc = launch_update(info, zs::FromResult{res, c}, grad16, master32, m32, v32, param16_out, n, pl, stream);
     }
@@ -1409,8 +1408,8 @@ int zero_shard_step_noalloc(const uint16_t* grad16, float* master32, float* m32,
     HIP_TRY(hipMemcpyAsync(w, words, sizeof w, hipMemcpyDeviceToHost, stream));
     HIP_TRY(hipStreamSynchronize(stream));
     if (!published(w[0], w[1], seq, &sum)) {
-        // a wait on the device was given up: its slots are emptied before the next launch
-        sd.stats_ready = sd.slots_ready = false;
+        // a one-launch step was given up: its slots are emptied before the next launch
+        sd.slots_ready = false;
         return fail(ZERO_EHIP, "%s: statistics of call %u not published by the step's kernels", fn, seq);
     }
     const zs::Result r = zs::make_result(sum, loss_scale, clip, seq);
