@@ -240,12 +240,11 @@ __global__ __launch_bounds__(BLOCK) void k_lamb_moments(const uint16_t* __restri
 
 // ---------------------------------------------------------------------------
 // Layer sums, two levels in a fixed order.  Workgroup c adds the partials of
-// item chunk c, items [chunk[c], chunk[c+1]) (a chunk never spans two layers),
-// and passes the sums on in its two slots (slot_word: neither sum is negative);
-// the workgroup of a layer's last chunk drains the others' and writes the
-// layer's sums.  It waits only for workgroups before it, which wait for nobody
-// it must make room for, so the wait ends however few are resident.  The second
-// level in a kernel of its own cost 4.7 us a step.
+// item chunk c, items [chunk[c], chunk[c+1]) (a chunk never spans two layers);
+// the workgroups of a layer bring their chunks' sums together through two slots
+// each (close_slots: neither sum is negative) and the one that closes them, the
+// last as a rule, writes the layer's.  The second level in a kernel of its own
+// cost 4.7 us a step.
 // ---------------------------------------------------------------------------
 constexpr int kChunkBlock = 256;
 constexpr int kChunkItems = 1024;   // items per chunk (4 per thread)
@@ -267,32 +266,19 @@ __global__ __launch_bounds__(kChunkBlock) void k_lamb_sums(const LayerSums* __re
         u += p.usq;
     }
     block_sum2<kChunkBlock>(w, u);
-    const int32_t s = chunk_layer[cb];
-    const int64_t first = chunk_first[s];
-    if (cb != chunk_first[s + 1] - 1) {
-        if (threadIdx.x == 0) {
-            astore(slots + 2 * cb, slot_word(w));
-            astore(slots + 2 * cb + 1, slot_word(u));
-        }
-        return;
-    }
     if (threadIdx.x >= 64)
         return;
-    if (threadIdx.x != 0)
-        w = u = 0.0;
-    for (int64_t i = first + threadIdx.x; i < cb; i += 64) {
-        uint64_t x = 0, y = 0;
-        for (uint32_t polls = 0; (x == 0 || y == 0) && polls < kSmallPolls; ++polls) {
-            x = aload(slots + 2 * i);
-            y = aload(slots + 2 * i + 1);
-        }
-        astore(slots + 2 * i, 0);
-        astore(slots + 2 * i + 1, 0);
-        w += x ? slot_sum(x) : __builtin_nan("");
-        u += y ? slot_sum(y) : __builtin_nan("");
+    const int32_t s = chunk_layer[cb];
+    const int64_t first = chunk_first[s];
+    const int count = (int)(chunk_first[s + 1] - first);
+    if (count > 1) {
+        const double mine[2] = {w, u};
+        double share[2];
+        if (!close_slots<2, true>(slots + 2 * first, count, (int)(cb - first), mine, share))
+            return;
+        w = wave_sum(share[0]);
+        u = wave_sum(share[1]);
     }
-    w = wave_sum(w);
-    u = wave_sum(u);
     if (threadIdx.x == 0)
         sums[s] = LayerSums{w, u};
 }

@@ -782,7 +782,7 @@ int zero_lamb_step(const zero_lamb_plan_t* plan_, const uint16_t* grad16, float*
     }
     zs::Result r;
     if ((rc = wait_result(ctx.get(), seq, stream, loss_scale, clip, &r))) {
-        plan->slots_ready = plan->small_slots.ready = false;  // a given-up launch's slots are emptied before the next
+        plan->small_slots.ready = false;  // a one-launch step that was given up: its slots are emptied before the next
         return rc;
     }
     set_last_stats(r, n, sm->v ? 1 : 0);

@@ -1,8 +1,8 @@
 """GPU test of what follows when a workgroup stops waiting for another one's sums.
 build() makes the library a second time with waits that end at the first empty
-slot, so that the closing workgroup of the statistics hands over to a late one in
-nearly every launch (as it does after some thousand polls when other work
-keeps a late workgroup off the device).  The sums are added in the same order
+slot, so that the closing workgroup of the statistics and of a layer's sums hands
+over to a late one in nearly every launch (as it does after some thousand polls
+when other work keeps a late workgroup off the device).  The sums are added in the same order
 whichever workgroup closes them, so every result equals the ordinary library's bit
 for bit, call after call: a slot that one call left filled, or a total that a call
 gave up on, would show in the next.  Gradients change from call to call, with
@@ -23,6 +23,7 @@ from paper_1910_02054_amd import workloads  # noqa: E402
 pytestmark = pytest.mark.gpu
 HP = (1e-3, 0.9, 0.999, 1e-8, 0.01)
 W = 64 * 4 * 8          # gradient elements a workgroup of the statistics reads per round
+C = 1024 * 512          # elements whose LAMB layer sums one workgroup adds
 
 
 @pytest.fixture(scope="module")
@@ -124,3 +125,27 @@ def test_fused_and_asynchronous_steps_closed_by_a_late_workgroup(libs):
             got = flag.item()
         assert got == skip, (k, got, skip)
     assert _equal(torch, *states)
+
+
+@pytest.mark.parametrize("sizes", [[C + 1, 3, 2 * C], [1, 66 * C + 5, 700]])
+def test_layer_sums_closed_by_a_late_workgroup(libs, sizes):
+    torch, zb, zi = libs
+    seg = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    n = int(seg[-1])
+    grads = _gradients(torch, n, 351, count=2)      # the first one overflows
+    states = [_state(torch, n, 361) for _ in range(2)]
+    sums = [torch.zeros(2 * len(sizes), dtype=torch.float64, device="cuda") for _ in range(2)]
+    with zb.LambPlan(seg) as plan, zi.LambPlan(seg) as impatient:
+        for k in range(24):
+            g = grads[k % 5 != 1]
+            for lib, p, state, out in ((zb, plan, states[0], sums[0]), (zi, impatient, states[1], sums[1])):
+                if k % 2 == 0:
+                    total = zb.zero_shard_stats(g)
+                    lib.zero_lamb_moments(p, g, *state[:3], total, *HP[1:], k + 1, 2.0 ** 16, 1.0, out)
+                    lib.zero_lamb_apply(p, *state, total, out, *HP, k + 1)
+                else:
+                    assert lib.zero_lamb_step(p, g, *state, *HP, k + 1, 2.0 ** 16, 1.0) == (k % 5 == 1)
+            assert torch.equal(*sums), (k, sums)
+            if k % 8 == 7:
+                assert _equal(torch, *states), k
+        torch.cuda.synchronize()
