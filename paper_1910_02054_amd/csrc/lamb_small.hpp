@@ -19,8 +19,12 @@ namespace zs {
 //      put into the piece's two slots; the workgroup then adds the slots of all
 //      pieces of its own layers in a fixed order.  (Layers of one piece need no
 //      exchange.)  Every workgroup has filled its gradient slot by then, so all
-//      are resident and none waits before filling its pieces' slots: this wait
-//      ends.
+//      are resident, and each fills all its pieces' slots before it waits for
+//      another's: this wait ends, one exchange deep.  (A wave that waited for its
+//      first piece's layer before filling its next piece's slots chained the
+//      workgroups where the last of five pieces runs on into the next workgroup:
+//      200 workgroups so cut took 260 us a step with its synchronisation, 26 us
+//      now and with one layer.)
 //   4. Step sizes and the update.
 // Latency bounds it: every array is touched once (28 bytes an element, where the
 // kernel sequence moves 42) behind two exchanges.  Against the kernel sequence,
@@ -178,30 +182,44 @@ __global__ __launch_bounds__(kLambSmallBlock, lamb_small_waves(V)) void k_lamb_s
     }
     __syncthreads();
     uint64_t* const pair = set + kSmallSlots;
-    for (int q = wave; q < pieces; q += W) {
-        LayerSums own{0.0, 0.0};
+    // every slot of the workgroup's pieces is filled before the first wait, so no wait depends on another
+    constexpr int Q = (kLambPieces + W - 1) / W;  // the most pieces of a wave
+    LayerSums own[Q];
+    int first[Q], end[Q];
 #pragma unroll
-        for (int x = 0; x < W; ++x) {
-            own.wsq += s_piece[q][x].wsq;
-            own.usq += s_piece[q][x].usq;
-        }
-        const int32_t layer = items[f + q].layer;
-        const int first = (int)layer_first[layer], end = (int)layer_first[layer + 1];
-        if (end - first > 1) {
-            if (lane == 0) {
-                slot_fill(pair + 2 * (f + q), slot_word(own.wsq));
-                slot_fill(pair + 2 * (f + q) + 1, slot_word(own.usq));
+    for (int j = 0; j < Q; ++j) {
+        const int q = wave + j * W;
+        own[j] = LayerSums{0.0, 0.0};
+        first[j] = end[j] = 0;
+        if (q < pieces) {
+#pragma unroll
+            for (int x = 0; x < W; ++x) {
+                own[j].wsq += s_piece[q][x].wsq;
+                own[j].usq += s_piece[q][x].usq;
             }
+            const int32_t layer = items[f + q].layer;
+            first[j] = (int)layer_first[layer];
+            end[j] = (int)layer_first[layer + 1];
+            if (end[j] - first[j] > 1 && lane == 0) {
+                (void)slot_fill(pair + 2 * (f + q), slot_word(own[j].wsq));
+                (void)slot_fill(pair + 2 * (f + q) + 1, slot_word(own[j].usq));
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < Q; ++j) {
+        const int q = wave + j * W;
+        if (end[j] - first[j] > 1) {
             double w = 0.0, u = 0.0;
-            for (int i = first + lane; i < end; i += 64) {
+            for (int i = first[j] + lane; i < end[j]; i += 64) {
                 w += slot_sum(slot_wait(pair + 2 * i));
                 u += slot_sum(slot_wait(pair + 2 * i + 1));
             }
-            own.wsq = wave_sum(w);
-            own.usq = wave_sum(u);
+            own[j].wsq = wave_sum(w);
+            own[j].usq = wave_sum(u);
         }
-        if (lane == 0)
-            s_step[q] = lamb_step_size(own, lr, phi_lo, phi_hi);
+        if (q < pieces && lane == 0)
+            s_step[q] = lamb_step_size(own[j], lr, phi_lo, phi_hi);
     }
     __syncthreads();
 

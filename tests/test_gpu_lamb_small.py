@@ -2,14 +2,16 @@
 layer pieces a workgroup) at the edges of its workgroups (1024, 2048 and 4096
 elements), of its grids (256 workgroups of each size) and just past them, with
 layers that end at, before and after those edges, one-element layers, a layer
-over the whole shard, unequal array offsets, an overflow, and a table too fine
-for it, which keeps the kernel sequence; zero_shard_last_step_stats tells which
+over the whole shard, unequal array offsets, an overflow, the most pieces of a
+workgroup and of a shard with layers that run on into the next workgroup, and
+tables too fine for it, which keep the kernel sequence; zero_shard_last_step_stats tells which
 ran.  Against the oracle (exact layer norms): every fp32 operation of the update
 is correctly rounded in the oracle's order and a layer's fp32 step size comes from
 fp64 norms, so the bound is the repository's 1e-6 and the observed difference is
 zero bits."""
 import os
 import sys
+import time
 
 import numpy as np
 import pytest
@@ -22,6 +24,7 @@ from paper_1910_02054_amd import workloads  # noqa: E402
 pytestmark = pytest.mark.gpu
 HP = (1e-3, 0.9, 0.999, 1e-8, 0.01)
 T = 1024
+EIGHT = [T * b + 10 + 140 * j for b in range(128) for j in range(7)]   # 8 pieces in each of 128 workgroups
 NONE, ALL = (0,) * 5, (3, 1, 1, 1, 2)
 
 
@@ -43,6 +46,9 @@ def _table(n, cuts):
     (1024 * T, [], ALL, False, 1),
     (1024 * T + 40, [77], NONE, False, 0),
     (40 * T, [T + 10 * k for k in range(9)], NONE, False, 0),
+    (40 * T, [c for c in EIGHT if c < 40 * T], NONE, False, 1),
+    (128 * T, EIGHT, NONE, False, 1),       # 1024 pieces, the most
+    (129 * T, EIGHT, NONE, False, 0),       # 1025
 ])
 def test_one_launch_lamb_step(n, cuts, shifts, overflow, path):
     import torch
@@ -70,3 +76,36 @@ def test_one_launch_lamb_step(n, cuts, shifts, overflow, path):
     d = H.compare_state([b.download() for b in bufs[1:]], ref)
     assert all(b.guards_intact() for b in bufs)
     print("[gpu-lamb-small] n=%d layers=%d %s" % (n, seg.size - 1, d), flush=True)
+
+
+def test_layers_across_workgroups_do_not_chain_them():
+    # five pieces a workgroup, the last of which runs on into the next workgroup: its sums must not wait
+    # for the first piece's layer, or the workgroups follow one another (200 exchanges of a microsecond each
+    # where a table of one layer has one)
+    import torch
+    from paper_1910_02054_amd import binding as zb
+    n = 200 * T
+    host = [*workloads.random_case(121, n), workloads.p16_sentinel(n)]
+    bufs = [H.Guarded(torch, n, dt, torch.device("cuda:0")) for dt in
+            (torch.float16, torch.float32, torch.float32, torch.float32, torch.float16)]
+    best = []
+    for cuts in ([], range(1, n, 256)):
+        for b, a in zip(bufs, host):
+            b.upload(a)
+        ref = [a.copy() for a in host[1:]]
+        seg = _table(n, cuts)
+        times = []
+        with zb.LambPlan(seg) as plan:
+            for t in range(1, 101):
+                torch.cuda.synchronize()
+                t0 = time.perf_counter()
+                assert zb.zero_lamb_step(plan, *(b.view for b in bufs), *HP, t, 2.0 ** 16, 1.0) == 0
+                torch.cuda.synchronize()
+                times.append(time.perf_counter() - t0)
+                if t == 1:
+                    H.oracle_lamb_step(host[0], *ref, seg, *HP, t, 2.0 ** 16, 1.0)
+                    H.compare_state([b.download() for b in bufs[1:]], ref)
+        assert zb.zero_shard_last_step_stats().path == 1
+        best.append(min(times) * 1e6)
+    print("[gpu-lamb-small] one layer %.1f us, 256-element layers across workgroups %.1f us" % tuple(best), flush=True)
+    assert best[1] < 3.0 * best[0], best
