@@ -19,8 +19,10 @@ namespace zs {
 //      put into the piece's two slots; the workgroup then adds the slots of all
 //      pieces of its own layers in a fixed order.  (Layers of one piece need no
 //      exchange.)  Every workgroup has filled its gradient slot by then, so all
-//      are resident, and each fills all its pieces' slots before it waits for
-//      another's: this wait ends, one exchange deep.  (A wave that waited for its
+//      are resident, none has given up, and each fills all its pieces' slots
+//      before it waits for another's: this wait ends, one exchange deep, and has
+//      no limit (the moments are written by then and the total is published, so
+//      there is nothing to give up to).  (A wave that waited for its
 //      first piece's layer before filling its next piece's slots chained the
 //      workgroups where the last of five pieces runs on into the next workgroup:
 //      200 workgroups so cut took 260 us a step with its synchronisation, 26 us
@@ -212,8 +214,8 @@ __global__ __launch_bounds__(kLambSmallBlock, lamb_small_waves(V)) void k_lamb_s
         if (end[j] - first[j] > 1) {
             double w = 0.0, u = 0.0;
             for (int i = first[j] + lane; i < end[j]; i += 64) {
-                w += slot_sum(slot_wait(pair + 2 * i));
-                u += slot_sum(slot_wait(pair + 2 * i + 1));
+                w += slot_sum(slot_read(pair + 2 * i));
+                u += slot_sum(slot_read(pair + 2 * i + 1));
             }
             own[j].wsq = wave_sum(w);
             own[j].usq = wave_sum(u);

@@ -63,6 +63,15 @@ __device__ __forceinline__ uint64_t slot_wait(uint64_t* slot) {
     }
 }
 
+// The value of a slot whose owner is known to be running and to fill it without
+// waiting for anybody.
+__device__ __forceinline__ uint64_t slot_read(const uint64_t* slot) {
+    uint64_t w;
+    while ((w = aload(slot)) == 0)
+        __builtin_amdgcn_s_sleep(1);
+    return w;
+}
+
 // Fixed-order sum of one double per thread, returned to every thread.
 // `lds`: BLOCK / 64 doubles that no earlier call of the kernel used.
 template <int BLOCK>
