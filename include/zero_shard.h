@@ -119,8 +119,8 @@ int zero_partition_layout(int64_t total_numel, int32_t nd, int32_t rank, zero_la
  * update in one kernel, the gradient read once); larger ones take the
  * statistics kernels and the update kernel.  The exchange relies on the whole
  * grid being resident at once; its wait is bounded, and should the device
- * not run the grid together within seconds, the step writes nothing and
- * returns ZERO_EHIP.  The call
+ * not run the grid together within seconds, that launch writes nothing and
+ * the kernels of larger shards, which wait for nobody, take the step.  The call
  * blocks until the skip decision is known (the statistics kernels publish it
  * in host-mapped memory, which the calling thread polls); the update kernel
  * may still be running on `stream` when it returns.  Returns 0 applied,

@@ -19,7 +19,7 @@ DEPS = SOURCES + [os.path.join(CSRC, f) for f in ("shard_kernels.hpp", "small_ke
 LIB = os.path.join(PKG, "libzeroshard.so")
 # The same sources with waits that end at once (shard_kernels.hpp), for the tests of what follows then.
 IMPATIENT_LIB = os.path.join(PKG, "libzeroshard_impatient.so")
-IMPATIENT_FLAGS = ["-DZS_CLOSE_POLLS=0u", "-DZS_SMALL_POLLS=4u"]
+IMPATIENT_FLAGS = ["-DZS_CLOSE_POLLS=0u", "-DZS_SMALL_POLLS=1u"]
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [

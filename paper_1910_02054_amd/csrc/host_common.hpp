@@ -136,7 +136,10 @@ int launch_stats_planned(Ctx* ctx, const uint16_t* grad16, int64_t n, double los
 
 // Waits (host polling) until the device has published the sum of call `seq`;
 // *out is the result record of that sum at the call's loss scale and clip.
-int wait_result(Ctx* ctx, uint32_t seq, hipStream_t stream, double loss_scale, double clip, zs::Result* out);
+// *given_up (may be NULL) tells that the call failed because the stream went
+// idle without it: a one-launch step then gave its exchange up and wrote nothing.
+int wait_result(Ctx* ctx, uint32_t seq, hipStream_t stream, double loss_scale, double clip, zs::Result* out,
+                bool* given_up = nullptr);
 
 // Sampling period of kernel profiling (0 = off), set by zero_profile_enable.
 int prof_every();

@@ -752,40 +752,52 @@ int zero_lamb_step(const zero_lamb_plan_t* plan_, const uint16_t* grad16, float*
         (rc = switch_stream(plan, stream)))
         return rc;
     const zs::AdamConst c = adam_const(lr, beta1, beta2, eps, weight_decay, step);
-    const uint32_t seq = next_seq(ctx.get());
     const zs::FromResult src{ctx->res, c};
-    LambProfRec pr;
-    bool prof = lprof_begin(plan, &pr);
-    const bool sampled = prof;
-    lprof_record(&pr, &prof, 0, stream);
-    if (!sm->v)
-        rc = launch_stats_planned(ctx.get(), grad16, n, loss_scale, clip, seq, stream);
-    lprof_record(&pr, &prof, 1, stream);
-    if (!rc && !sm->v)
-        rc = launch_moments(plan, *w, head, grad16, master32, m32, v32, src, stream);
-    lprof_record(&pr, &prof, 2, stream);
-    if (!rc && !sm->v)
-        rc = launch_sums(plan, *w, plan->sums, ctx->res, false, stream);
-    lprof_record(&pr, &prof, 3, stream);
-    if (!rc && sm->v)
-        rc = launch_small(plan, *sm, head, grad16, master32, m32, v32, param16_out, ctx->host_dev, loss_scale, clip,
-                          seq, c, lr, phi_lo, phi_hi, stream);
-    else if (!rc)
-        rc = launch_apply(plan, *w, head, master32, m32, v32, param16_out, plan->sums, src, lr, phi_lo, phi_hi,
-                          stream);
-    lprof_record(&pr, &prof, 4, stream);
-    if (sampled)
-        lprof_end(pr, prof && !rc);
-    if (rc) {
-        (void)hipEventRecord(plan->done, stream);  // what was queued before the failure
-        return rc;
-    }
     zs::Result r;
-    if ((rc = wait_result(ctx.get(), seq, stream, loss_scale, clip, &r))) {
-        plan->small_slots.ready = false;  // a one-launch step that was given up: its slots are emptied before the next
-        return rc;
+    bool given_up = false;
+    const auto attempt = [&](bool small) -> int {
+        const uint32_t seq = next_seq(ctx.get());
+        LambProfRec pr;
+        bool prof = lprof_begin(plan, &pr);
+        const bool sampled = prof;
+        int e = ZERO_OK;
+        lprof_record(&pr, &prof, 0, stream);
+        if (!small)
+            e = launch_stats_planned(ctx.get(), grad16, n, loss_scale, clip, seq, stream);
+        lprof_record(&pr, &prof, 1, stream);
+        if (!e && !small)
+            e = launch_moments(plan, *w, head, grad16, master32, m32, v32, src, stream);
+        lprof_record(&pr, &prof, 2, stream);
+        if (!e && !small)
+            e = launch_sums(plan, *w, plan->sums, ctx->res, false, stream);
+        lprof_record(&pr, &prof, 3, stream);
+        if (!e && small)
+            e = launch_small(plan, *sm, head, grad16, master32, m32, v32, param16_out, ctx->host_dev, loss_scale, clip,
+                             seq, c, lr, phi_lo, phi_hi, stream);
+        else if (!e)
+            e = launch_apply(plan, *w, head, master32, m32, v32, param16_out, plan->sums, src, lr, phi_lo, phi_hi,
+                             stream);
+        lprof_record(&pr, &prof, 4, stream);
+        if (sampled)
+            lprof_end(pr, prof && !e);
+        if (e) {
+            (void)hipEventRecord(plan->done, stream);  // what was queued before the failure
+            return e;
+        }
+        return wait_result(ctx.get(), seq, stream, loss_scale, clip, &r, &given_up);
+    };
+    bool small = sm->v != 0;
+    rc = attempt(small);
+    if (rc && given_up && small) {
+        // the device did not run the one-launch grid together: its slots are emptied before the next
+        // launch, and the kernel sequence, which needs no such thing, takes the step
+        plan->small_slots.ready = small = false;
+        if (!(rc = get_work(plan, head, &w)))
+            rc = attempt(false);
     }
-    set_last_stats(r, n, sm->v ? 1 : 0);
+    if (rc)
+        return rc;
+    set_last_stats(r, n, small ? 1 : 0);
     return r.skip ? ZERO_SKIPPED : ZERO_OK;
 }
 

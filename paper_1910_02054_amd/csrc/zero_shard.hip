@@ -660,8 +660,11 @@ bool published(uint64_t w0, uint64_t w1, uint32_t seq, double* sum) {
 // Wait until the device has published call `seq`.  No event is recorded on the
 // stream for this: event markers between kernels cost several microseconds of
 // GPU idle time each.
-int wait_result(Ctx* ctx, uint32_t seq, hipStream_t stream, double loss_scale, double clip, zs::Result* out) {
+int wait_result(Ctx* ctx, uint32_t seq, hipStream_t stream, double loss_scale, double clip, zs::Result* out,
+                bool* given_up) {
     double sum = 0.0;
+    if (given_up)
+        *given_up = false;
     const auto ready = [&] {
         return published(__atomic_load_n(ctx->host, __ATOMIC_RELAXED), __atomic_load_n(ctx->host + 1, __ATOMIC_RELAXED),
                          seq, &sum);
@@ -682,6 +685,8 @@ int wait_result(Ctx* ctx, uint32_t seq, hipStream_t stream, double loss_scale, d
                     break;
                 // a one-launch step was given up: its slots are emptied before the next launch
                 ctx->slots.ready = false;
+                if (given_up)
+                    *given_up = true;
                 return fail(ZERO_EHIP, "statistics of call %u not published although the stream is idle", seq);
             }
             if (e != hipErrorNotReady)
@@ -945,43 +950,50 @@ int zero_shard_step(const uint16_t* grad16, float* master32, float* m32, float* 
     const zs::AdamConst c = adam_const(lr, beta1, beta2, eps, weight_decay, step);
     Plan pl = plan_step(grad16, master32, m32, v32, n, ctx->info->ncu);
     plan_small(&pl, ctx->info);
-    const uint32_t seq = next_seq(ctx.get());
 
-    ProfRec pr{};
-    const int prof = prof_begin(&ctx->prof_tick, &ctx->prof_epoch, &pr);
-    if (prof < 0)
-        return prof;
-    if (prof)
-        prof_record(pr.start, stream, &pr);
-    if (pl.small_grid) {
-        // one launch: its whole time counts as the update's
+    zs::Result r;
+    bool given_up = false;
+    const auto attempt = [&]() -> int {
+        const uint32_t seq = next_seq(ctx.get());
+        ProfRec pr{};
+        const int prof = prof_begin(&ctx->prof_tick, &ctx->prof_epoch, &pr);
+        if (prof < 0)
+            return prof;
+        int e;
         if (prof)
-            prof_record(pr.mid, stream, &pr);
-        rc = launch_small_into(&ctx->slots, ctx->host_dev, grad16, master32, m32, v32, param16_out, n, pl, loss_scale,
-                               clip, seq, c, stream);
-    } else {
-        rc = launch_stats_into(ctx->info, &ctx->stats, grad16, n, pl,
-                               zs::FinishStep{ctx->res, ctx->host_dev, loss_scale, clip, seq}, stream);
-        if (!rc && prof)
-            prof_record(pr.mid, stream, &pr);
-        if (!rc)
-            rc = launch_update(ctx->info, zs::FromResult{ctx->res, c}, grad16, master32, m32, v32, param16_out, n, pl,
-                               stream);
-    }
-    if (rc) {
+            prof_record(pr.start, stream, &pr);
+        if (pl.small_grid) {
+            // one launch: its whole time counts as the update's
+            if (prof)
+                prof_record(pr.mid, stream, &pr);
+            e = launch_small_into(&ctx->slots, ctx->host_dev, grad16, master32, m32, v32, param16_out, n, pl,
+                                  loss_scale, clip, seq, c, stream);
+        } else {
+            e = launch_stats_into(ctx->info, &ctx->stats, grad16, n, pl,
+                                  zs::FinishStep{ctx->res, ctx->host_dev, loss_scale, clip, seq}, stream);
+            if (!e && prof)
+                prof_record(pr.mid, stream, &pr);
+            if (!e)
+                e = launch_update(ctx->info, zs::FromResult{ctx->res, c}, grad16, master32, m32, v32, param16_out, n,
+                                  pl, stream);
+        }
         if (prof) {
-            pr.ok = false;
+            if (!e)
+                prof_record(pr.end, stream, &pr);
+            else
+                pr.ok = false;
             prof_end(pr);
         }
-        return rc;
+        // The update is already queued: wait only for the statistics.
+        return e ? e : wait_result(ctx.get(), seq, stream, loss_scale, clip, &r, &given_up);
+    };
+    rc = attempt();
+    if (rc && given_up && pl.small_grid) {
+        // the device did not run the one-launch grid together; the kernel sequence needs no such thing
+        pl.small_grid = 0;
+        rc = attempt();
     }
-    if (prof) {
-        prof_record(pr.end, stream, &pr);
-        prof_end(pr);
-    }
-    // The update is already queued: wait only for the statistics.
-    zs::Result r;
-    if ((rc = wait_result(ctx.get(), seq, stream, loss_scale, clip, &r)))
+    if (rc)
         return rc;
     set_stats(r, n, pl.small_grid ? 1 : 0);
     return r.skip ? ZERO_SKIPPED : ZERO_OK;
@@ -1386,33 +1398,40 @@ int zero_shard_step_noalloc(const uint16_t* grad16, float* master32, float* m32,
     plan_small(&pl, info);
     if (pl.stats_blocks > zs::kMaxStatsBlocks)
         return fail(ZERO_EINVAL, "%s: launch needs more partials than the fixed workspace holds", fn);
-    if (++sd.seq == 0)
-        ++sd.seq;
-    const uint32_t seq = sd.seq;
-    if (pl.small_grid) {
-        rc = launch_small_into(&slots, words, grad16, master32, m32, v32, param16_out, n, pl, loss_scale, clip, seq, c,
-                               stream);
-        sd.slots_ready = slots.ready;
-        sd.slots_set = slots.set;
-    } else {
-        rc = launch_stats_into(info, &stats, grad16, n, pl, zs::FinishStep{res, words, loss_scale, clip, seq}, stream);
-        if (!rc)
-            rc = launch_update(info, zs::FromResult{res, c}, grad16, master32, m32, v32, param16_out, n, pl, stream);
-    }
-    if (rc)
-        return rc;
-    // the sum comes back with a copy after the update: the call returns once the whole step has
-    // completed on the stream
-    uint64_t w[2] = {0, 0};
     double sum = 0.0;
-    HIP_TRY(hipMemcpyAsync(w, words, sizeof w, hipMemcpyDeviceToHost, stream));
-    HIP_TRY(hipStreamSynchronize(stream));
-    if (!published(w[0], w[1], seq, &sum)) {
-        // a one-launch step was given up: its slots are emptied before the next launch
+    for (;;) {
+        if (++sd.seq == 0)
+            ++sd.seq;
+        const uint32_t seq = sd.seq;
+        if (pl.small_grid) {
+            rc = launch_small_into(&slots, words, grad16, master32, m32, v32, param16_out, n, pl, loss_scale, clip,
+                                   seq, c, stream);
+            sd.slots_ready = slots.ready;
+            sd.slots_set = slots.set;
+        } else {
+            rc = launch_stats_into(info, &stats, grad16, n, pl, zs::FinishStep{res, words, loss_scale, clip, seq},
+                                   stream);
+            if (!rc)
+                rc = launch_update(info, zs::FromResult{res, c}, grad16, master32, m32, v32, param16_out, n, pl,
+                                   stream);
+        }
+        if (rc)
+            return rc;
+        // the sum comes back with a copy after the update: the call returns once the whole step has
+        // completed on the stream
+        uint64_t w[2] = {0, 0};
+        HIP_TRY(hipMemcpyAsync(w, words, sizeof w, hipMemcpyDeviceToHost, stream));
+        HIP_TRY(hipStreamSynchronize(stream));
+        if (published(w[0], w[1], seq, &sum))
+            break;
+        // a one-launch step was given up: its slots are emptied before the next launch, and the kernel
+        // sequence, which needs no grid run together, takes the step
         sd.slots_ready = false;
-        return fail(ZERO_EHIP, "%s: statistics of call %u not published by the step's kernels", fn, seq);
+        if (!pl.small_grid)
+            return fail(ZERO_EHIP, "%s: statistics of call %u not published by the step's kernels", fn, seq);
+        pl.small_grid = 0;
     }
-    const zs::Result r = zs::make_result(sum, loss_scale, clip, seq);
+    const zs::Result r = zs::make_result(sum, loss_scale, clip, sd.seq);
     set_stats(r, n, pl.small_grid ? 1 : 0);
     return r.skip ? ZERO_SKIPPED : ZERO_OK;
 }

@@ -151,30 +151,28 @@ def test_layer_sums_closed_by_a_late_workgroup(libs, sizes):
         torch.cuda.synchronize()
 
 
-@pytest.mark.parametrize("optimizer", ["adam", "lamb"])
-def test_one_launch_steps_that_stop_waiting(libs, optimizer):
-    # a one-launch step that gives its exchange up writes nothing and says so; one that does not is
-    # right, with LAMB layers that run on from workgroup to workgroup
+@pytest.mark.parametrize("entry", ["step", "noalloc", "lamb"])
+def test_one_launch_steps_that_stop_waiting(libs, entry):
+    # a one-launch step that gives its exchange up has written nothing, and the kernel sequence takes
+    # the step; LAMB's layers run on from workgroup to workgroup
     torch, zb, zi = libs
     n = 200 * 1024
     grads = _gradients(torch, n, 371)
     states = [_state(torch, n, 381) for _ in range(2)]
     seg = np.unique(np.concatenate([[0], np.arange(1, n, 256), [n]])).astype(np.int64)
-    taken = 0
+    paths = [0, 0]
     with zb.LambPlan(seg) as plan, zi.LambPlan(seg) as impatient:
-        def step(lib, p, state, k):
-            if optimizer == "adam":
-                return lib.zero_shard_step(grads[k % 4], *state, *HP, k + 1, 2.0 ** 16, 1.0)
-            return lib.zero_lamb_step(p, grads[k % 4], *state, *HP, k + 1, 2.0 ** 16, 1.0)
         for k in range(200):
-            try:
-                got = step(zi, impatient, states[1], k)
-            except zi.ZeroError as e:
-                assert e.code == zi.ZERO_EHIP
-            else:
-                assert step(zb, plan, states[0], k) == got == (k % 4 == 2)
-                assert zb.zero_shard_last_step_stats().path == 1
-                taken += 1
-            assert _equal(torch, *states), k
+            for lib, p, state in ((zb, plan, states[0]), (zi, impatient, states[1])):
+                args = (grads[k % 4], *state, *HP, k + 1, 2.0 ** 16, 1.0)
+                if entry == "lamb":
+                    skip = lib.zero_lamb_step(p, *args)
+                else:
+                    skip = (lib.zero_shard_step if entry == "step" else lib.zero_shard_step_noalloc)(*args)
+                assert skip == (k % 4 == 2), k
+            assert zb.zero_shard_last_step_stats().path == 1
+            paths[zi.zero_shard_last_step_stats().path] += 1
+            assert _equal(torch, *states), (k, paths)
         torch.cuda.synchronize()
-    print("[gpu-handover] %s: %d of 200 one-launch steps taken" % (optimizer, taken), flush=True)
+    print("[gpu-handover] %s: %d of 200 one-launch steps given up" % (entry, paths[0]), flush=True)
+    assert paths[0] > 0
