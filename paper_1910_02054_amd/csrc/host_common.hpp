@@ -69,6 +69,26 @@ struct StatsSlots {
 // them empty, like any launch).
 int ready_slots(uint64_t* words, int64_t n, bool* ready, hipStream_t stream);
 
+// Allocations made while `stream` may be capturing a graph switch this thread
+// to the relaxed capture mode, in which allocating is permitted.
+struct RelaxedCapture {
+    bool on = false;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    explicit RelaxedCapture(hipStream_t stream) {
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
+            (void)hipGetLastError();
+            return;
+        }
+        if (st != hipStreamCaptureStatusNone && hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess)
+            on = true;
+    }
+    ~RelaxedCapture() {
+        if (on)
+            (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+};
+
 // Per-(device, stream) context: the constant-size workspace of the gradient
 // statistics and the result record the update kernels read.  A context is
 // shared (std::shared_ptr) between the registry and the calls using it, so a

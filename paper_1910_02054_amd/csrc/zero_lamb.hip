@@ -206,14 +206,14 @@ struct Packer {
             std::memcpy(bytes.data() + at, h.data(), h.size() * sizeof(T));
         return at;
     }
-    // Device memory for the packed lists and `more` bytes after them.
-    int upload(unsigned char** d, size_t more = 0) const {
+    // Device memory for the packed lists and `more` bytes after them; the copy is queued on `stream`.
+    int upload(unsigned char** d, size_t more, hipStream_t stream) const {
         if (hipMalloc(reinterpret_cast<void**>(d), bytes.size() + more) != hipSuccess) {
             *d = nullptr;
             (void)hipGetLastError();
             return fail(ZERO_ENOMEM, "zero_lamb: could not allocate work lists of %zu bytes", bytes.size() + more);
         }
-        const hipError_t e = hipMemcpy(*d, bytes.data(), bytes.size(), hipMemcpyHostToDevice);
+        const hipError_t e = hipMemcpyAsync(*d, bytes.data(), bytes.size(), hipMemcpyHostToDevice, stream);
         if (e != hipSuccess) {
             (void)hipFree(*d);
             *d = nullptr;
@@ -227,8 +227,11 @@ struct Packer {
 // items on the device.  Made on the host, the items of a 250M shard are 12 MB to
 // fill, pack and upload: a plan's first step took 9.6 ms there (3.4 ms without the
 // packing) and 3.6 ms (1.4) on 94M; now 1.8 and 0.75 ms, where a later step takes
-// 1.66 and 0.63.  Split phase on 5.9M: 0.28 -> 0.12 ms.  Caller holds plan->mu.
-int get_work(zero_lamb_plan* plan, int head, LambWork** out) {
+// 1.66 and 0.63.  Split phase on 5.9M: 0.28 -> 0.12 ms.  There is a list for each
+// of kHeads positions of the master array in its line, so a captured call may be
+// the first at its position however many the plan has served: a list is made
+// during a capture, too.  Caller holds plan->mu.
+int get_work(zero_lamb_plan* plan, int head, hipStream_t stream, LambWork** out) {
     LambWork& w = plan->work[head];
     if (!w.built) {
         HostWork h;
@@ -242,23 +245,32 @@ int get_work(zero_lamb_plan* plan, int head, LambWork** out) {
                               pk.add(h.chunk_first)};
         pk.bytes.resize((pk.bytes.size() + 15) / 16 * 16);
         const size_t items = pk.bytes.size(), tiles = items + (size_t)(h.n_items + 1) * sizeof(zs::LambItem);
+        // on the null stream and waited for: any stream may use the lists next.  While `stream` is being
+        // captured the null stream may not be used: a stream of their own then
+        RelaxedCapture relaxed(stream);
+        hipStream_t on = nullptr;
+        if (relaxed.on)
+            HIP_TRY(hipStreamCreateWithFlags(&on, hipStreamNonBlocking));
         unsigned char* d = nullptr;
-        const int rc = pk.upload(&d, tiles - items + (size_t)(h.ntiles + 1) * sizeof(int64_t));
+        int rc = pk.upload(&d, tiles - items + (size_t)(h.ntiles + 1) * sizeof(int64_t), on);
+        if (!rc) {
+            const unsigned grid = (unsigned)((h.ntiles + zs::kItemsBlock) / zs::kItemsBlock);
+            zs::k_lamb_items<<<grid, zs::kItemsBlock, 0, on>>>(
+                reinterpret_cast<const int64_t*>(d + at[0]), reinterpret_cast<const int64_t*>(d + at[1]),
+                plan->n_seg, (int64_t)head, h.ntiles, kLambTile, reinterpret_cast<zs::LambItem*>(d + items),
+                reinterpret_cast<int64_t*>(d + tiles));
+            hipError_t e = hipGetLastError();
+            if (e == hipSuccess)
+                e = hipStreamSynchronize(on);
+            if (e != hipSuccess) {
+                (void)hipFree(d);
+                rc = fail(ZERO_EHIP, "zero_lamb: making work lists: %s", hipGetErrorString(e));
+            }
+        }
+        if (on)
+            (void)hipStreamDestroy(on);
         if (rc)
             return rc;
-        // on the null stream, as the copy was, and waited for: any stream may use the lists next
-        const unsigned grid = (unsigned)((h.ntiles + zs::kItemsBlock) / zs::kItemsBlock);
-        zs::k_lamb_items<<<grid, zs::kItemsBlock, 0, nullptr>>>(
-            reinterpret_cast<const int64_t*>(d + at[0]), reinterpret_cast<const int64_t*>(d + at[1]), plan->n_seg,
-            (int64_t)head, h.ntiles, kLambTile, reinterpret_cast<zs::LambItem*>(d + items),
-            reinterpret_cast<int64_t*>(d + tiles));
-        hipError_t e = hipGetLastError();
-        if (e == hipSuccess)
-            e = hipStreamSynchronize(nullptr);
-        if (e != hipSuccess) {
-            (void)hipFree(d);
-            return fail(ZERO_EHIP, "zero_lamb: making work lists: %s", hipGetErrorString(e));
-        }
         w.base = d;
         w.items = reinterpret_cast<zs::LambItem*>(d + items);
         w.tile_first = reinterpret_cast<int64_t*>(d + tiles);
@@ -360,9 +372,13 @@ int get_small(zero_lamb_plan* plan, int head, LambSmall** out) {
             Packer pk;
             const size_t at[3] = {pk.add(items), pk.add(wg_first), pk.add(layer_first)};
             unsigned char* d = nullptr;
-            const int rc = pk.upload(&d);
+            const int rc = pk.upload(&d, 0, nullptr);
             if (rc)
                 return rc;
+            if (hipStreamSynchronize(nullptr) != hipSuccess) {
+                (void)hipFree(d);
+                return fail(ZERO_EHIP, "zero_lamb: copying work lists failed");
+            }
             w.items = reinterpret_cast<zs::LambItem*>(d + at[0]);
             w.wg_first = reinterpret_cast<int64_t*>(d + at[1]);
             w.layer_first = reinterpret_cast<int64_t*>(d + at[2]);
@@ -748,7 +764,7 @@ int zero_lamb_step(const zero_lamb_plan_t* plan_, const uint16_t* grad16, float*
     const int head = (int)line_head(master32, sizeof(float));
     LambSmall* sm = nullptr;
     LambWork* w = nullptr;
-    if ((rc = get_small(plan, head, &sm)) || (!sm->v && (rc = get_work(plan, head, &w))) ||
+    if ((rc = get_small(plan, head, &sm)) || (!sm->v && (rc = get_work(plan, head, stream, &w))) ||
         (rc = switch_stream(plan, stream)))
         return rc;
     const zs::AdamConst c = adam_const(lr, beta1, beta2, eps, weight_decay, step);
@@ -792,7 +808,7 @@ int zero_lamb_step(const zero_lamb_plan_t* plan_, const uint16_t* grad16, float*
         // the device did not run the one-launch grid together: its slots are emptied before the next
         // launch, and the kernel sequence, which needs no such thing, takes the step
         plan->small_slots.ready = small = false;
-        if (!(rc = get_work(plan, head, &w)))
+        if (!(rc = get_work(plan, head, stream, &w)))
             rc = attempt(false);
     }
     if (rc)
@@ -830,7 +846,7 @@ int zero_lamb_moments(const zero_lamb_plan_t* plan_, const uint16_t* grad16, con
         return rc;
     const int head = (int)line_head(master32, sizeof(float));
     LambWork* w = nullptr;
-    if ((rc = get_work(plan, head, &w)) || (rc = switch_stream(plan, stream)))
+    if ((rc = get_work(plan, head, stream, &w)) || (rc = switch_stream(plan, stream)))
         return rc;
     const zs::AdamConst c = adam_const(0.0, beta1, beta2, eps, weight_decay, step);
     const float mult = zs::make_result(global_sumsq, loss_scale, clip, 0).mult;
@@ -873,7 +889,7 @@ int zero_lamb_apply(const zero_lamb_plan_t* plan_, float* master32, const float*
         return rc;
     const int head = (int)line_head(master32, sizeof(float));
     LambWork* w = nullptr;
-    if ((rc = get_work(plan, head, &w)) || (rc = switch_stream(plan, stream)))
+    if ((rc = get_work(plan, head, stream, &w)) || (rc = switch_stream(plan, stream)))
         return rc;
     const zs::AdamConst c = adam_const(lr, beta1, beta2, eps, weight_decay, step);
     return launch_apply(plan, *w, head, master32, m32, v32, param16_out,

@@ -242,26 +242,6 @@ void free_ctx_buffers(Ctx* c) {
     c->host = c->host_dev = nullptr;
 }
 
-// Allocations made while `stream` may be capturing a graph switch this thread
-// to the relaxed capture mode, in which allocating is permitted.
-struct RelaxedCapture {
-    bool on = false;
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    explicit RelaxedCapture(hipStream_t stream) {
-        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(stream, &st) != hipSuccess) {
-            (void)hipGetLastError();
-            return;
-        }
-        if (st != hipStreamCaptureStatusNone && hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess)
-            on = true;
-    }
-    ~RelaxedCapture() {
-        if (on)
-            (void)hipThreadExchangeStreamCaptureMode(&mode);
-    }
-};
-
 int new_ctx(int dev, hipStream_t stream, const DevInfo* info, std::shared_ptr<Ctx>* out) {
     std::shared_ptr<Ctx> c = std::make_shared<Ctx>();
     c->dev = dev;

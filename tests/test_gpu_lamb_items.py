@@ -52,3 +52,46 @@ def test_items_at_tile_edges(n, edges, shift):
     d = H.compare_state([b.download() for b in bufs[1:]], ref)
     assert all(b.guards_intact() for b in bufs)
     print("[gpu-lamb-items] n=%d layers=%d shift=%d %s" % (n, seg.size - 1, shift, d), flush=True)
+
+
+def test_split_phase_captured_on_arrays_at_another_line_offset():
+    # a plan whose lists were made by a call on arrays at a line's start, captured on arrays 16 bytes into
+    # a line: the capture has to come by that offset's list, and its replays are the eager calls' steps
+    import torch
+    from paper_1910_02054_amd import binding as zb
+    n = 700_001
+    seg = np.array([0, 1, 300_000, 300_700, n], np.int64)
+    hp = (1e-3, 0.9, 0.999, 1e-6, 0.01)
+    g16, theta, m, v = workloads.random_case(151, n)
+    dts = (torch.float16, torch.float32, torch.float32, torch.float32, torch.float16)
+    sets = [[H.Guarded(torch, n, dt, torch.device("cuda:0"), shift=s) for dt in dts] for s in (0, 4)]
+    for bufs in sets:
+        for b, a in zip(bufs, (g16, theta, m, v, workloads.p16_sentinel(n))):
+            b.upload(a)
+    sums = torch.zeros(2 * (seg.size - 1), dtype=torch.float64, device="cuda")
+    total = zb.zero_shard_stats(sets[0][0].view)
+
+    def step(plan, bufs):
+        views = [b.view for b in bufs]
+        zb.zero_lamb_moments(plan, *views[:4], total, *hp[1:], 1, 2.0 ** 16, 1.0, sums)
+        zb.zero_lamb_apply(plan, *views[1:], total, sums, *hp, 1)
+
+    stream = torch.cuda.Stream()
+    with zb.LambPlan(seg) as plan:
+        stream.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(stream):
+            step(plan, sets[0])
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            step(plan, sets[1])
+        for _ in range(3):
+            graph.replay()
+            torch.cuda.synchronize()
+            for x, y in zip(*([b.download().copy() for b in bufs] for bufs in sets)):
+                assert np.array_equal(x.view(np.uint8), y.view(np.uint8))
+            with zb.LambPlan(seg) as eager:
+                step(eager, sets[0])
+                torch.cuda.synchronize()
+        del graph
+    assert all(b.guards_intact() for bufs in sets for b in bufs)
