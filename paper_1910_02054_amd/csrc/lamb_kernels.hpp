@@ -259,6 +259,9 @@ __global__ __launch_bounds__(kChunkBlock) void k_lamb_sums(const LayerSums* __re
         return;
     const int64_t cb = blockIdx.x;
     const int64_t a = chunk[cb], e = chunk[cb + 1];
+    const int32_t s = chunk_layer[cb];  // read ahead of the sums: two dependent reads
+    const int64_t first = chunk_first[s];
+    const int count = (int)(chunk_first[s + 1] - first);
     double w = 0.0, u = 0.0;
     for (int64_t i = a + threadIdx.x; i < e; i += kChunkBlock) {
         const LayerSums p = part[i];
@@ -268,9 +271,6 @@ __global__ __launch_bounds__(kChunkBlock) void k_lamb_sums(const LayerSums* __re
     block_sum2<kChunkBlock>(w, u);
     if (threadIdx.x >= 64)
         return;
-    const int32_t s = chunk_layer[cb];
-    const int64_t first = chunk_first[s];
-    const int count = (int)(chunk_first[s + 1] - first);
     if (count > 1) {
         const double mine[2] = {w, u};
         double share[2];

@@ -403,55 +403,64 @@ __device__ __forceinline__ bool close_slots(uint64_t* slots, int count, int me, 
             return false;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
-    for (;;) {
-        int empty = -1;
+#pragma unroll
+    for (int k = 0; k < W; ++k)
+        sums[k] = 0.0;
+    int base = 0;
+    do {
+        const int i = base + lane;
+        uint64_t* const theirs = slots + W * i;
+        uint64_t w[W];
 #pragma unroll
         for (int k = 0; k < W; ++k)
-            sums[k] = 0.0;
-        int i = lane;
+            w[k] = own[k];
+        // one exit and branches of the whole wave: this is on the path to every total
+        uint64_t late;
+        bool handed = false;
+        uint32_t polls = 0;
         do {
-            if (i < count) {
-                uint64_t w[W];
+            bool missing = false;
+            if (i < count && i != me) {
 #pragma unroll
                 for (int k = 0; k < W; ++k)
-                    w[k] = i == me ? own[k] : aload(slots + W * i + k);
+                    w[k] = aload(theirs + k);
 #pragma unroll
-                for (int k = 0; k < W; ++k) {
-                    for (uint32_t polls = 0; w[k] == 0 && polls < kClosePolls; ++polls)
-                        w[k] = aload(slots + W * i + k);
-                    if (w[k] == 0)
-                        empty = W * i + k;
-                    sums[k] += slot_sum(w[k]);
-                }
+                for (int k = 0; k < W; ++k)
+                    missing = missing || w[k] == 0;
             }
-            i += 64;
-        } while (MANY && i - lane < count);
-        const uint64_t late = __ballot(empty >= 0);
-        if (__builtin_expect(late == 0, 1))
-            break;
-        const int target = __builtin_amdgcn_readlane(empty, __builtin_ctzll(late));
-        bool handed = false;
-        if (lane == 0) {
+            late = __ballot(missing);
+            if (__builtin_expect(late != 0 && polls++ >= kClosePolls, 0)) {
+                if (lane == __builtin_ctzll(late)) {
+                    int empty = 0;
 #pragma unroll
-            for (int k = 0; k < W; ++k)
-                astore(slots + W * me + k, own[k]);
-            // the release: whoever finds the mark finds this member's sums, too
-            uint64_t held = 0;
-            handed = __hip_atomic_compare_exchange_strong(slots + target, &held, kSlotMark, __ATOMIC_RELEASE,
-                                                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+                    for (int k = W - 1; k >= 0; --k) {
+                        astore(slots + W * me + k, own[k]);
+                        empty = w[k] == 0 ? k : empty;
+                    }
+                    // the release: whoever finds the mark finds this member's sums, too
+                    uint64_t held = 0;
+                    handed = __hip_atomic_compare_exchange_strong(theirs + empty, &held, kSlotMark, __ATOMIC_RELEASE,
+                                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                late = __any(handed) ? 0 : late;
+            }
+        } while (late != 0);
         if (__any(handed))
             return false;
-    }
-    int i = lane;
-    do {
         if (i < count) {
 #pragma unroll
             for (int k = 0; k < W; ++k)
-                astore(slots + W * i + k, 0);
+                sums[k] += slot_sum(w[k]);
         }
-        i += 64;
-    } while (MANY && i - lane < count);
+        base += 64;
+    } while (MANY && base < count);
+    for (int i = lane; i < count; i += 64) {
+#pragma unroll
+        for (int k = 0; k < W; ++k)
+            astore(slots + W * i + k, 0);
+        if (!MANY)
+            break;
+    }
     return true;
 }
 
@@ -539,8 +548,9 @@ __device__ __forceinline__ bool close_total(uint64_t* slots, int count, int me, 
 // took 4 us more than that kernel.)  Steps before and after: resident 1M 14.9 ->
 // 13.3 us and 20K 14.8 -> 11.4, fused 5.9M 36.1 -> 35.3, 94M 420 -> 417.5, 250M
 // 1116 -> 1115.  That a late workgroup can take the closing over, where a bounded
-// wait was given up with a wrong or missing total, costs 0.25 us (resident 1M
-// 12.45 -> 12.70); the code that is skipped for it takes most of that.
+// wait was given up with a wrong or missing total, costs 0.3 us (resident 1M
+// 12.57 -> 12.86, asynchronous 5.9M 35.3 -> 35.6); the code that is skipped for it
+// takes most of that, not the compare-and-swap.
 // ---------------------------------------------------------------------------
 constexpr int kStatsSlots = kMaxStatsBlocks + kMaxStatsBlocks / 64;  // the workgroups', then the groups'
 static_assert(kMaxStatsBlocks <= 64 * 64, "one wave drains the groups");
