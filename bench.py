@@ -439,14 +439,14 @@ def main():
     if lamb:
         step_gbps = LAMB_STEP_BYTES_PER_PARAM * n / (ms * 1e-3) / 1e9
         k = lprof.steps
-        kernel_ms = {"stats_and_finalize": lprof.stats_ms / k, "moments": lprof.moments_ms / k,
+        kernel_ms = {"statistics": lprof.stats_ms / k, "moments": lprof.moments_ms / k,
                      "layer_sums": lprof.layer_ms / k, "apply": lprof.apply_ms / k, "profiled_steps": k}
         upd_gbps = LAMB_MOMENTS_BYTES_PER_PARAM * n / (kernel_ms["moments"] * 1e-3) / 1e9
         apply_gbps = LAMB_APPLY_BYTES_PER_PARAM * n / (kernel_ms["apply"] * 1e-3) / 1e9
         roof_kernel, traffic = "k_lamb_moments", measured_lamb_traffic(n)
     else:
         step_gbps = STEP_BYTES_PER_PARAM * n / (ms * 1e-3) / 1e9
-        kernel_ms = {"stats_and_finalize": prof.stats_ms / prof.steps, "update": prof.update_ms / prof.steps,
+        kernel_ms = {"statistics": prof.stats_ms / prof.steps, "update": prof.update_ms / prof.steps,
                      "profiled_steps": prof.steps}
         upd_gbps = UPDATE_BYTES_PER_PARAM * n / (kernel_ms["update"] * 1e-3) / 1e9
         fused = not (args.resident or args.split_phase)
@@ -487,7 +487,7 @@ def main():
         out["config"].update(path="split phase: zero_shard_stats_async, device-resident global sum, "
                                   "zero_shard_apply_async (no host wait)" if args.async_seam else
                                   "split phase: zero_shard_stats, host-side global sum, zero_shard_apply")
-        out["kernel_ms"]["stats_and_finalize"] = None  # timed per apply: only the result-record kernel
+        out["kernel_ms"]["statistics"] = None  # timed per apply: only the result-record kernel
     if lamb:
         out["config"].update(optimizer="lamb", layers=int(seg.size - 1))
         out["lamb_apply"] = {"kernel": "k_lamb_apply", "achieved_gbps": apply_gbps,

@@ -766,7 +766,7 @@ __device__ __forceinline__ float direction(float m, float v, const AdamConst& c)
 //     midpoint between floats and lies at least 2^-49 from one, so the rounding
 //     is the quotient's.
 //   sqrt: v_rsq_f32 and one fused residual step (equal to the correctly rounded
-//     root for every float in [2^-102, 2^85], compared one by one on the chip).
+//     root for every float in [2^-100, 2^84): the GPU tests go through them all).
 //   mhat / denom: v_rcp_f32, one Newton step, and two residual corrections
 //     (Markstein): the general division's own sequence without its scaling.
 __device__ __forceinline__ float direction_quick(float m, float v, const AdamConst& c) {

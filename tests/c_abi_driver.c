@@ -10,7 +10,7 @@
  *
  * Cases: shards of several lengths, with all arrays 16-byte aligned, all
  * shifted by the same element count (vector path with a scalar head) and
- * shifted by different counts (scalar path); per case three fused steps, the
+ * shifted by different counts; per case three fused steps, the
  * second with an inf gradient (skipped, nothing written), then one split-phase
  * step (zero_shard_stats, then zero_shard_apply with that sum as the global
  * one), each compared byte for byte with the oracle; then LAMB steps through a

@@ -62,3 +62,39 @@ def test_direction_equals_the_general_operations(kind, beta1, beta2, eps, t, n):
         assert same.all(), (name, a[~same][:4], r[~same][:4], m[~same][:4], v[~same][:4])
     assert all(b.guards_intact() for b in bufs)
     print("[gpu-direction] %s n=%d beta1=%g eps=%g same" % (kind, n, beta1, eps), flush=True)
+
+
+@pytest.mark.parametrize("beta2,scale,lo,hi", [(2.0 ** -30, 0, -100, 60), (1.0 - 2.0 ** -24, 24, 36, 60)])
+def test_square_root_of_every_float_of_the_short_sequence(beta2, scale, lo, hi):
+    # every second moment w of the short sequence's range [2^-100, 2^60) as its own root's argument (1 - beta2
+    # rounds to 1), and those that 1 - beta2 = 2^-24 takes to [2^60, 2^84).  The root s is seen through the
+    # division by it: m is 1/16 of the correctly rounded root (numpy's, of two binades; the others are theirs
+    # times a power of two), and m / s is 1/16 exactly if and only if s is that root, since a quotient of
+    # different floats differs from 1 by at least 2^-24.
+    import torch
+    from paper_1910_02054_amd import binding as zb
+    mant = 1 << 23
+    one = np.float32(1.0).view(np.int32)
+    root = [torch.from_numpy(np.sqrt(np.arange(one, one + mant, dtype=np.int32).view(np.float32) *
+                                     np.float32(2 ** odd))).cuda() for odd in (0, 1)]
+    bits = torch.arange(mant, dtype=torch.int32, device="cuda")
+    per = 4                                                # binades a step
+    n = per * mant
+    g, p16 = (torch.zeros(n, dtype=torch.float16, device="cuda") for _ in range(2))
+    theta, m, v = (torch.empty(n, dtype=torch.float32, device="cuda") for _ in range(3))
+    for first in range(lo, hi, per):
+        theta.zero_()
+        for k in range(per):
+            e, part = first + k, slice(k * mant, (k + 1) * mant)
+            w = bits + ((e + 127) << 23)
+            if scale:                                      # beta2 times the next float above w rounds to w
+                v[part] = (w + 1).view(torch.float32)
+                assert first > lo or torch.equal(v[part] * np.float32(beta2).item(), w.view(torch.float32))
+            else:
+                v[part] = w.view(torch.float32) * 2.0 ** 30
+            # beta1 = 1/2: the kernel halves m, and the bias correction doubles it again
+            m[part] = root[e % 2] * 2.0 ** ((e - e % 2 + scale) // 2 - 4)
+        assert zb.zero_shard_step(g, theta, m, v, p16, 1.0, 0.5, beta2, 0.0, 0.0, 1, 1.0, 0.0) == 0
+        wrong = torch.nonzero(theta != -0.0625)
+        assert wrong.numel() == 0, (first, v[wrong[0]], theta[wrong[0]], wrong.numel())
+    print("[gpu-direction] roots of %d floats equal" % ((hi - lo) * mant), flush=True)

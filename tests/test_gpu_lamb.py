@@ -5,7 +5,7 @@ LAMB (You et al.) is one of the adaptive optimizers ZeRO's related work
 (Sec. 2.3) lists as made affordable by partitioning optimizer state.  Layer
 tables come from GPT-2-like shapes of ZeRO's evaluation (Sec. 10), cut at the
 rank's shard; small and ragged tables cover layers of 1..3 elements, layers
-that cross tiles, misaligned views and the scalar path.  The bar is the Adam
+that cross tiles, and views misaligned alike and each its own way.  The bar is the Adam
 path's: master/m/v within max|d| <= 1e-6 * max(1, |x|), fp16 within 1 ulp,
 skip flags and loss-scale sequence exact, guard canaries intact.
 """
@@ -130,7 +130,7 @@ def _random_layers(rng, n, small=False):
     (4099, True, (3,) * 5),
     (100_003, True, (0,) * 5),
     (100_003, False, (3,) * 5),
-    (100_003, True, (0, 1, 2, 3, 0)),   # mixed misalignment: scalar path
+    (100_003, True, (0, 1, 2, 3, 0)),   # mixed misalignment
     (1_000_003, False, (1,) * 5),
 ])
 def test_lamb_random_layer_tables(env, n, small, shifts):

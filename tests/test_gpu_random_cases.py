@@ -1,7 +1,7 @@
 """Seeded randomized differential tests on the GPU.
 
 Many small shard steps with random lengths (0 to 300,000), array alignments
-(equal shifts: vector path with a head; unequal shifts: scalar path), Adam
+(equal and unequal shifts: vectors from the master array's first line), Adam
 hyperparameters (lr including 0, beta1 and beta2 including 0, eps, decoupled
 weight decay), step t, loss scales (powers of two and not), clip thresholds
 (off, binding, never reached), warm or cold moments and injected inf/NaN

@@ -1,16 +1,16 @@
 """GPU parity of the one-launch small-shard step.
 
 zero_shard_step takes a single launch for shards small enough for one
-resident grid (about 1.5 million elements on MI355X) whose five arrays share
-one misalignment: the gradient statistics, a grid barrier and the fused Adam
-update in one kernel (Sec. 5.1-5.2 shard step, Sec. 3.1 mixed-precision
-Adam).  Checked against the oracle at every step: lengths that select each
-vectors-per-thread variant (the 1,048,576-element tiny workload shard among
-them), lengths past the one-launch limit (the statistics and update kernels),
+resident grid (about 1.5 million elements on MI355X) whose fp32 arrays share
+one misalignment: the gradient statistics, an exchange of the workgroups' sums
+and the fused Adam update in one kernel (Sec. 5.1-5.2 shard step, Sec. 3.1
+mixed-precision Adam).  Checked against the oracle at every step: lengths of one
+workgroup to a full grid of several tiles each (the 1,048,576-element tiny
+workload shard among them), lengths past the one-launch limit (the statistics and update kernels),
 every element misalignment, a ragged tail, overflow at the first, middle and
 last element (nothing written, the skip decision exact), clipping on and off,
 hundreds of back-to-back steps without a host synchronisation between them
-(the barrier counter's arithmetic), and steps on two streams from two
+(the exchange slots that one launch fills and the next empties), and steps on two streams from two
 threads.
 """
 import os
@@ -136,8 +136,8 @@ def test_small_step_clipping_and_decay(env, clip, wd):
 
 
 def test_back_to_back_steps_without_synchronisation(env):
-    # 300 steps queued one after another: each launch's barrier target is the counter's
-    # arrivals so far plus its grid, so a miscount would deadlock-then-abort or pass early
+    # 300 steps queued one after another: each launch fills one set of slots and empties the
+    # other, so a slot left over from an earlier launch would be taken for this one's sum
     torch, zb, dev = env
     n, steps = 65_536 + 5, 300
     _, theta, m, v = workloads.random_case(4600, n)
@@ -199,8 +199,7 @@ def test_two_streams_two_threads(env):
 
 
 def test_resident_small_step_replays_from_a_graph(env):
-    # the resident step on a small shard is one launch whose barrier words belong to its
-    # record: captured into a graph (with no eager call before) and replayed, each replay is the
+    # the resident step on a small shard, whose statistics slots belong to its record: captured into a graph (with no eager call before) and replayed, each replay is the
     # next step, equal to eager resident steps on the same inputs and following the oracle,
     # its loss scaler included (an overflow at the third step)
     torch, zb, dev = env
@@ -249,8 +248,8 @@ def test_resident_small_step_replays_from_a_graph(env):
 
 
 def test_alternating_grid_sizes_on_one_stream(env):
-    # shards whose one-launch grids have 2 to 512 workgroups, stepped in turn on one stream:
-    # the barrier words each launch leaves behind must serve the next launch of any size
+    # shards whose one-launch grids have 1 to 256 workgroups, stepped in turn on one stream:
+    # the slots each launch leaves behind must serve the next launch of any size
     torch, zb, dev = env
     sizes = [4377, 1_048_576, 9, 65_537, 4377, 300_001, 1_048_576, 5]
     cases = {}

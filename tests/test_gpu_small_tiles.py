@@ -45,6 +45,7 @@ def test_small_step_tile_and_grid_edges(n, overflow):
             st = zb.zero_shard_last_step_stats()
             assert flag == skip == (1 if overflow and g16.size == n else 0)
             assert st.skipped == skip and (skip or st.mult == sc.mult)
+            assert st.path == (1 if g16.size <= 3 * G * T else 0), (g16.size, st.path)
     torch.cuda.synchronize()
     for bufs, _, ref in sets:
         d = H.compare_state([b.download() for b in bufs[1:]], ref)

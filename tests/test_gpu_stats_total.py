@@ -1,5 +1,5 @@
 """GPU test of the statistics pass's total at the edges of its two levels: one
-workgroup (1024 elements), a group of 64, the first workgroup of a second group,
+workgroup (2048 elements), a group of 64, the first workgroup of a second group,
 a full grid and a grid whose last group is short; called twice on one stream, so
 the slots that the first call emptied serve the second.  The oracle sums
 exactly; the kernel's fp64 sums of a few thousand exact squares per workgroup are
