@@ -17,9 +17,9 @@
  *     negative = error (ZERO_E*); zero_last_error() then describes it.
  *   - Array arguments are DEVICE pointers owned by the caller.  The library
  *     never allocates, frees or retains them and touches exactly [0, n).
- *   - The library owns a small per-(device, stream) workspace (per-workgroup
- *     partial sums, one result record, exchange slots, two pinned host
- *     words: about 68 KiB of device memory), allocated on a stream's first
+ *   - The library owns a small per-(device, stream) workspace (a slot for each
+ *     workgroup's sum, one result record, the one-launch step's exchange slots,
+ *     two pinned host words: 37 KiB of device memory), allocated on a stream's first
  *     call and held until zero_stream_release(stream) or the process ends, so
  *     the library's memory grows with the number of distinct streams it has
  *     seen.  Its size does not depend on n (constant-size buffers, Sec. 6.2).
@@ -134,8 +134,8 @@ int zero_shard_step(const uint16_t* grad16, float* master32, float* m32, float* 
  * harnesses that forbid the allocator): zero_shard_step with the same
  * arguments, checks, kernels, results and return values, that calls no
  * hipMalloc, hipFree or other allocating routine.  Its workspace (statistics
- * partials for up to 4096 workgroups, the one-launch step's exchange slots and
- * the result: 69 KiB) is one fixed device array per GPU, held by
+ * slots for up to 4096 workgroups, the one-launch step's exchange slots and
+ * the result: 37 KiB) is one fixed device array per GPU, held by
  * every GPU the library runs on until the process ends; n up to 2^40 (the
  * library's limit, ZERO_EINVAL above it) needs no more.  Differences: the call
  * returns once the whole step (update included) has completed on `stream`,
@@ -220,8 +220,8 @@ int zero_shard_apply_async(const uint16_t* grad16, float* master32, float* m32, 
  *   step just taken.  A record whose hyperparameters are outside the ranges
  *   zero_shard_step accepts (or min_scale not finite and > 0) is not a valid
  *   step: nothing is written and only its `skipped` field changes, to -1.
- * Workspace: each state record has its own (statistics partials, result
- * record, constants; about 64 KiB of device memory), allocated on the first
+ * Workspace: each state record has its own (statistics slots, result
+ * record, constants; 33 KiB of device memory), allocated on the first
  * step taken with it and held until zero_resident_release(state) or the
  * process ends.  Eager calls and graph replays with that record use it, and
  * nothing else does; so steps with one record must not overlap each other
@@ -406,9 +406,12 @@ int zero_model_state_bytes(double psi, double nd, int32_t stage, double k, doubl
  * [seg_off[s], seg_off[s+1]) of the shard.  n = 0 requires n_seg = 0.  A
  * layer that continues on a neighbouring rank's shard appears clipped to this
  * shard; its norms then need the split-phase calls below.  The plan is tied to
- * the device current at creation and owns device memory (about 16 bytes per
- * 256 elements plus 32 bytes per layer, and the work lists, built per array
- * alignment on first use); zero_lamb_plan_destroy waits for the plan's own
+ * the device current at creation and owns device memory: 16 bytes per 512
+ * elements and 48 per layer, 36 KiB of exchange slots for shards of up to about a
+ * million elements, and the work lists (24 bytes per 512 elements and 52 per
+ * layer), one for each position of master32 in its 128-byte line (32 at most)
+ * that calls come with, made by the first, also while its stream is captured;
+ * zero_lamb_plan_destroy waits for the plan's own
  * queued work and frees it.  Calls on one plan are serialised by the library:
  * each call's last kernel completes a plan-owned event, and a call on a
  * different stream from the plan's previous one makes its stream wait for
@@ -427,7 +430,9 @@ int zero_lamb_plan_destroy(zero_lamb_plan_t* plan);
  * with n taken from the plan; phi_lo >= 0, phi_hi >= phi_lo (may be +inf),
  * neither NaN.  Shards of up to about a million elements whose layers are not
  * too fine (a workgroup of 1024 to 4096 elements meets at most 8) take a single
- * launch, as zero_shard_step's small shards do and under the same residency.  The library's per-layer sums live in the plan. */
+ * launch, as zero_shard_step's small shards do and under the same residency;
+ * one that is given up writes nothing and the kernels of larger shards take the
+ * step.  The library's per-layer sums live in the plan. */
 int zero_lamb_step(const zero_lamb_plan_t* plan, const uint16_t* grad16, float* master32, float* m32, float* v32,
                    uint16_t* param16_out, double lr, double beta1, double beta2, double eps, double weight_decay,
                    int64_t step, double loss_scale, double clip, double phi_lo, double phi_hi, void* stream);

@@ -32,9 +32,11 @@ namespace zs {
 // kernel sequence moves 42) behind two exchanges.  Against the kernel sequence,
 // whole synchronous steps: 2000 elements 21.0 -> 14.0 us, 200K 21.2 -> 15.2, 500K
 // 21.9 -> 15.9, 1M (65 layers) 23.5 -> 17.9.  256-thread workgroups, because
-// at four tiles (120 registers) a quarter of the chip holds 256 of them and so
+// at four tiles (121 registers) a quarter of the chip holds 256 of them and so
 // 1M elements; the arithmetic of 16 elements a thread, one wave per SIMD, is then
-// about half of the kernel's 17 us.
+// about half of the kernel's time.  That register limit is the size limit: a step on
+// 1,048,576 elements of 64 layers takes 15.2 us, one on 1,048,700, in the kernel
+// sequence, 21.4 (1.5M 23.3).
 // ---------------------------------------------------------------------------
 constexpr int kLambSmallBlock = 256;
 constexpr int kLambPieces = 8;          // the most layer pieces of a workgroup
@@ -42,6 +44,7 @@ constexpr int kLambSmallItems = 1024;   // the most layer pieces of a shard
 constexpr int kLambSmallWords = kSmallSlots + 2 * kLambSmallItems;  // one set of slots
 
 static_assert(kSmallSlots <= kLambSmallBlock, "a thread reads at most one gradient slot");
+static_assert(2 * kLambSmallWords * sizeof(uint64_t) == 36 * 1024, "the size that the interface states");
 
 // Waves per SIMD that the registers of k_lamb_small<V> leave: a quarter of the
 // chip then holds 256 workgroups at every V.

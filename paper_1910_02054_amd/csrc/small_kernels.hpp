@@ -35,13 +35,13 @@ namespace zs {
 // in hand (20.3 against 19.5 us on 3M), gained nothing; loading the gradient
 // tile by tile instead of at once costs 0.7 us on 600K and more.
 //
-// A slot (see shard_kernels.hpp) is filled once, by a compare-and-swap.  Two sets of slots alternate from launch to launch of a
-// stream, and each launch empties the other set.  The wait is bounded: a
-// workgroup that gives up on an empty slot fills it with kSlotMark in the
-// owner's place.  Each slot has one final value that everybody reads, so either
-// every workgroup updates or none does; then nothing is written, the total is
-// not published and the host's wait ends with an error once the stream is
-// idle.
+// A slot (see shard_kernels.hpp) is filled once, by a compare-and-swap.  Two sets
+// of slots alternate from launch to launch of a stream, and each launch empties
+// the other set.  The wait is bounded: a workgroup that gives up on an empty slot
+// fills it with kSlotMark in the owner's place.  Each slot has one final value that
+// everybody reads, so either every workgroup updates or none does; then nothing is
+// written, the total is not published, and the host, which finds the stream idle
+// without it, empties the slots and launches the kernel sequence.
 // ---------------------------------------------------------------------------
 constexpr int kSmallBlock = 512;
 constexpr int kSmallSlots = 256;                       // the largest grid

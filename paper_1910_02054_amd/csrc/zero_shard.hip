@@ -70,10 +70,13 @@ constexpr bool kCopyNTL = true, kCopyNTS = true, kCopyXCD = false;
 // One-launch small-shard step (k_small_step): shards whose fp32 arrays share
 // one misalignment (the fp16 arrays may start at any element) and that give a
 // workgroup at most zs::kSmallTiles tiles: 1.5M elements on a full grid of 256
-// workgroups, the limit that the interface states.  Up to there the grid holds
-// the chip about as well as the update's own launch and saves two launches:
-// 1.5M elements take 13.1 us a step, 15.4 in the kernel sequence.  (With more
-// tiles the gain is gone at 8M: 44.1 against 44.6 us.)
+// workgroups, the limit that the interface states: there a step takes 11.0 us, and
+// the sequence 14.2 just past it.  It is not where the single launch stops being
+// the faster one.  In one launch and in the sequence, whole steps in us with the
+// gradient of 4, 6, 8 and 16 tiles in registers: 2M 14.2 and 14.3, 3M 16.9 and
+// 19.1, 4M 22.7 and 24.8, 5.9M 36.5 and 32.4, 8M 45.7 and 42.9.  Above six tiles
+// (3.1M) the registers spill, and the smaller sizes pay for that: 1.5M takes 11.1 us
+// in a kernel of six tiles, 12.4 in one of eight, 16.6 in one of sixteen.
 // A grid takes at most 1/share of the device's co-resident capacity, where
 // share is the number of hardware queues the process may use (at least
 // kSmallCapShare; HIP gives a process four unless GPU_MAX_HW_QUEUES says
@@ -753,6 +756,12 @@ constexpr size_t kScratchRes = kScratchSlots + sizeof(uint64_t) * zs::kSlotWords
 constexpr size_t kScratchHost = kScratchRes + 256;
 constexpr size_t kScratchBytes = kScratchHost + 256;
 static_assert(kScratchRes % 256 == 0 && sizeof(zs::Result) <= 256, "scratch layout");
+// the sizes that the interface states
+static_assert(kScratchBytes == 37 * 1024, "zero_shard_step_noalloc's workspace");
+static_assert(sizeof(uint64_t) * (zs::kStatsSlots + zs::kSlotWords) + sizeof(zs::Result) <= 37 * 1024,
+              "a stream's workspace");
+static_assert(sizeof(uint64_t) * zs::kStatsSlots + sizeof(zs::Result) + sizeof(zs::AdamConst) <= 33 * 1024,
+              "a state record's workspace");
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
