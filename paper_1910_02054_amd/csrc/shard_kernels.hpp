@@ -8,7 +8,7 @@
 // Two kernels run per step, all HBM-streaming (no dense contraction, so no
 // MFMA):
 //   k_stats     one read of the fp16 gradients; per-workgroup fp64 sum of the
-//               exact fp32 squares, totalled by the last workgroup.  The sum is
+//               exact fp32 squares, totalled by one of them (close_slots).  The sum is
 //               non-finite iff some gradient is inf or NaN, which is the
 //               overflow test (every finite square is below 2^32, so no finite
 //               sum over fewer than 2^990 elements overflows fp64).  From it the

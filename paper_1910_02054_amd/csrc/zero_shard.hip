@@ -1241,7 +1241,7 @@ int zero_shard_step_resident(const uint16_t* grad16, float* master32, float* m32
         return prof;
     if (prof)
         prof_record(pr.start, stream, &pr);
-    // statistics, whose last workgroup fills the result record and the constants and advances the
+    // statistics, whose closing workgroup fills the result record and the constants and advances the
     // state record's loss-scale schedule (an empty shard's total is 0), then the update
     rc = launch_stats_into(info, &ws->stats, grad16, n, pl, zs::FinishResident{state, ws->res, ws->dconst, seq, {}},
                            stream);
