@@ -666,6 +666,10 @@ int wait_result(Ctx* ctx, uint32_t seq, hipStream_t stream, double loss_scale, d
             if (e == hipSuccess) {  // everything queued has finished
                 if (ready())
                     break;
+                // a step taken for given up is run again: only past a full synchronisation
+                HIP_TRY(hipStreamSynchronize(stream));
+                if (ready())
+                    break;
                 // a one-launch step was given up: its slots are emptied before the next launch
                 ctx->slots.ready = false;
                 if (given_up)
